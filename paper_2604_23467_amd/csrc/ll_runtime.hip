@@ -20,6 +20,7 @@
 #include "prefill_kernels.h"
 #include "prefill_skinny.h"
 #include "prefill_gemm.h"
+#include "prefill_tile.h"
 #include "batch_kernels.h"
 
 // Scratch of ll_prefill_static(): the buffers a short prefill needs besides its inputs and outputs
@@ -97,6 +98,19 @@ int prompt_bucket(int n) {   // smallest of {64,128,256,512,1024} holding n rows
   return b;
 }
 
+// Does the instance hold the fragment-major weight copy?  (config_ok() admits only shapes that fit its
+// 16-row blocks: d_model is a multiple of 64.)
+bool has_copy(const ll_config& c) { return !(c.flags & LL_FLAG_LEAN_WORKSPACE); }
+
+// Bucket of a prompt (or chunk) of n > 32 rows.  Reading the weight copy, the projections come in row tiles that
+// also suit 192 and 384 rows: a prompt of 350 tokens in a 512-row bucket computes 512 rows' worth of tiles
+// (4.05 against 4.9 ms at the 7B shape for all 32 layers' projections at 384 rows).
+int bucket_of(const ll_config& c, int n) {
+  if (has_copy(c) && n > 128 && n <= 192) return 192;
+  if (has_copy(c) && n > 256 && n <= 384) return 384;
+  return prompt_bucket(n);
+}
+
 // Shapes the short-prompt kernels accept: 16-row blocks that keep RoPE pairs / gate-up pairs together
 bool skinny_ok(const ll_config& c) {
   return c.d_model % 16 == 0 && c.head_dim % 16 == 0 && c.ffn_hidden % 8 == 0;
@@ -149,6 +163,127 @@ GemmPlan gemm_plan(int N, int K, int nmat, int Mb, int ldc) {
     p.max_slices = ks;
   }
   return p;
+}
+
+// ---- projections of 33..1024 rows from the fragment-major weight copy (prefill_tile.h) ----
+// One list of instantiations: X(kind, mode, row waves, K waves, row blocks, column blocks, K steps per stage, ring
+// stages or look-ahead, weights used once), kind T = pf_tile_kernel, S = pf_stream_kernel (four K waves).
+struct TileShape {
+  char kind;
+  int wm, wk, mt, nb, s32, ns;
+  bool wnt;
+};
+constexpr int tile_rows(const TileShape& t) { return 32 * t.wm * t.mt; }
+
+// Which tile a projection takes at a bucket of Mb rows.  `wide_k`: the down projection's long K loop can be cut into
+// more pieces of wider tiles (512 rows: 51 us in 4 pieces of 128 columns, 62 us in 2 of 64), the O projection
+// is better off with fewer slices (25.3 against 27.3 us).  Each line is the fastest of those measured at the 7B
+// shape; the rule behind them: one round of 256 workgroups, tiles as square as that allows, K split
+// between the waves while the rows are few.  Measured there (us, Q/K/V with RoPE and cache write / O / gate/up with
+// SwiGLU / down): 64 rows 26.0 / 9.9 / 34.3 / 20.3, 128: 29.9 / 12.9 / 40.4 / 25.5, 192: 37.4 / 16.5 / 50.2 / 31.1,
+// 256: 39.8 / 18.7 / 57.0 / 36.0, 384: 50.9 / 21.7 / 78.6 / 43.7, 512: 59.3 / 25.3 / 87.2 / 50.7,
+// 1024: 97.5 / 39.9 / 164.8 / 87.0.
+constexpr TileShape tile_shape(int mode, int Mb, bool wide_k) {
+  if (mode == SK_QKV) {
+    return Mb <= 64 ? TileShape{'S', 1, 4, 2, 2, 0, 8, true} : Mb <= 128 ? TileShape{'S', 1, 4, 2, 3, 0, 8, false}
+         : Mb <= 192 ? TileShape{'S', 1, 4, 3, 3, 0, 8, false} : Mb <= 256 ? TileShape{'T', 2, 2, 2, 3, 8, 3, false}
+         : Mb <= 384 ? TileShape{'T', 2, 2, 3, 3, 8, 3, false} : Mb <= 512 ? TileShape{'T', 4, 1, 2, 3, 8, 3, false}
+         : TileShape{'T', 4, 1, 2, 6, 4, 3, false};
+  }
+  if (mode == SK_GATEUP) {
+    return Mb <= 64 ? TileShape{'S', 1, 4, 2, 3, 0, 8, true} : Mb <= 128 ? TileShape{'T', 4, 1, 1, 3, 8, 3, true}
+         : Mb <= 192 ? TileShape{'T', 2, 2, 3, 3, 8, 3, true} : Mb <= 256 ? TileShape{'T', 4, 1, 2, 3, 8, 3, true}
+         : Mb <= 384 ? TileShape{'T', 4, 1, 3, 3, 8, 3, true} : TileShape{'T', 4, 1, 2, 6, 4, 3, false};
+  }
+  if (Mb <= 64) return wide_k ? TileShape{'S', 1, 4, 2, 2, 0, 8, true} : TileShape{'S', 1, 4, 2, 1, 0, 8, true};
+  if (Mb <= 128) return wide_k ? TileShape{'T', 2, 2, 2, 2, 8, 4, true} : TileShape{'S', 1, 4, 4, 2, 0, 6, true};
+  if (Mb <= 192) return TileShape{'T', 2, 2, 3, 2, 8, 4, true};
+  if (Mb <= 256) return TileShape{'T', 4, 1, 2, 2, 8, 4, true};
+  if (Mb <= 384) return wide_k ? TileShape{'T', 2, 2, 3, 4, 4, 4, false} : TileShape{'T', 2, 2, 3, 2, 8, 4, false};
+  if (Mb <= 512 && !wide_k) return TileShape{'T', 4, 1, 2, 2, 8, 4, false};
+  return TileShape{'T', 4, 1, 2, 4, 4, 4, false};
+}
+bool tile_wide_k(int N, int K) { return K >= 2 * N; }
+
+// Pieces the K loop of a residual projection is cut into: what fills one round of workgroups, none empty
+int tile_pieces(int N, int K, int Mb) {
+  const TileShape t = tile_shape(SK_RES, Mb, tile_wide_k(N, K));
+  const int ctiles = (skinny_units(SK_RES, N) + 2 * t.nb - 1) / (2 * t.nb), mtiles = Mb / tile_rows(t);
+  const int ksteps = (K + 31) / 32, stages = t.kind == 'T' ? (ksteps + t.s32 - 1) / t.s32 : (ksteps + 7) / 8;
+  int ks = num_cus() / (ctiles * mtiles);
+  ks = ks < 1 ? 1 : ks > 8 ? 8 : ks;
+  if (ks > stages) ks = stages;
+  const int q = (stages + ks - 1) / ks;
+  return (stages + q - 1) / q;
+}
+
+struct TileLaunch {
+  hipStream_t s;          // null kernel arguments and init != 0: raise the LDS limit instead of launching
+  const TileArgs* a;
+  int grid;
+  hipError_t err;
+  bool init;
+};
+template <int MODE, int I>
+void tile_go(TileLaunch& L) {
+  constexpr int kRows[] = {64, 128, 192, 256, 384, 512, 1024};
+  constexpr TileShape t = tile_shape(MODE, kRows[I >> 1], (I & 1) != 0);
+  if constexpr (t.kind == 'T') {
+    auto k = pf_tile_kernel<MODE, t.wm, t.wk, t.mt, t.nb, t.s32, t.ns, t.wnt>;
+    constexpr int lds = PT_LDS_BYTES(t.nb, t.s32, t.ns);
+    static_assert(lds <= 160 * 1024 && (t.wk == 1 || lds >= t.wm * t.mt * t.nb * 4096), "ring and exchange fit the LDS");
+    if (L.init) L.err = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    else hipLaunchKernelGGL(k, dim3(L.grid), dim3(PT_THREADS), lds, L.s, *L.a);
+  } else {
+    auto k = pf_stream_kernel<MODE, t.mt, t.nb, t.ns, t.wnt>;
+    constexpr int lds = PS_LDS_BYTES(t.mt, t.nb);
+    static_assert(lds <= 160 * 1024, "partial sums fit the LDS");
+    if (L.init) L.err = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    else hipLaunchKernelGGL(k, dim3(L.grid), dim3(PT_THREADS), lds, L.s, *L.a);
+  }
+}
+template <int MODE>
+void tile_dispatch(TileLaunch& L, int Mb, bool wide_k) {
+  const int i = (Mb <= 64 ? 0 : Mb <= 128 ? 1 : Mb <= 192 ? 2 : Mb <= 256 ? 3 : Mb <= 384 ? 4 : Mb <= 512 ? 5 : 6) * 2 + wide_k;
+  switch (i) {
+    case 0: return tile_go<MODE, 0>(L);
+    case 1: return tile_go<MODE, 1>(L);
+    case 2: return tile_go<MODE, 2>(L);
+    case 3: return tile_go<MODE, 3>(L);
+    case 4: return tile_go<MODE, 4>(L);
+    case 5: return tile_go<MODE, 5>(L);
+    case 6: return tile_go<MODE, 6>(L);
+    case 7: return tile_go<MODE, 7>(L);
+    case 8: return tile_go<MODE, 8>(L);
+    case 9: return tile_go<MODE, 9>(L);
+    case 10: return tile_go<MODE, 10>(L);
+    case 11: return tile_go<MODE, 11>(L);
+    case 12: return tile_go<MODE, 12>(L);
+    default: return tile_go<MODE, 13>(L);
+  }
+}
+template <int MODE>
+void launch_tile(hipStream_t s, TileArgs a, int Mb, int ks) {
+  const bool wide = MODE == SK_RES && tile_wide_k(a.N, a.K);
+  const TileShape t = tile_shape(MODE, Mb, wide);
+  a.tb = Mb / 16;
+  a.mtiles = Mb / tile_rows(t);
+  a.ctiles = (pt_units(MODE, a.N) + 2 * t.nb - 1) / (2 * t.nb);
+  a.ks = ks;
+  TileLaunch L{s, &a, (a.ctiles * ks + 7) / 8 * 8 * a.mtiles, hipSuccess, false};    // column tiles are dealt to the 8 XCDs
+  tile_dispatch<MODE>(L, Mb, wide);
+}
+// Raises the dynamic LDS limit of every instantiation (before anything is captured)
+hipError_t tile_init() {
+  for (int Mb : {64, 128, 192, 256, 384, 512, 1024})
+    for (int wide = 0; wide < 2; ++wide) {
+      TileLaunch L{nullptr, nullptr, 0, hipSuccess, true};
+      tile_dispatch<SK_QKV>(L, Mb, wide != 0);
+      if (L.err == hipSuccess) tile_dispatch<SK_GATEUP>(L, Mb, wide != 0);
+      if (L.err == hipSuccess) tile_dispatch<SK_RES>(L, Mb, wide != 0);
+      if (L.err != hipSuccess) return L.err;
+    }
+  return hipSuccess;
 }
 
 struct Layout {
@@ -214,7 +349,11 @@ Layout make_layout(const ll_config& c) {
   L.pf_q = take(M * d * 2);
   L.pf_o = take(M * ((d + 31) / 32 * 32) * 2);
   size_t part = 0;                                       // slices of the widest GEMM output of any bucket
-  for (int mb = 64; mb <= L.mb_max; mb <<= 1) {
+  if (has_copy(c)) {
+    for (int mb : {64, 128, 192, 256, 384, 512, 1024})
+      if (mb <= L.mb_max)
+        part = std::max(part, (size_t)std::max(tile_pieces(d, d, mb), tile_pieces(d, F, mb)) * mb * d);
+  } else for (int mb = 64; mb <= L.mb_max; mb <<= 1) {
     const GemmPlan plans[4] = {gemm_plan(d, d, 3, mb, 3 * d), gemm_plan(d, d, 1, mb, d),
                                gemm_plan(F, d, 2, mb, 2 * F), gemm_plan(d, F, 1, mb, d)};
     for (const GemmPlan& p : plans) part = std::max(part, p.max_slices * p.map.slice_floats);
@@ -232,7 +371,7 @@ Layout make_layout(const ll_config& c) {
   L.mk_trace = take((size_t)(5 * c.n_layers + 2) * 8 * 8);
   // Second copy of the weights in the short-prompt kernels' operand order (see sk_shuffle_kernel):
   // [layer][q,k,v | o | gate,up | down] then the LM head, 1 KB per 16-row block and 32-wide K step.
-  if (skinny_ok(c) && !(c.flags & LL_FLAG_LEAN_WORKSPACE)) {
+  if (has_copy(c)) {
     const size_t kd = (d + 31) / 32, kf = (F + 31) / 32;
     L.wf_qkv = 0;
     L.wf_o = L.wf_qkv + align_up((size_t)skinny_units(SK_QKV, c.d_model) * kd * 1024);
@@ -603,7 +742,7 @@ void enqueue_decode(Instance* I, hipStream_t s) {
 // Projection GEMM A W_z^T into the slice buffer; the returned map tells the consuming kernel
 // which slices to add up for which column.
 SliceMap launch_gemm(Instance* I, hipStream_t s, const PfBuffers& B, const half_t* A, const void* w0, const void* w1,
-                     const void* w2, int nmat, int ldc, int N, int K, int Mb, const half_t* wf = nullptr) {
+                     const void* w2, int nmat, int ldc, int N, int K, int Mb) {
   const GemmPlan p = gemm_plan(N, K, nmat, Mb, ldc);
   GemmArgs ga{};
   ga.A = A;
@@ -614,20 +753,11 @@ SliceMap launch_gemm(Instance* I, hipStream_t s, const PfBuffers& B, const half_
   ga.N = N; ga.K = K; ga.ldc = ldc; ga.nmat = nmat;
   ga.mtiles = p.mtiles; ga.runs = p.runs; ga.map = p.map;
   dim3 grid((p.runs + 7) / 8 * 8 * p.mtiles);      // runs are dealt to the 8 XCDs
-  ga.Wf = wf;
   const bool once = p.mtiles == 1;      // a single row tile: every weight byte is used once
-  if (gemm_bm(Mb, nmat) == 128 && wf && nmat == 1 && once)
-    hipLaunchKernelGGL((pf_gemm_kernel<128, 3, 2, 4, 64, 1, true, true>), grid, dim3(PF_GEMM_THREADS_OF(2, 4)), PF_GEMM_LDS_BYTES(128, 3, 64), s, ga);
-  else if (gemm_bm(Mb, nmat) == 128 && wf && nmat == 1)
+  if (gemm_bm(Mb, nmat) == 128 && once)
     hipLaunchKernelGGL((pf_gemm_kernel<128, 3, 2, 4, 64, 1, true>), grid, dim3(PF_GEMM_THREADS_OF(2, 4)), PF_GEMM_LDS_BYTES(128, 3, 64), s, ga);
-  else if (gemm_bm(Mb, nmat) == 128 && once)
-    hipLaunchKernelGGL((pf_gemm_kernel<128, 3, 2, 4, 64, 1, false, true>), grid, dim3(PF_GEMM_THREADS_OF(2, 4)), PF_GEMM_LDS_BYTES(128, 3, 64), s, ga);
   else if (gemm_bm(Mb, nmat) == 128)
     hipLaunchKernelGGL((pf_gemm_kernel<128, 3, 2, 4, 64>), grid, dim3(PF_GEMM_THREADS_OF(2, 4)), PF_GEMM_LDS_BYTES(128, 3, 64), s, ga);
-  else if (wf && nmat == 1 && !once)
-    hipLaunchKernelGGL((pf_gemm_kernel<64, 3, 1, 4, 64, 1, true, false>), grid, dim3(PF_GEMM_THREADS_OF(1, 4)), PF_GEMM_LDS_BYTES(64, 3, 64), s, ga);
-  else if (wf && nmat == 1)
-    hipLaunchKernelGGL((pf_gemm_kernel<64, 3, 1, 4, 64, 1, true>), grid, dim3(PF_GEMM_THREADS_OF(1, 4)), PF_GEMM_LDS_BYTES(64, 3, 64), s, ga);
   else
     hipLaunchKernelGGL((pf_gemm_kernel<64, 3, 1, 4, 64>), grid, dim3(PF_GEMM_THREADS_OF(1, 4)), PF_GEMM_LDS_BYTES(64, 3, 64), s, ga);
   return p.map;
@@ -714,7 +844,7 @@ void enqueue_prefill_skinny(Instance* I, hipStream_t s, const PfBuffers& B, int 
 // Prefill attention of layer l for a bucket of Mb >= 64 rows: the longer the prompt, the more
 // key groups share a query block (a chunk of a long prompt attends everything cached before it)
 template <int HD>
-void launch_attn_hd(Instance* I, hipStream_t s, const PfBuffers& B, int l, int Mb) {
+void launch_attn_hd(Instance* I, hipStream_t s, const PfBuffers& B, int l, int Mb, int tb) {
   const ll_config& c = I->cfg;
   dim3 grid(c.n_heads, Mb / 64);
   const half_t* Qh = B.Q;
@@ -722,23 +852,67 @@ void launch_attn_hd(Instance* I, hipStream_t s, const PfBuffers& B, int l, int M
   const int groups = (Mb >= 256 || c.max_seq - 1 > kMaxPromptBucket) ? 4 : Mb >= 128 ? 2 : 1;
   if (groups == 4)
     hipLaunchKernelGGL((pf_attn_kernel<HD, 4>), grid, dim3(512), PF_ATTN_LDS_BYTES(HD, 4), s, Qh, I->kcache(l),
-                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, 0);
+                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, tb);
   else if (groups == 2)
     hipLaunchKernelGGL((pf_attn_kernel<HD, 2>), grid, dim3(256), PF_ATTN_LDS_BYTES(HD, 2), s, Qh, I->kcache(l),
-                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, 0);
+                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, tb);
   else
     hipLaunchKernelGGL((pf_attn_kernel<HD, 1>), grid, dim3(128), PF_ATTN_LDS_BYTES(HD, 1), s, Qh, I->kcache(l),
-                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, 0);
+                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, tb);
 }
 
-void launch_attn(Instance* I, hipStream_t s, const PfBuffers& B, int l, int Mb) {
-  if (I->cfg.head_dim == 128) launch_attn_hd<128>(I, s, B, l, Mb);
-  else launch_attn_hd<64>(I, s, B, l, Mb);
+// tb: token blocks of the output's fragment-major layout, 0 for row-major
+void launch_attn(Instance* I, hipStream_t s, const PfBuffers& B, int l, int Mb, int tb) {
+  if (I->cfg.head_dim == 128) launch_attn_hd<128>(I, s, B, l, Mb, tb);
+  else launch_attn_hd<64>(I, s, B, l, Mb, tb);
+}
+
+// Prompts (or chunks) of 33..1024 rows with the weight copy: per layer the norm (which adds the previous residual
+// projection's slices to X), Q/K/V with RoPE and cache write, attention, O, norm, gate/up with SwiGLU, down.
+void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb, bool with_head) {
+  const ll_config& c = I->cfg;
+  const int d = c.d_model, F = c.ffn_hidden, tb = Mb / 16;
+  const int ks_o = tile_pieces(d, d, Mb), ks_down = tile_pieces(d, F, Mb);
+  auto slices = [&](int ks) {                      // ks slices for every column, as the norm's slice sum counts them
+    SliceMap m{};
+    m.nslabs = ks; m.quota = 1; m.ntiles = (d + 255) / 256; m.N = d; m.slice_floats = (size_t)Mb * d;
+    return m;
+  };
+  hipLaunchKernelGGL(pf_embed_kernel, dim3(Mb, (d + LL_WG * 8 - 1) / (LL_WG * 8)), dim3(LL_WG), 0, s,
+                     (const half_t*)I->w.tok_emb, B.tokens, I->state(), B.X, d);
+  const float* part = nullptr;                     // slices still to be added to X
+  for (int l = 0; l < c.n_layers; ++l) {
+    const ll_layer_weights& W = I->layers[l];
+    hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, B.X, (const half_t*)W.attn_norm,
+                       B.Xn, d, c.rms_eps, I->state(), part, slices(ks_down), tb);
+    TileArgs a{};
+    a.st = I->state(); a.head_dim = c.head_dim; a.max_seq = c.max_seq;
+    a.A = B.Xn; a.Wf = I->wfrag(l, I->L.wf_qkv); a.N = d; a.K = d;
+    a.Q = B.Q; a.kc = I->kcache(l); a.vc = I->vcache(l); a.rope = I->at<float2>(I->L.rope);
+    launch_tile<SK_QKV>(s, a, Mb, 1);
+    launch_attn(I, s, B, l, Mb, tb);
+    a.C = B.part; a.slice_floats = (size_t)Mb * d;
+    a.A = B.O; a.Wf = I->wfrag(l, I->L.wf_o);
+    launch_tile<SK_RES>(s, a, Mb, ks_o);
+    hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, B.X, (const half_t*)W.ffn_norm,
+                       B.Xn, d, c.rms_eps, I->state(), B.part, slices(ks_o), tb);
+    a.A = B.Xn; a.Wf = I->wfrag(l, I->L.wf_gu); a.N = F; a.Hout = B.H;
+    launch_tile<SK_GATEUP>(s, a, Mb, 1);
+    a.A = B.H; a.Wf = I->wfrag(l, I->L.wf_down); a.N = d; a.K = F;
+    launch_tile<SK_RES>(s, a, Mb, ks_down);
+    part = B.part;
+  }
+  if (with_head) {             // (a chunk that is not the prompt's last needs nothing of X any more)
+    hipLaunchKernelGGL(pf_fold_kernel, dim3(Mb, (d + LL_WG * 4 - 1) / (LL_WG * 4)), dim3(LL_WG), 0, s, B.X,
+                       I->state(), part, slices(ks_down), d);
+    enqueue_head(I, s, B, B.X, 1, 1);
+  }
 }
 
 void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) {
   const PfBuffers& B = I->pf;
   if (Mb <= 32 && I->skinny) return enqueue_prefill_skinny(I, s, B, Mb, with_head);
+  if (has_copy(I->cfg)) return enqueue_prefill_tile(I, s, B, Mb, with_head);
   const ll_config& c = I->cfg;
   const int d = c.d_model, F = c.ffn_hidden;
   float* X = B.X;
@@ -756,15 +930,15 @@ void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) 
     hipLaunchKernelGGL(pf_rope_kv_kernel, dim3(Mb, (d / 8 + LL_WG - 1) / LL_WG), dim3(LL_WG), 0, s, P, qkv,
                        I->at<float2>(I->L.rope), I->state(), Qh, I->kcache(l), I->vcache(l), d,
                        c.head_dim, c.max_seq);
-    launch_attn(I, s, B, l, Mb);
-    res = launch_gemm(I, s, B, Oh, W.wo, nullptr, nullptr, 1, d, d, d, Mb, I->wfrag(l, I->L.wf_o));
+    launch_attn(I, s, B, l, Mb, 0);
+    res = launch_gemm(I, s, B, Oh, W.wo, nullptr, nullptr, 1, d, d, d, Mb);
     res_part = P;
     hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, X, (const half_t*)W.ffn_norm,
                        Xn, d, c.rms_eps, I->state(), res_part, res, 0);
     const SliceMap gu = launch_gemm(I, s, B, Xn, W.w_gate, W.w_up, nullptr, 2, 2 * F, F, d, Mb);
     hipLaunchKernelGGL(pf_swiglu_kernel, dim3(Mb, (F + LL_WG * 4 - 1) / (LL_WG * 4)), dim3(LL_WG), 0,
                        s, P, gu, I->state(), Hm, F);
-    res = launch_gemm(I, s, B, Hm, W.w_down, nullptr, nullptr, 1, d, d, F, Mb, I->wfrag(l, I->L.wf_down));
+    res = launch_gemm(I, s, B, Hm, W.w_down, nullptr, nullptr, 1, d, d, F, Mb);
   }
   if (with_head && res_part)    // (a chunk that is not the prompt's last needs nothing of X any more)
     hipLaunchKernelGGL(pf_fold_kernel, dim3(Mb, (d + LL_WG * 4 - 1) / (LL_WG * 4)), dim3(LL_WG), 0, s, X,
@@ -1137,27 +1311,16 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&bt_select_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, SMP_Z_WORDS * 4),
                    "hipFuncSetAttribute(batch select)")) return bail(rc);
-  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<128, 3, 2, 4, 64, 1, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(128, 3, 64)),
-                   "hipFuncSetAttribute(gemm 128, fragment-major weights)")) return bail(rc);
   if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<128, 3, 2, 4, 64>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(128, 3, 64)),
                    "hipFuncSetAttribute(gemm 128)")) return bail(rc);
-  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<128, 3, 2, 4, 64, 1, true, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(128, 3, 64)),
-                   "hipFuncSetAttribute(gemm 128, fragment-major weights used once)")) return bail(rc);
-  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<128, 3, 2, 4, 64, 1, false, true>),
+  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<128, 3, 2, 4, 64, 1, true>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(128, 3, 64)),
                    "hipFuncSetAttribute(gemm 128, weights used once)")) return bail(rc);
-  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<64, 3, 1, 4, 64, 1, true, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(64, 3, 64)),
-                   "hipFuncSetAttribute(gemm 64, fragment-major weights shared by two row tiles)")) return bail(rc);
   if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<64, 3, 1, 4, 64>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(64, 3, 64)),
                    "hipFuncSetAttribute(gemm 64)")) return bail(rc);
-  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<64, 3, 1, 4, 64, 1, true>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(64, 3, 64)),
-                   "hipFuncSetAttribute(gemm 64, fragment-major weights)")) return bail(rc);
+  if (!hip_or_bail(tile_init(), "hipFuncSetAttribute(prefill projections)")) return bail(rc);
   if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_attn_kernel<128, 4>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PF_ATTN_LDS_BYTES(128, 4)),
                    "hipFuncSetAttribute(attention 128 x 4)")) return bail(rc);
@@ -1216,7 +1379,8 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
 
   I->skinny = skinny_ok(*cfg);
   (void)num_cus();
-  for (int b = I->skinny ? 16 : 64; b <= L.mb_max; b <<= 1) I->pf_buckets.push_back(b);
+  for (int b : {16, 32, 64, 128, 192, 256, 384, 512, 1024})
+    if (b <= L.mb_max && (b > 32 ? bucket_of(*cfg, b) == b : I->skinny)) I->pf_buckets.push_back(b);
   // Opt-in: attention and O projection in one launch.  It needs the whole of W_o in the registers of one
   // round of workgroups (rows of at most 4096), at most two attention workgroups per head, and a CU
   // for every workgroup of the launch (the projection's wait needs them all resident).
@@ -1350,7 +1514,7 @@ int32_t ll_prefill(const int32_t* tokens, int32_t n) {
   for (int p0 = 0; p0 < n;) {
     const int m = n - p0 > I->L.mb_max ? I->L.mb_max : n - p0;
     const bool last = p0 + m == n;
-    const int Mb = (I->skinny && m <= 32) ? (m <= 16 ? 16 : 32) : prompt_bucket(m);
+    const int Mb = (I->skinny && m <= 32) ? (m <= 16 ? 16 : 32) : bucket_of(I->cfg, m);
     memset(hs, 0, sizeof(DevState));
     hs->pos = p0;
     hs->n_prompt = m;

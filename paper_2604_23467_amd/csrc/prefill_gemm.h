@@ -1,5 +1,6 @@
-// Prefill projection GEMM for gfx950, prompts of 33..512 tokens (Sec. IV-E / Table I, the upper
-// part of the TTFT range): C[M][ldc] (fp32) += A[M][K] (fp16 activations) * W_z[N][K]^T (fp16).
+// Prefill projection GEMM for gfx950 on the caller's row-major weights, prompts of 33..1024 rows (Sec. IV-E / Table I,
+// the upper part of the TTFT range) of instances without the fragment-major copy (LL_FLAG_LEAN_WORKSPACE;
+// with the copy prefill_tile.h takes its place): C[M][ldc] (fp32) += A[M][K] (fp16 activations) * W_z[N][K]^T (fp16).
 //
 // v_mfma_f32_32x32x16_f16, the full-rate fp16 matrix instruction of this chip (measured: 2.0
 // PFLOP/s with one wave per SIMD and 8 independent accumulators; the 16x16x32 form reaches
@@ -41,9 +42,6 @@
 struct GemmArgs {
   const half_t* A;        // [>= mtiles * BM rows][K]
   const half_t* W[3];
-  const half_t* Wf;       // optional: matrix 0 in the short-prompt kernels' fragment-major order (16-row blocks x
-                          // 32-wide K steps, 1 KB each, zero beyond K; see sk_shuffle_kernel with plain row blocks);
-                          // kernels instantiated with WFRAG read the weights from it in whole 1 KB pieces
   float* C;               // slices: [slice][rows][ldc]
   const DevState* st;
   const half_t* zeros;    // >= 16 bytes of zeros in global memory
@@ -89,9 +87,8 @@ struct GemmArgs {
 // tokens, slower at 128; four waves of 128 x 64 on this kernel: within 2 % either way.  A timing-only build
 // that never waits for the direct loads runs as long as the real one, and one without the loads takes 37 / 17 /
 // 59 / 32 us: the loads cost their stand-alone time on top of the rest whether or not anybody waits for them.
-template <int BM, int NS, int WM, int WN, int BK, int OCC = 1, bool WFRAG = false, bool WNT = (BM == 64)>
+template <int BM, int NS, int WM, int WN, int BK, int OCC = 1, bool WNT = (BM == 64)>
 __global__ __launch_bounds__(PF_GEMM_THREADS_OF(WM, WN), OCC) void pf_gemm_kernel(GemmArgs g) {
-  static_assert(!WFRAG || BK == 64, "the fragment-major weight path pairs two 32-wide K steps per slab");
   constexpr int NWAVES = WM * WN;
   constexpr int MT = BM / WM / 32;                     // 32-row accumulators per wave
   constexpr int NT = PF_BN / WN / 32;                  // 32-column accumulators per wave
@@ -145,17 +142,10 @@ __global__ __launch_bounds__(PF_GEMM_THREADS_OF(WM, WN), OCC) void pf_gemm_kerne
 #pragma unroll
   for (int i = 0; i < A_LD; ++i)
     arow[i] = g.A + (size_t)(m0 + (wave * A_LD + i) * RPL + lrow) * K + lchunk * 8;
-  const int ksteps32 = (K + 31) >> 5;
 #pragma unroll
   for (int i = 0; i < W_LD; ++i) {
-    if (WFRAG) {
-      // piece f of the stage = 16-row block f / 2 of the tile, K step f % 2 of the slab: 1 KB of consecutive bytes
-      const int f = wave * W_LD + i, blk = n0 / 16 + (f >> 1);
-      wrow[i] = (blk * 16 < g.N) ? g.Wf + (((size_t)blk * ksteps32 + (f & 1)) * 64 + lane) * 8 : nullptr;
-    } else {
-      const int n = n0 + (wave * W_LD + i) * RPL + lrow;
-      wrow[i] = (n < g.N) ? g.W[z] + (size_t)n * K + lchunk * 8 : nullptr;
-    }
+    const int n = n0 + (wave * W_LD + i) * RPL + lrow;
+    wrow[i] = (n < g.N) ? g.W[z] + (size_t)n * K + lchunk * 8 : nullptr;
   }
   // Every workgroup walks its K range from a different starting slab (and wraps around): all
   // tiles reading the same 128-byte column of their weight rows at the same time would keep
@@ -177,13 +167,7 @@ __global__ __launch_bounds__(PF_GEMM_THREADS_OF(WM, WN), OCC) void pf_gemm_kerne
                                        16, 0, 0);
     } else {
       const int i = idx - A_LD;
-      const half_t* src;
-      if (WFRAG) {          // K step 2 sl + (piece % 2); the copy is zero beyond K, steps past its end come from the zeros
-        const int st = sl * 2 + ((wave * W_LD + i) & 1);
-        src = (it < iters && st < ksteps32 && wrow[i]) ? wrow[i] + (size_t)sl * 1024 : g.zeros;
-      } else {
-        src = (kin && wrow[i]) ? wrow[i] + k0 : g.zeros;
-      }
+      const half_t* src = (kin && wrow[i]) ? wrow[i] + k0 : g.zeros;
       __builtin_amdgcn_global_load_lds((const LL_GLOBAL void*)src,
                                        (__attribute__((address_space(3))) void*)(sw + (wave * W_LD + i) * RPL * BK),
                                        16, 0, W_AUX);
@@ -227,17 +211,7 @@ __global__ __launch_bounds__(PF_GEMM_THREADS_OF(WM, WN), OCC) void pf_gemm_kerne
 #pragma unroll
     for (int i = 0; i < MT; ++i) fa[i] = *reinterpret_cast<const h8*>(sa + i * 32 * BK + pc);
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      if (WFRAG) {
-        // row R of the tile sits in piece (R / 16) * 2 + ks / 2 at lane position ((ks % 2) * 2 + half) * 16 + R % 16:
-        // 8 lanes read 128 consecutive bytes, no swizzle needed
-        const int R = wn * (PF_BN / WN) + j * 32 + r;
-        fb[j] = *reinterpret_cast<const h8*>(pf_lds + stage * STAGE_HALVES + BM * BK +
-                                             ((((R >> 4) * 2 + (ks >> 1)) * 64) + ((ks & 1) * 2 + half) * 16 + (R & 15)) * 8);
-      } else {
-        fb[j] = *reinterpret_cast<const h8*>(sw + j * 32 * BK + pc);
-      }
-    }
+    for (int j = 0; j < NT; ++j) fb[j] = *reinterpret_cast<const h8*>(sw + j * 32 * BK + pc);
   };
   // The slab hand-over sits in front of a slab's LAST k-step, not behind it: by then a wave holds the
   // slab's last fragments in registers, so once every wave is there the slab's stage is free and its refill
