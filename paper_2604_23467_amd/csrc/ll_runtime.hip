@@ -474,7 +474,8 @@ struct Instance {
   int* host_ring = nullptr;      // pinned, device-visible; kernels write generated ids here
   int* dev_ring = nullptr;       // device address of host_ring
   int ring_size = 0;
-  int* host_stage = nullptr;     // pinned staging for the prompt ids + DevState
+  int* host_stage = nullptr;     // pinned, device-visible staging: DevState, then the prompt ids
+  int* dev_stage = nullptr;      // device address of host_stage
   // host mirror of the device state (never read back from the GPU on the hot path)
   int pos = 0, steps = 0;
   bool last_was_prefill = false;
@@ -795,6 +796,12 @@ void launch_skinny(hipStream_t s, const PfBuffers& B, SkinnyArgs a, int Mb) {
   else hipLaunchKernelGGL((pf_skinny_kernel<MODE, 2, 0>), grid, block, 0, s, a);
 }
 
+// First kernel of a prefill: the state block and the ids of up to Mb rows from the staging buffer
+void enqueue_stage(Instance* I, hipStream_t s, const PfBuffers& B, int Mb, bool clear_zeros) {
+  hipLaunchKernelGGL(pf_stage_kernel, dim3(1), dim3(LL_WG), 0, s, (const int*)I->dev_stage, (int*)I->state(), B.tokens,
+                     Mb, clear_zeros ? (int*)B.zeros : nullptr);
+}
+
 // Prompts of at most 32 tokens: five kernels per layer, every projection streams its weights
 // once and finishes its own epilogue; the norms ride on the projections around them.
 void enqueue_prefill_skinny(Instance* I, hipStream_t s, const PfBuffers& B, int Mb, bool with_head) {
@@ -911,6 +918,7 @@ void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb
 
 void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) {
   const PfBuffers& B = I->pf;
+  enqueue_stage(I, s, B, Mb, false);
   if (Mb <= 32 && I->skinny) return enqueue_prefill_skinny(I, s, B, Mb, with_head);
   if (has_copy(I->cfg)) return enqueue_prefill_tile(I, s, B, Mb, with_head);
   const ll_config& c = I->cfg;
@@ -1113,6 +1121,7 @@ struct Batch {
   std::vector<std::vector<int>> pages;         // pages of every slot, in order
   BatchState* h_state = nullptr;               // pinned mirrors of the device state and page table
   int* h_table = nullptr;
+  int *d_state_src = nullptr, *d_table_src = nullptr;     // device addresses of the two mirrors
   int* h_out = nullptr;                        // pinned, device-visible: tokens of the last step
   int* d_out = nullptr;
   hipGraph_t graph = nullptr;
@@ -1197,11 +1206,12 @@ void enqueue_batch_step(Instance* I, hipStream_t s) {
                      c.vocab, I->at<SampleCfg>(I->L.sample_cfg), bs, B->d_out);
 }
 
-int push_batch_state(Instance* I) {
+// The slots' state and the page-table rows of slots first .. first + count - 1, host mirrors -> device
+int push_batch_state(Instance* I, int first, int count) {
   Batch* B = I->batch;
-  HIPCHK(hipMemcpyAsync(B->at<BatchState>(B->L.state), B->h_state, sizeof(BatchState), hipMemcpyHostToDevice, I->stream));
-  HIPCHK(hipMemcpyAsync(B->at<int>(B->L.page_table), B->h_table, (size_t)BT_MAX_BATCH * B->L.pt_stride * 4,
-                        hipMemcpyHostToDevice, I->stream));
+  hipLaunchKernelGGL(bt_push_kernel, dim3(count), dim3(LL_WG), 0, I->stream, (const int*)B->d_state_src,
+                     (int*)B->at<BatchState>(B->L.state), B->d_table_src, B->at<int>(B->L.page_table), B->L.pt_stride, first);
+  HIPCHK(hipGetLastError());
   return LL_OK;
 }
 
@@ -1278,8 +1288,11 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   if (!hip_or_bail(hipHostGetDevicePointer((void**)&I->dev_ring, I->host_ring, 0),
                    "hipHostGetDevicePointer")) return bail(rc);
   if (!hip_or_bail(hipHostMalloc((void**)&I->host_stage, sizeof(DevState) + (size_t)L.mb_max * 4 + 64,
-                                 hipHostMallocDefault), "hipHostMalloc(stage)")) return bail(rc);
+                                 hipHostMallocMapped), "hipHostMalloc(stage)")) return bail(rc);
+  if (!hip_or_bail(hipHostGetDevicePointer((void**)&I->dev_stage, I->host_stage, 0),
+                   "hipHostGetDevicePointer(stage)")) return bail(rc);
   memset(I->host_ring, 0, (size_t)I->ring_size * 4);
+  memset(I->host_stage, 0, sizeof(DevState) + (size_t)L.mb_max * 4 + 64);
 
   // RoPE table: angle pos * theta^(-2j/head_dim) and its cos/sin in double, stored as float
   {
@@ -1397,10 +1410,7 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   // afterwards.  Token 0 at position 0 / a one-token prompt touch only valid memory.
   if ((rc = write_state(I, 0, 0, 1, 0)) != LL_OK) return bail(rc);
   enqueue_decode(I, I->stream);
-  for (int b : I->pf_buckets) {
-    if ((rc = write_state(I, 0, 0, 1, 0)) != LL_OK) return bail(rc);
-    enqueue_prefill(I, I->stream, b);
-  }
+  for (int b : I->pf_buckets) enqueue_prefill(I, I->stream, b);      // (each starts from the staged state: one token)
   if (!hip_or_bail(hipStreamSynchronize(I->stream), "warm-up")) return bail(rc);
   if (!hip_or_bail(hipGetLastError(), "warm-up launch")) return bail(rc);
 
@@ -1433,12 +1443,15 @@ int ll_shutdown(void) {
 
 int ll_reset(void) {
   if (!g) return fail(LL_E_NOT_INIT, "ll_reset: not initialised");
-  int rc = write_state(g, 0, 0, 0, 0);
-  if (rc != LL_OK) return rc;
-  // also clears a barrier time-out left behind by a failed step
-  HIPCHK(hipMemsetAsync(g->at<unsigned>(g->L.mk_bar), 0, (size_t)MK_BAR_WORDS * 4, g->stream));
-  HIPCHK(hipMemsetAsync(g->at<unsigned>(g->L.attn_cnt), 0, (size_t)g->cfg.n_heads * 4, g->stream));
-  HIPCHK(hipMemsetAsync(g->at<char>(g->L.ao_sync), 0, 64 * 4, g->stream));
+  // The next prefill brings its own state block, and nothing runs on an empty context before it; only the modes whose
+  // workgroups wait for one another have device words to clear (a time-out left behind by a failed step).
+  if (g->use_mega || g->fused_attn) {
+    int rc = write_state(g, 0, 0, 0, 0);
+    if (rc != LL_OK) return rc;
+    HIPCHK(hipMemsetAsync(g->at<unsigned>(g->L.mk_bar), 0, (size_t)MK_BAR_WORDS * 4, g->stream));
+    HIPCHK(hipMemsetAsync(g->at<unsigned>(g->L.attn_cnt), 0, (size_t)g->cfg.n_heads * 4, g->stream));
+    HIPCHK(hipMemsetAsync(g->at<char>(g->L.ao_sync), 0, 64 * 4, g->stream));
+  }
   HIPCHK(hipStreamSynchronize(g->stream));
   g->pos = 0;
   g->steps = 0;
@@ -1506,7 +1519,8 @@ int32_t ll_prefill(const int32_t* tokens, int32_t n) {
   const int chk = prefill_check(I, "ll_prefill", tokens, n);
   if (chk != LL_OK) return chk;
 
-  // prompt ids and the state block travel in one pinned staging buffer.  A prompt longer than the
+  // Prompt ids and the state block travel in one pinned staging buffer that the prefill's first kernel reads (two
+  // host-to-device copies in front of it cost 15 us more).  A prompt longer than the
   // largest bucket goes through in chunks of that size: every chunk but the last runs the layers
   // only (its rows just fill the KV cache), the last one also produces the first token.
   DevState* hs = reinterpret_cast<DevState*>(I->host_stage);
@@ -1519,8 +1533,6 @@ int32_t ll_prefill(const int32_t* tokens, int32_t n) {
     hs->pos = p0;
     hs->n_prompt = m;
     memcpy(htok, tokens + p0, (size_t)m * 4);
-    HIPCHK(hipMemcpyAsync(I->state(), hs, sizeof(DevState), hipMemcpyHostToDevice, I->stream));
-    HIPCHK(hipMemcpyAsync(I->pf.tokens, htok, (size_t)m * 4, hipMemcpyHostToDevice, I->stream));
     if (eager(I)) {
       enqueue_prefill(I, I->stream, Mb, last);
       HIPCHK(hipGetLastError());
@@ -1559,15 +1571,13 @@ int32_t ll_prefill_static(const int32_t* tokens, int32_t n) {
                                "use ll_prefill", need, (unsigned)LL_STATIC_SCRATCH_BYTES);
 
   // The array keeps what the last call left: the block of zeros that out-of-range operand loads are
-  // aimed at is cleared here; everything else is written by this call before it is read.
-  HIPCHK(hipMemsetAsync(B.zeros, 0, 256, I->stream));
+  // aimed at is cleared by the first kernel; everything else is written by this call before it is read.
   DevState* hs = reinterpret_cast<DevState*>(I->host_stage);
   int* htok = reinterpret_cast<int*>(reinterpret_cast<char*>(I->host_stage) + sizeof(DevState));
   memset(hs, 0, sizeof(DevState));
   hs->n_prompt = n;
   memcpy(htok, tokens, (size_t)n * 4);
-  HIPCHK(hipMemcpyAsync(I->state(), hs, sizeof(DevState), hipMemcpyHostToDevice, I->stream));
-  HIPCHK(hipMemcpyAsync(B.tokens, htok, (size_t)n * 4, hipMemcpyHostToDevice, I->stream));
+  enqueue_stage(I, I->stream, B, n <= 16 ? 16 : 32, true);
   enqueue_prefill_skinny(I, I->stream, B, n <= 16 ? 16 : 32, true);     // launched kernel by kernel: no graph holds these addresses
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(I->stream));
@@ -1651,13 +1661,16 @@ int ll_batch_open(int32_t max_batch, int32_t page_tokens, int32_t n_pages, void*
     if (e != hipSuccess) { rc = fail(LL_E_HIP, "%s: %s", what, hipGetErrorString(e)); return false; }
     return true;
   };
-  if (!ok(hipHostMalloc((void**)&B->h_state, sizeof(BatchState), hipHostMallocDefault), "hipHostMalloc(batch state)"))
+  if (!ok(hipHostMalloc((void**)&B->h_state, sizeof(BatchState), hipHostMallocMapped), "hipHostMalloc(batch state)"))
     return bail(rc);
-  if (!ok(hipHostMalloc((void**)&B->h_table, (size_t)BT_MAX_BATCH * BL.pt_stride * 4, hipHostMallocDefault),
+  if (!ok(hipHostMalloc((void**)&B->h_table, (size_t)BT_MAX_BATCH * BL.pt_stride * 4, hipHostMallocMapped),
           "hipHostMalloc(page table)")) return bail(rc);
   if (!ok(hipHostMalloc((void**)&B->h_out, BT_MAX_BATCH * 4, hipHostMallocMapped), "hipHostMalloc(batch out)"))
     return bail(rc);
-  if (!ok(hipHostGetDevicePointer((void**)&B->d_out, B->h_out, 0), "hipHostGetDevicePointer(batch out)")) return bail(rc);
+  if (!ok(hipHostGetDevicePointer((void**)&B->d_out, B->h_out, 0), "hipHostGetDevicePointer(batch out)") ||
+      !ok(hipHostGetDevicePointer((void**)&B->d_state_src, B->h_state, 0), "hipHostGetDevicePointer(batch state)") ||
+      !ok(hipHostGetDevicePointer((void**)&B->d_table_src, B->h_table, 0), "hipHostGetDevicePointer(page table)"))
+    return bail(rc);
   memset(B->h_state, 0, sizeof(BatchState));
   memset(B->h_table, 0, (size_t)BT_MAX_BATCH * BL.pt_stride * 4);          // every slot: page 0
   for (int b = 0; b < BT_MAX_BATCH; ++b) B->h_out[b] = -1;
@@ -1673,7 +1686,7 @@ int ll_batch_open(int32_t max_batch, int32_t page_tokens, int32_t n_pages, void*
   // page 0 must hold finite numbers: free slots attend nothing, but their K/V rows are written there
   if (!ok(hipMemsetAsync(B->at<char>(BL.kv), 0, (size_t)c.n_layers * 2 * BL.kv_layer_halves * 2, I->stream),
           "hipMemset(pool)")) return bail(rc);
-  if ((rc = push_batch_state(I)) != LL_OK) return bail(rc);
+  if ((rc = push_batch_state(I, 0, BT_MAX_BATCH)) != LL_OK) return bail(rc);
   enqueue_batch_step(I, I->stream);                                         // warm-up on empty slots
   if (!ok(hipStreamSynchronize(I->stream), "batch warm-up")) return bail(rc);
   if (!ok(hipGetLastError(), "batch warm-up launch")) return bail(rc);
@@ -1732,7 +1745,7 @@ int32_t ll_batch_add(const int32_t* tokens, int32_t n, int32_t* first_token) {
   B->h_state->next_token[slot] = t1;
   B->h_state->active[slot] = 1;
   B->h_state->steps[slot] = 1;                  // the prefill drew with index 0
-  if ((rc = push_batch_state(I)) != LL_OK) return rc;
+  if ((rc = push_batch_state(I, slot, 1)) != LL_OK) return rc;
   const ll_config& c = I->cfg;
   hipLaunchKernelGGL(bt_scatter_kernel, dim3(n, c.n_layers * 2), dim3(LL_WG), 0, I->stream, I->kcache(0),
                      I->L.kv_layer_halves, c.max_seq, B->kpool(0), B->L.kv_layer_halves, B->L.pool_rows,
@@ -1756,7 +1769,7 @@ int ll_batch_remove(int32_t slot) {
   B->h_state->next_token[slot] = 0;
   B->h_state->active[slot] = 0;
   B->h_state->steps[slot] = 0;
-  int rc = push_batch_state(g);
+  int rc = push_batch_state(g, slot, 1);
   if (rc != LL_OK) return rc;
   HIPCHK(hipStreamSynchronize(g->stream));
   return LL_OK;
@@ -1842,7 +1855,7 @@ int ll_batch_dbg_force_next_token(int32_t slot, int32_t tok) {
   if (slot < 0 || slot >= B->max_batch || !B->h_state->active[slot] || tok < 0 || tok >= g->cfg.vocab)
     return fail(LL_E_BAD_ARG, "ll_batch_dbg_force_next_token: bad argument");
   B->h_state->next_token[slot] = tok;
-  int rc = push_batch_state(g);
+  int rc = push_batch_state(g, slot, 1);
   if (rc != LL_OK) return rc;
   HIPCHK(hipStreamSynchronize(g->stream));
   return LL_OK;

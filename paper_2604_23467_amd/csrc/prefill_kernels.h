@@ -13,6 +13,18 @@
 #pragma once
 #include "ll_device.h"
 
+// State block and prompt ids from the pinned staging buffer (host memory: one round trip over the bus for all of
+// it, so ids are fetched for every row of the bucket without waiting for n; the rows past n are not used).  zeros:
+// optionally 256 bytes to clear.  One workgroup.
+__global__ __launch_bounds__(LL_WG) void pf_stage_kernel(const int* __restrict__ stage, int* __restrict__ state,
+                                                         int* __restrict__ tokens, int rows, int* __restrict__ zeros) {
+  constexpr int WORDS = sizeof(DevState) / 4;
+  const int tid = threadIdx.x;
+  if (tid < WORDS) state[tid] = stage[tid];
+  for (int i = tid; i < rows; i += LL_WG) tokens[i] = stage[WORDS + i];
+  if (zeros && tid < 64) zeros[tid] = 0;
+}
+
 // X[r] = float(E[tokens[r]]) for r < n, 0 otherwise.  grid = (Mb, ceil(d / 2048))
 __global__ __launch_bounds__(LL_WG) void pf_embed_kernel(const half_t* __restrict__ emb,
                                                          const int* __restrict__ tokens,
