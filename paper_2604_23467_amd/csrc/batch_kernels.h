@@ -22,20 +22,24 @@ struct BatchState {
 };
 
 // Attention of slot b's new query (position pos[b], already written to the cache) for one head.
-// grid = (heads, rows of the step = 16 or 32), 512 threads (two workgroups per CU; two trips of 128 keys
-// in flight); tb = rows / 16 selects the output's fragment-major layout.  As in the single-sequence kernel a key row is read
+// grid = (heads, rows of the step = 16 or 32), NT threads, four waves per SIMD (the register limit says so: left
+// alone the compiler took 145 registers and half as many workgroups fitted a CU); tb = rows / 16 selects the output's
+// fragment-major layout.  512 threads at 16 rows; 256 at 32, where twice as many workgroups then run side by side and
+// the many short sequences of a mixed batch leave fewer lanes idle (16 sequences of 10..560 keys 12.6 -> 11.3 us per
+// layer, 32 sequences 22.9 -> 19.9; 32 sequences in 512-thread workgroups: 21.3).  Two trips of 16 keys per wave are
+// in flight; the kernel's time is that of the longest sequences' trips, some 225 instructions per wave and trip.  As in the single-sequence kernel a key row is read
 // by HD / 8 adjacent lanes with one 16-byte load each and every lane group keeps an online-softmax
 // state over the keys it is dealt; groups merge by shuffles, waves through LDS.  Output: fp16,
 // in the fragment-major operand layout of the O projection.
-#define BT_ATTN_THREADS 512
-template <int HD>
-__global__ __launch_bounds__(BT_ATTN_THREADS) void bt_attn_kernel(
+#define BT_ATTN_THREADS(TB) ((TB) == 1 ? 512 : 256)
+template <int HD, int NT>
+__global__ __launch_bounds__(NT, 4) void bt_attn_kernel(
     const half_t* __restrict__ Q, const half_t* __restrict__ kc, const half_t* __restrict__ vc,
     const BatchState* __restrict__ bs, const int* __restrict__ page_table, int pt_stride, int page_tokens,
     half_t* __restrict__ O, int d, int pool_rows, int tb) {
   constexpr int LPR = HD / 8;      // lanes per key row
   constexpr int GPW = 64 / LPR;    // lane groups per wave
-  constexpr int NW = BT_ATTN_THREADS / 64;
+  constexpr int NW = NT / 64;
   constexpr int UK = 4;            // keys in flight per group
   __shared__ float s_m[NW], s_l[NW], s_acc[NW][HD];
   extern __shared__ int s_pt[];    // this slot's page-table row: a key's address then costs no global round trip
@@ -47,7 +51,7 @@ __global__ __launch_bounds__(BT_ATTN_THREADS) void bt_attn_kernel(
   const int active = bs->active[b];
   const int n_keys = bs->pos[b] + 1;
   const h8 q = load_h8(Q + (size_t)b * d + h * HD + li * 8);
-  for (int i = tid; i < pt_stride; i += BT_ATTN_THREADS) s_pt[i] = page_table[b * pt_stride + i];
+  for (int i = tid; i < pt_stride; i += NT) s_pt[i] = page_table[b * pt_stride + i];
   if (!active) {
     if (tid < HD / 8) *reinterpret_cast<h8*>(O + act_offset(b, h * HD + tid * 8, d, tb)) = h8{0, 0, 0, 0, 0, 0, 0, 0};
     return;
@@ -60,6 +64,9 @@ __global__ __launch_bounds__(BT_ATTN_THREADS) void bt_attn_kernel(
   const half_t* kh = kc + (size_t)h * pool_rows * HD + li * 8;
   const half_t* vh = vc + (size_t)h * pool_rows * HD + li * 8;
 
+  // Page of a position by a reciprocal instead of an integer division per key: (u + 1/2) / page_tokens is at least
+  // 1 / (2 page_tokens) away from an integer, more than its rounding error for every u < 2^20 (the limit of max_seq).
+  const float rpt = 1.0f / (float)page_tokens;
   float m = -INFINITY, l = 0.f, acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
@@ -72,7 +79,7 @@ __global__ __launch_bounds__(BT_ATTN_THREADS) void bt_attn_kernel(
 #pragma unroll
     for (int j = 0; j < UK; ++j) {
       const int u = min(base + j * STRIDE + gi, n_keys - 1);
-      const int pg = u / page_tokens;
+      const int pg = (int)(((float)u + 0.5f) * rpt);     // u / page_tokens
       const size_t row = (size_t)(s_pt[pg] + (u - pg * page_tokens));
       kk[j] = load_stream(kh + row * HD);
       vv[j] = load_stream(vh + row * HD);
@@ -107,7 +114,9 @@ __global__ __launch_bounds__(BT_ATTN_THREADS) void bt_attn_kernel(
   };
   h8 ka[UK], va[UK], kb[UK], vb[UK];
   issue(wave * GPW, ka, va);
-  for (int base = wave * GPW; base < n_keys; base += 2 * TRIP) {
+  if (n_keys <= TRIP) {
+    consume(wave * GPW, ka, va);
+  } else for (int base = wave * GPW; base < n_keys; base += 2 * TRIP) {
     issue(base + TRIP, kb, vb);
     __builtin_amdgcn_sched_barrier(0);
     consume(base, ka, va);
@@ -138,23 +147,18 @@ __global__ __launch_bounds__(BT_ATTN_THREADS) void bt_attn_kernel(
     }
   }
   __syncthreads();
-  if (tid < HD / 8) {
+  if (tid < HD) {
     float M = -INFINITY;
 #pragma unroll
     for (int i = 0; i < NW; ++i) M = fmaxf(M, s_m[i]);
-    float L = 0.f, A[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float L = 0.f, A = 0.f;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       const float w = (s_m[i] > -INFINITY) ? __expf(s_m[i] - M) : 0.f;    // M is finite: key 0 is always attended
       L += s_l[i] * w;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) A[e] += s_acc[i][tid * 8 + e] * w;
+      A += s_acc[i][tid] * w;
     }
-    const float rl = 1.0f / L;
-    h8 o;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (half_t)(A[e] * rl);
-    *reinterpret_cast<h8*>(O + act_offset(b, h * HD + tid * 8, d, tb)) = o;
+    O[act_offset(b, h * HD + tid, d, tb)] = (half_t)(A / L);
   }
 }
 

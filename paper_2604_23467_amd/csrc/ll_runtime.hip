@@ -1168,12 +1168,14 @@ void enqueue_batch_step(Instance* I, hipStream_t s) {
     a.Wf = I->wfrag(l, I->L.wf_qkv);
     launch_skinny<SK_QKV>(s, P, a, Mb);
     dim3 agrid(c.n_heads, Mb);
-    if (c.head_dim == 128)
-      hipLaunchKernelGGL(bt_attn_kernel<128>, agrid, dim3(BT_ATTN_THREADS), (size_t)B->L.pt_stride * 4, s, Qh, B->kpool(l), B->vpool(l), bs,
+    auto attn = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, agrid, dim3(threads), (size_t)B->L.pt_stride * 4, s, Qh, B->kpool(l), B->vpool(l), bs,
                          table, B->L.pt_stride, B->page_tokens, Oh, d, B->L.pool_rows, tb);
-    else
-      hipLaunchKernelGGL(bt_attn_kernel<64>, agrid, dim3(BT_ATTN_THREADS), (size_t)B->L.pt_stride * 4, s, Qh, B->kpool(l), B->vpool(l), bs,
-                         table, B->L.pt_stride, B->page_tokens, Oh, d, B->L.pool_rows, tb);
+    };
+    if (c.head_dim == 128) tb == 1 ? attn(bt_attn_kernel<128, BT_ATTN_THREADS(1)>, BT_ATTN_THREADS(1))
+                                     : attn(bt_attn_kernel<128, BT_ATTN_THREADS(2)>, BT_ATTN_THREADS(2));
+    else tb == 1 ? attn(bt_attn_kernel<64, BT_ATTN_THREADS(1)>, BT_ATTN_THREADS(1))
+                 : attn(bt_attn_kernel<64, BT_ATTN_THREADS(2)>, BT_ATTN_THREADS(2));
     a.row_pos = nullptr; a.page_table = nullptr;
     a.X = Oh; a.W[0] = (const half_t*)W.wo; a.W[1] = a.W[2] = nullptr; a.N = d; a.K = d; a.Xres = X;
     a.gain_next = (const half_t*)W.ffn_norm; a.Xh_next = Xn; a.ss_out = ss_ffn;
