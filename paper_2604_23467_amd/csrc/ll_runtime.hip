@@ -848,24 +848,18 @@ void enqueue_prefill_skinny(Instance* I, hipStream_t s, const PfBuffers& B, int 
   if (with_head) enqueue_head(I, s, B, X, 1, 1);
 }
 
-// Prefill attention of layer l for a bucket of Mb >= 64 rows: the longer the prompt, the more
-// key groups share a query block (a chunk of a long prompt attends everything cached before it)
+// Prefill attention of layer l for a bucket of Mb >= 64 rows: key groups that share a query block (a chunk of a long
+// prompt attends everything cached before it); two are best where a block has two key tiles, four beyond
 template <int HD>
 void launch_attn_hd(Instance* I, hipStream_t s, const PfBuffers& B, int l, int Mb, int tb) {
   const ll_config& c = I->cfg;
   dim3 grid(c.n_heads, Mb / 64);
-  const half_t* Qh = B.Q;
-  half_t* Oh = B.O;
-  const int groups = (Mb >= 256 || c.max_seq - 1 > kMaxPromptBucket) ? 4 : Mb >= 128 ? 2 : 1;
-  if (groups == 4)
-    hipLaunchKernelGGL((pf_attn_kernel<HD, 4>), grid, dim3(512), PF_ATTN_LDS_BYTES(HD, 4), s, Qh, I->kcache(l),
-                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, tb);
-  else if (groups == 2)
-    hipLaunchKernelGGL((pf_attn_kernel<HD, 2>), grid, dim3(256), PF_ATTN_LDS_BYTES(HD, 2), s, Qh, I->kcache(l),
-                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, tb);
+  if (Mb >= 128 || c.max_seq - 1 > kMaxPromptBucket)
+    hipLaunchKernelGGL((pf_attn_kernel<HD, 4>), grid, dim3(512), PF_ATTN_LDS_BYTES(HD, 4), s, B.Q, I->kcache(l),
+                       I->vcache(l), I->state(), B.O, c.d_model, c.max_seq, tb);
   else
-    hipLaunchKernelGGL((pf_attn_kernel<HD, 1>), grid, dim3(128), PF_ATTN_LDS_BYTES(HD, 1), s, Qh, I->kcache(l),
-                       I->vcache(l), I->state(), Oh, c.d_model, c.max_seq, tb);
+    hipLaunchKernelGGL((pf_attn_kernel<HD, 2>), grid, dim3(256), PF_ATTN_LDS_BYTES(HD, 2), s, B.Q, I->kcache(l),
+                       I->vcache(l), I->state(), B.O, c.d_model, c.max_seq, tb);
 }
 
 // tb: token blocks of the output's fragment-major layout, 0 for row-major
@@ -1339,6 +1333,9 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_attn_kernel<128, 4>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PF_ATTN_LDS_BYTES(128, 4)),
                    "hipFuncSetAttribute(attention 128 x 4)")) return bail(rc);
+  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_attn_kernel<128, 2>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, PF_ATTN_LDS_BYTES(128, 2)),
+                   "hipFuncSetAttribute(attention 128 x 2)")) return bail(rc);
   if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_attn_kernel<64, 4>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PF_ATTN_LDS_BYTES(64, 4)),
                    "hipFuncSetAttribute(attention 64 x 4)")) return bail(rc);

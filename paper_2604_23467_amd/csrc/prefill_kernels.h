@@ -167,8 +167,8 @@ __global__ __launch_bounds__(LL_WG) void pf_rope_kv_kernel(const float* __restri
 }
 
 // Causal attention of one head for a block of 64 queries, on the matrix cores.
-// grid = (heads, Mb / 64), 128 threads: each of the two waves owns 32 queries
-// and walks the keys in tiles of 32 with an online softmax.
+// grid = (heads, Mb / 64), longest blocks first; 128 G threads: G groups of two waves, group g taking the key tiles
+// (32 keys) g, g + G, ... of the block; each of a group's two waves owns 32 queries, with an online softmax.
 //
 // Both products are computed transposed so that the softmax needs no transpose:
 //   S^T[key][q] = sum_d K[key][d] Q[q][d]      A = K tile (LDS), B = Q (registers)
@@ -178,17 +178,26 @@ __global__ __launch_bounds__(LL_WG) void pf_rope_kv_kernel(const float* __restri
 // 15 register operations plus one cross-half shuffle, the rescale of O^T is a
 // per-lane scalar, and the probabilities are already in B-operand position:
 // k-slot j of lane half hf in k-step s holds key 16 s + 8 (j / 4) + 4 hf + j % 4.
-// The V tile is written to LDS transposed with its keys in exactly that order,
-// so an A fragment of V^T is one 16-byte LDS read.
 //
-// Long prompts make the last query blocks walk many key tiles, one after the other with nothing
-// else on the CU to hide a tile's chain of LDS round trips, matrix instructions and exponentials.
-// So G groups of two waves share a query block: group g takes the key tiles g, g + G, ... with
-// tile buffers of its own, and group 0 merges the groups' (max, sum, O^T) at the end.
-#define PF_ATTN_TILE_HALVES(HD) (32 * ((HD) + 8) + (HD) * 36)
+// K and V tiles go global -> LDS directly, row-major, one tile ahead, and stay row-major: the V^T operand is read with
+// the transposing LDS read (ds_read_b64_tr_b16: 16 lanes fetch four rows of 16 columns and each receives one
+// column of the four rows, which is exactly a k-slot quad above).  Within a row of HD halves the 16-byte chunk c sits at
+// c ^ swz(key), which keeps both kinds of reads off one another's banks.
+//
+// What bounds it: a trip of all four groups moves 64 KB into LDS and reads 128 KB from it (some 2000 cycles of the LDS
+// port) around 700 cycles of vector work (softmax, rescale) and 16 matrix instructions per wave: 1.8 us.  So
+// the scale is folded into the exponential's argument (one multiply-add per score), only tiles on the diagonal
+// are masked, the rescale is skipped when no query's maximum moved, all operands of a tile are requested at
+// once, and the groups' partial results are merged by all threads (by one group it cost as much as two tiles).
+// Per layer at the 7B shape, tiles staged through registers and V transposed by 2-byte pair stores before / now:
+// 50 tokens 5.9 / 5.4 us, 100: 7.7 / 6.4, 250: 13.0 / 9.3, 350: 16.0 / 10.8, 500: 20.7 / 14.5, the two chunks of
+// 2000 tokens 41 and 82 / 26 and 58.  Groups (same order): one 5.8 / 8.9 / 14.5 / - / 27 us, two 5.4 / 7.1 / 10.6 /
+// - / 19.5, four 5.9 / 6.4 / 9.3 / 10.8 / 14.5.
+#define PF_ATTN_TILE_HALVES(HD) (2 * 32 * (HD))                       /* one K and one V tile */
+#define PF_ATTN_MERGE_BYTES(HD, G) ((G) == 1 ? 0 : (G) * 128 * ((HD) / 2 + 2) * 4)
 #define PF_ATTN_LDS_BYTES(HD, G) \
-  ((G) * PF_ATTN_TILE_HALVES(HD) * 2 > ((G) - 1) * 128 * ((HD) / 2 + 2) * 4 \
-       ? (G) * PF_ATTN_TILE_HALVES(HD) * 2 : ((G) - 1) * 128 * ((HD) / 2 + 2) * 4)
+  ((G) * 2 * PF_ATTN_TILE_HALVES(HD) * 2 > PF_ATTN_MERGE_BYTES(HD, G) ? (G) * 2 * PF_ATTN_TILE_HALVES(HD) * 2 \
+                                                                      : PF_ATTN_MERGE_BYTES(HD, G))
 
 template <int HD, int G>
 __global__ __launch_bounds__(128 * G) void pf_attn_kernel(const half_t* __restrict__ Q,
@@ -198,20 +207,36 @@ __global__ __launch_bounds__(128 * G) void pf_attn_kernel(const half_t* __restri
                                                           half_t* __restrict__ O, int d, int max_seq,
                                                           int frag_tb) {
   constexpr int QB = 64, TK = 32, KS = HD / 16, DT = HD / 32, CPR = HD / 8;
-  constexpr int K_STRIDE = HD + 8;   // halves: 16-byte fragment reads of 8 rows hit 8 distinct bank groups
-  constexpr int V_STRIDE = 36;       // halves per d row of V^T (32 keys + pad): rows 18 words apart, see stash()
+  constexpr int RPL = 64 / CPR;               // tile rows one 1 KB direct load covers
+  constexpr int LOADS = TK / RPL;             // direct loads of a K (or V) tile: wave 0 of the group brings K, wave 1 V
   extern __shared__ __attribute__((aligned(16))) half_t pf_attn_lds[];
-  const int h = blockIdx.x, q0 = blockIdx.y * QB;
+  const int h = blockIdx.x, q0 = (gridDim.y - 1 - blockIdx.y) * QB;
   const int n = st->n_prompt, p0 = st->pos;   // rows of this chunk, positions cached before it
   if (q0 >= n) return;
   const int tid = threadIdx.x & 127, lane = tid & 63, hf = lane >> 5, ql = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7);
-  half_t* Ks = pf_attn_lds + grp * PF_ATTN_TILE_HALVES(HD);
-  half_t* Vt = Ks + TK * K_STRIDE;
+  half_t* buf = pf_attn_lds + grp * 2 * PF_ATTN_TILE_HALVES(HD);      // two stages of [K tile | V tile]
   const int qi = q0 + wave * 32 + ql;
-  const int wave_last_q = q0 + wave * 32 + 31;
-  const float scale = 1.0f / sqrtf((float)HD);
+  const int wave_q = q0 + wave * 32;          // the wave's first query
+  const float c2 = 1.44269504088896340736f / sqrtf((float)HD);        // scores enter exp2 scaled by log2(e) / sqrt(HD)
+
+  // chunk swizzle of a key's row (even, so that pairs of chunks stay pairs)
+  auto swz = [](int key) { return HD == 128 ? (key & 7) * 2 : ((key >> 1) & 3) * 2; };
+  const half_t* src = (wave ? vc : kc) + (size_t)h * max_seq * HD;
+  const int last_row = p0 + n - 1, last_key = p0 + min(q0 + QB, n) - 1;   // the block's last valid query attends it
+  auto issue = [&](int k0, int stage) {
+    half_t* dst = buf + stage * PF_ATTN_TILE_HALVES(HD) + wave * TK * HD;
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      const int row = i * RPL + lane / CPR, c = (lane % CPR) ^ swz(row);
+      __builtin_amdgcn_global_load_lds((const LL_GLOBAL void*)(src + (size_t)min(k0 + row, last_row) * HD + c * 8),
+                                       (__attribute__((address_space(3))) void*)(dst + i * 512), 16, 0, 0);
+    }
+  };
+  constexpr int STEP = G * TK;
+  const int kg = grp * TK;
+  if (kg <= last_key) issue(kg, 0);
 
   h8 qf[KS];
   {
@@ -224,175 +249,147 @@ __global__ __launch_bounds__(128 * G) void pf_attn_kernel(const half_t* __restri
   for (int t = 0; t < DT; ++t)
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f;               // running maximum of the raw scores, running sum
 
-  const half_t* kh = kc + (size_t)h * max_seq * HD;
-  const half_t* vh = vc + (size_t)h * max_seq * HD;
-  const int last_key = p0 + min(q0 + QB, n) - 1;   // the block's last valid query attends it
-
-  // K/V tiles travel global -> registers -> LDS; the loads run two tiles ahead of the tile being
-  // multiplied, so their latency (the whole cost of a tile otherwise) hides behind two tiles' work
-  constexpr int ITEMS = TK * CPR / 128;      // 16-byte pieces of K (and of V) per thread and tile
-  static_assert(TK * CPR % 128 == 0, "tile pieces divide over the workgroup");
-  // V pieces are dealt differently: a thread takes the same 8 d values of TWO neighbouring keys,
-  // which sit side by side in a V^T row, so the transposed store is 8 dwords instead of 16
-  // halves; and lanes run over 8 column pieces x 8 key pairs, which lands a wave's 64 dwords of
-  // one store in (almost) distinct banks: d rows are 18 words apart, 8 rows (one piece) 144.
-  // (With a key's 16 pieces on neighbouring lanes every store hit two banks 16 ways.)
-  constexpr int VITEMS = TK / 2 * CPR / 128;                  // key pairs x pieces per thread
-  static_assert(TK / 2 * CPR % 128 == 0 && CPR % 8 == 0, "V pieces divide over the workgroup");
-  auto v_item = [&](int it, int& c, int& key) {     // piece and even key (inside the tile) of this thread's item
-    const int x = (tid >> 6) + 2 * it;              // lanes: 8 pieces x 8 key pairs; wave and item: the high parts
-    c = (tid & 7) + 8 * (x % (CPR / 8));
-    key = 2 * (((tid >> 3) & 7) + 8 * (x / (CPR / 8)));
-  };
-  h8 kpre[2][ITEMS], vpre[2][2 * VITEMS];
-  auto fetch = [&](int k0, h8 (&kk)[ITEMS], h8 (&vv)[2 * VITEMS]) {
+  // LDS byte offsets of this lane's operand reads: K row ql (chunk 2 ks + hf), V^T quads (see above)
+  const int koff = ql * HD * 2 + swz(ql) * 16 + hf * 16;
+  const int vkey = 4 * hf + ((lane & 15) >> 2);
+  const int voff = TK * HD * 2 + vkey * HD * 2 + ((((lane >> 4) & 1) * 2 + ((lane & 3) >> 1)) ^ swz(vkey)) * 16 + (lane & 1) * 8;
+  typedef __fp16 v4f16 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) v4f16 lds_v4f16;
+  // Operands of a tile: all of them are requested before the first product (and before the next tile's direct
+  // loads: the compiler holds a transposing read back until every direct load in flight has landed).
+  h4 fv[DT][2][2];
+  h8 fk[KS];
+  auto load_tile = [&](const half_t* b) {
+    const char* base = reinterpret_cast<const char*>(b);
 #pragma unroll
-    for (int it = 0; it < ITEMS; ++it) {
-      const int idx = tid + it * 128;
-      const int key = idx / CPR, c = idx - key * CPR;
-      const int kr = min(k0 + key, p0 + n - 1);
-      kk[it] = load_h8(kh + (size_t)kr * HD + c * 8);
-    }
+    for (int ks = 0; ks < KS; ++ks) fk[ks] = *reinterpret_cast<const h8*>(base + (koff ^ (ks * 32)));
 #pragma unroll
-    for (int it = 0; it < VITEMS; ++it) {
-      int c, key;
-      v_item(it, c, key);
-      vv[2 * it] = load_h8(vh + (size_t)min(k0 + key, p0 + n - 1) * HD + c * 8);
-      vv[2 * it + 1] = load_h8(vh + (size_t)min(k0 + key + 1, p0 + n - 1) * HD + c * 8);
-    }
-  };
-  auto stash = [&](const h8 (&kk)[ITEMS], const h8 (&vv)[2 * VITEMS]) {
+    for (int t = 0; t < DT; ++t)
 #pragma unroll
-    for (int it = 0; it < ITEMS; ++it) {
-      const int idx = tid + it * 128;
-      const int key = idx / CPR, c = idx - key * CPR;
-      *reinterpret_cast<h8*>(Ks + key * K_STRIDE + c * 8) = kk[it];
-    }
-#pragma unroll
-    for (int it = 0; it < VITEMS; ++it) {
-      int c, key;
-      v_item(it, c, key);
-      // position of this key inside a V^T row: k-step s = key / 16, then half and slot as above
-      const int r16 = key & 15;
-      const int pos = ((key >> 4) * 2 + ((r16 & 7) >> 2)) * 8 + (r16 >> 3) * 4 + (r16 & 3);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-        const h2 pr = {vv[2 * it][e], vv[2 * it + 1][e]};
-        *reinterpret_cast<h2*>(Vt + (c * 8 + e) * V_STRIDE + pos) = pr;
-      }
-    }
+      for (int i = 0; i < 4; ++i)
+        fv[t][i >> 1][i & 1] = __builtin_bit_cast(
+            h4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_v4f16*)(base + ((voff ^ (t * 64)) + i * 8 * HD * 2))));
   };
   auto tile = [&](int k0) {
-    if (k0 > p0 + wave_last_q) return;   // whole tile above this wave's diagonal
-
-    f16v sc;
+    f16v sc, sd;                              // two chains of products
 #pragma unroll
-    for (int e = 0; e < 16; ++e) sc[e] = 0.f;
+    for (int e = 0; e < 16; ++e) sc[e] = sd[e] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const h8 a = *reinterpret_cast<const h8*>(Ks + ql * K_STRIDE + ks * 16 + hf * 8);
-      sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, qf[ks], sc, 0, 0, 0);
+    for (int ks = 0; ks < KS; ks += 2) {
+      sc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fk[ks], qf[ks], sc, 0, 0, 0);
+      sd = __builtin_amdgcn_mfma_f32_32x32x16_f16(fk[ks + 1], qf[ks + 1], sd, 0, 0, 0);
     }
-    float mx = -INFINITY;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int key = k0 + 8 * (e >> 2) + 4 * hf + (e & 3);
-      sc[e] = (key <= p0 + qi) ? sc[e] * scale : -INFINITY;
-      mx = fmaxf(mx, sc[e]);
+    for (int e = 0; e < 16; ++e) sc[e] += sd[e];
+    if (k0 + TK - 1 > p0 + wave_q) {          // a tile on the wave's diagonal
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        if (k0 + 8 * (e >> 2) + 4 * hf + (e & 3) > p0 + qi) sc[e] = -INFINITY;
     }
+    float mx = sc[0];
+#pragma unroll
+    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, sc[e]);
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float mn = fmaxf(m, mx);            // finite: tile 0 always holds key 0 <= qi
-    const float corr = __expf(m - mn);
+    if (__any(mx > m)) {
+      // finite: p0 and the waves' first queries are multiples of 32, so a tile that is not skipped
+      // holds at least one key for each of its queries
+      const float mn = fmaxf(m, mx);
+      const float corr = __builtin_amdgcn_exp2f((m - mn) * c2);
+      m = mn;
+      l *= corr;
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[t][e] *= corr;
+    }
+    const float mc = m * c2;
     float rs = 0.f;
     h8 pb[2];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const float p = __expf(sc[e] - mn);
+      const float p = __builtin_amdgcn_exp2f(sc[e] * c2 - mc);
       rs += p;
       pb[e >> 3][e & 7] = (half_t)p;
     }
-    rs += __shfl_xor(rs, 32);
-    l = l * corr + rs;
-    m = mn;
+    l += rs + __shfl_xor(rs, 32);
 #pragma unroll
-    for (int t = 0; t < DT; ++t) {
+    for (int s2 = 0; s2 < 2; ++s2)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[t][e] *= corr;
-#pragma unroll
-      for (int s2 = 0; s2 < 2; ++s2) {
-        const half_t* vp = Vt + (t * 32 + ql) * V_STRIDE + (s2 * 2 + hf) * 8;     // 8-byte aligned: rows are 72 bytes
-        const h4 a0 = *reinterpret_cast<const h4*>(vp), a1 = *reinterpret_cast<const h4*>(vp + 4);
+      for (int t = 0; t < DT; ++t) {
+        const h4 a0 = fv[t][s2][0], a1 = fv[t][s2][1];
         const h8 a = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
         acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, pb[s2], acc[t], 0, 0, 0);
       }
-    }
   };
 
-  // group g walks tiles g, g + G, ...; every group makes the same number of trips (barriers)
-  constexpr int STEP = G * TK;
-  const int kg = grp * TK;
-  if (kg <= last_key) fetch(kg, kpre[0], vpre[0]);
-  if (kg + STEP <= last_key) fetch(kg + STEP, kpre[1], vpre[1]);
-  for (int kb = 0; kb <= last_key; kb += 2 * STEP) {
+  // every group makes the same number of trips (barriers)
+  int stage = 0;
+  for (int kb = 0; kb <= last_key; kb += STEP, stage ^= 1) {
     const int k0 = kb + kg;
-    __syncthreads();   // the previous tile has been consumed
-    if (k0 <= last_key) stash(kpre[0], vpre[0]);
-    __syncthreads();
-    if (k0 + 2 * STEP <= last_key) fetch(k0 + 2 * STEP, kpre[0], vpre[0]);
-    if (k0 <= last_key) tile(k0);
-    if (kb + STEP > last_key) break;
-    __syncthreads();
-    if (k0 + STEP <= last_key) stash(kpre[1], vpre[1]);
-    __syncthreads();
-    if (k0 + 3 * STEP <= last_key) fetch(k0 + 3 * STEP, kpre[1], vpre[1]);
-    if (k0 + STEP <= last_key) tile(k0 + STEP);
+    // this wave's half of tile k0 has landed and its reads of the other stage are over ...
+    wait_vm_at_most<0>();
+    wait_lgkm_at_most<0>();
+    __builtin_amdgcn_s_barrier();             // ... and so for everybody
+    asm volatile("" ::: "memory");
+    const bool mine = k0 <= last_key && k0 <= p0 + wave_q + 31;      // not above the wave's diagonal
+    if (mine) load_tile(buf + stage * PF_ATTN_TILE_HALVES(HD));
+    __builtin_amdgcn_sched_barrier(0);
+    if (k0 + STEP <= last_key) issue(k0 + STEP, stage ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (mine) tile(k0);
   }
 
-  if constexpr (G > 1) {
-    // merge: groups 1.. leave (m, l, O^T) in LDS, [group - 1][value][thread of the group]
-    float* mg = reinterpret_cast<float*>(pf_attn_lds);
-    constexpr int VALS = DT * 16 + 2;
+  if constexpr (G == 1) {
+    if (qi < n) {
+      const float rl = 1.0f / l;
+#pragma unroll
+      for (int t = 0; t < DT; ++t)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {   // rows 32 t + 8 g4 + 4 hf + (0..3) of O^T = 4 consecutive columns of O
+          h4 o;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) o[j] = (half_t)(acc[t][g4 * 4 + j] * rl);
+          *reinterpret_cast<h4*>(O + act_offset(qi, h * HD + t * 32 + g4 * 8 + hf * 4, d, frag_tb)) = o;
+        }
+    }
+  } else {
+    // merge: every group leaves (m, l, O^T) in LDS, [group][quad of values][thread of the group][4] and [group][2][thread];
+    // then group g adds up and stores its share of the quads
+    constexpr int QUADS = DT * 4, SHARE = QUADS / G;
+    static_assert(QUADS % G == 0, "quads divide over the groups");
+    float* mo = reinterpret_cast<float*>(pf_attn_lds);
+    float* ml = mo + G * QUADS * 128 * 4;
     __syncthreads();   // all tiles consumed: the tile buffers are free
-    if (grp > 0) {
-      float* mine = mg + (size_t)(grp - 1) * VALS * 128 + tid;
-      mine[0] = m;
-      mine[128] = l;
 #pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) mine[(2 + t * 16 + e) * 128] = acc[t][e];
-    }
+    for (int i = 0; i < QUADS; ++i)
+      *reinterpret_cast<f4*>(mo + ((grp * QUADS + i) * 128 + tid) * 4) =
+          f4{acc[i >> 2][(i & 3) * 4], acc[i >> 2][(i & 3) * 4 + 1], acc[i >> 2][(i & 3) * 4 + 2], acc[i >> 2][(i & 3) * 4 + 3]};
+    ml[grp * 256 + tid] = m;
+    ml[grp * 256 + 128 + tid] = l;
     __syncthreads();
-    if (grp > 0) return;
+    if (qi >= n) return;
+    float w[G], M = -INFINITY, L = 0.f;
 #pragma unroll
-    for (int g = 1; g < G; ++g) {
-      const float* other = mg + (size_t)(g - 1) * VALS * 128 + tid;
-      const float mo = other[0], lo = other[128];
-      const float mn = fmaxf(m, mo);                 // finite: group 0 always holds key 0
-      const float ca = __expf(m - mn), cb = __expf(mo - mn);   // a group without an unmasked key has mo = -inf, cb = 0
-      l = l * ca + lo * cb;
-      m = mn;
+    for (int g = 0; g < G; ++g) { w[g] = ml[g * 256 + tid]; M = fmaxf(M, w[g]); }      // finite: group 0 always holds key 0
 #pragma unroll
-      for (int t = 0; t < DT; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[t][e] = acc[t][e] * ca + other[(2 + t * 16 + e) * 128] * cb;
+    for (int g = 0; g < G; ++g) {
+      w[g] = __builtin_amdgcn_exp2f((w[g] - M) * c2);          // a group without an unmasked key has m = -inf: weight 0
+      L += ml[g * 256 + 128 + tid] * w[g];
     }
-  }
-
-  if (qi < n) {
-    const float rl = 1.0f / l;
+    const float rl = 1.0f / L;
 #pragma unroll
-    for (int t = 0; t < DT; ++t)
+    for (int i = 0; i < SHARE; ++i) {
+      const int quad = grp * SHARE + i;
+      f4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {   // rows 32 t + 8 g4 + 4 hf + (0..3) of O^T = 4 consecutive columns of O
-        h4 o;
+      for (int g = 0; g < G; ++g) v += *reinterpret_cast<const f4*>(mo + ((g * QUADS + quad) * 128 + tid) * 4) * w[g];
+      h4 o;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = (half_t)(acc[t][g4 * 4 + j] * rl);
-        *reinterpret_cast<h4*>(O + act_offset(qi, h * HD + t * 32 + g4 * 8 + hf * 4, d, frag_tb)) = o;
-      }
+      for (int j = 0; j < 4; ++j) o[j] = (half_t)(v[j] * rl);
+      *reinterpret_cast<h4*>(O + act_offset(qi, h * HD + (quad >> 2) * 32 + (quad & 3) * 8 + hf * 4, d, frag_tb)) = o;
+    }
   }
 }
 
