@@ -164,7 +164,8 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
     const int tok = m0 + (wm * MT + mt) * 32 + r;
-    avoff[mt] = (tok >> 4) * 1024 + (half * 16 + (tok & 15)) * 16 + (WK == 2 ? wk * 512 : 0);
+    avoff[mt] = (tok >> 4) * 1024 + (half * 16 + (tok & 15)) * 16 + (WK == 2 ? wk * 512 : 0) +
+                ((tok & ~15) < n ? 0 : 0x40000000);         // 16-row blocks past the prompt: out of range, no traffic
   }
   auto load_a = [&](__amdgpu_buffer_rsrc_t ar, int ws, int mt) -> h8 {
     const int s = WK == 1 ? ws >> 1 : ws, ks = WK == 1 ? ws & 1 : 0;
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_stream_kernel(TileArgs a) {
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
     const int tok = m0 + i * 32 + r;
-    av[i] = (tok >> 4) * 1024 + (half * 16 + (tok & 15)) * 16;
+    av[i] = (tok >> 4) * 1024 + (half * 16 + (tok & 15)) * 16 + ((tok & ~15) < n ? 0 : 0x40000000);
   }
   auto ld = [](__amdgpu_buffer_rsrc_t rs, int off) { return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0)); };
   auto ldw = [](__amdgpu_buffer_rsrc_t rs, int off) { return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, WNT ? 2 : 0)); };
@@ -358,7 +359,7 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_stream_kernel(TileArgs a) {
   auto issue = [&](int k16, h8 (&A)[MT], h8 (&W)[NB]) {
     const bool in = k16 < k_end;
     const int wo = in ? k16 * 512 : 0x40000000;                                     // past the range: reads zero
-    const int ao = in ? (k16 >> 1) * (int)astep + (k16 & 1) * 512 : 0x40000000;
+    const int ao = in ? (k16 >> 1) * (int)astep + (k16 & 1) * 512 : 0x20000000;
 #pragma unroll
     for (int j = 0; j < NB; ++j) W[j] = ldw(wr, wv[j] + wo);
 #pragma unroll
