@@ -78,10 +78,10 @@ enum {
                               excludes LL_FLAG_EAGER and LL_FLAG_PERSISTENT. */
   LL_FLAG_LEAN_WORKSPACE = 32,
                            /* do without the second copy of the projection weights that ll_init otherwise
-                              writes into the workspace in the short-prompt kernels' operand order (about
-                              the size of the layers' weights again: 13 GB at the 7B shape; prompts of at
-                              most 32 tokens and batched steps then read the caller's row-major weights,
-                              some 15 % slower) */
+                              writes into the workspace in the matrix instructions' operand order (about
+                              the size of the layers' weights again: 13 GB at the 7B shape; prompts and
+                              batched steps then read the caller's row-major weights: up to 32
+                              tokens some 15 %, longer prompts up to a quarter slower) */
   LL_FLAG_FUSED_ATTN_OPROJ = 16
                            /* a measured experiment, off by default: decode attention and O projection of
                               a layer in ONE launch, the projection's workgroups holding all of W_o in
@@ -270,11 +270,11 @@ int ll_batch_dbg_time_steps(int32_t k, float *ms_out);
  * blocked a step, captures overlapped with a replay, nanoseconds spent capturing }. */
 int ll_dbg_graph_stats(int64_t *out4);
 
-/* How the prefill projection GEMM out[rows][nmat * N] = A[rows][K] W^T deals its work (prompts of
- * more than 32 tokens; host arithmetic only, needs no instance and no GPU):
+/* How the prefill projection GEMM out[rows][nmat * N] = A[rows][K] W^T on row-major weights deals its work
+ * (prompts of more than 32 tokens under LL_FLAG_LEAN_WORKSPACE; host arithmetic only, needs no instance and no GPU):
  * out6 = { rows per tile, row tiles, runs (workgroups per row tile), K slabs per run, K slabs per
  * column tile as the runs count them (padded when runs end at tile borders), most slices any
- * column tile is cut into }.  rows is a prompt bucket (64, 128, 256, 512 or 1024). */
+ * column tile is cut into }.  rows is a prompt bucket of that mode (64, 128, 256, 512 or 1024). */
 int ll_dbg_gemm_plan(int32_t N, int32_t K, int32_t nmat, int32_t rows, int32_t *out6);
 /* Number of slices that hold the partial products of output column col (0 <= col < nmat * N)
  * under that plan, or a negative LL_E_* code. */
