@@ -180,7 +180,7 @@ constexpr int tile_rows(const TileShape& t) { return 32 * t.wm * t.mt; }
 // is better off with fewer slices (25.3 against 27.3 us).  Each line is the fastest of those measured at the 7B
 // shape; the rule behind them: one round of 256 workgroups, tiles as square as that allows, K split
 // between the waves while the rows are few.  Measured there (us, Q/K/V with RoPE and cache write / O / gate/up with
-// SwiGLU / down): 64 rows 26.0 / 9.9 / 34.3 / 20.3, 128: 29.9 / 12.9 / 40.4 / 25.5, 192: 37.4 / 16.5 / 50.2 / 31.1,
+// SwiGLU / down): 64 rows 23.4 / 9.9 / 34.3 / 20.3, 128: 29.9 / 12.9 / 40.4 / 25.5, 192: 37.4 / 16.5 / 50.2 / 31.1,
 // 256: 39.8 / 18.7 / 57.0 / 36.0, 384: 50.9 / 21.7 / 78.6 / 43.7, 512: 59.3 / 25.3 / 87.2 / 50.7,
 // 1024: 97.5 / 39.9 / 164.8 / 87.0.
 constexpr TileShape tile_shape(int mode, int Mb, bool wide_k) {
@@ -215,6 +215,18 @@ int tile_pieces(int N, int K, int Mb) {
   if (ks > stages) ks = stages;
   const int q = (stages + ks - 1) / ks;
   return (stages + q - 1) / q;
+}
+
+// 16-row weight blocks per column tile: whole tiles, except that the stream kernel takes the fewest that still make one
+// round of workgroups.  Its time goes with the bytes that one CU fetches, so a CU without a workgroup is lost: Q/K/V
+// at 50 rows in 256 tiles of 48 columns 23.4 us, in 192 of 64 columns 28.4 us.  A tile kernel multiplies the rows that
+// read as zero like the others and gains nothing (gate/up at 512 rows in 252 tiles of 176 columns instead of 230 of
+// 192: the whole prefill 1 % slower).  `per_ctile`: workgroups per column tile.
+int tile_units(int mode, int N, const TileShape& t, int per_ctile) {
+  const int units = pt_units(mode, N), most = 2 * t.nb;
+  for (int u = t.nb; t.kind == 'S' && u < most; ++u)
+    if ((units + u - 1) / u * per_ctile <= num_cus()) return u;
+  return most;
 }
 
 struct TileLaunch {
@@ -268,7 +280,8 @@ void launch_tile(hipStream_t s, TileArgs a, int Mb, int ks) {
   const TileShape t = tile_shape(MODE, Mb, wide);
   a.tb = Mb / 16;
   a.mtiles = Mb / tile_rows(t);
-  a.ctiles = (pt_units(MODE, a.N) + 2 * t.nb - 1) / (2 * t.nb);
+  a.upt = tile_units(MODE, a.N, t, a.mtiles * ks);
+  a.ctiles = (pt_units(MODE, a.N) + a.upt - 1) / a.upt;
   a.ks = ks;
   TileLaunch L{s, &a, (a.ctiles * ks + 7) / 8 * 8 * a.mtiles, hipSuccess, false};    // column tiles are dealt to the 8 XCDs
   tile_dispatch<MODE>(L, Mb, wide);

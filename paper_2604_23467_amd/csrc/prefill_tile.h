@@ -30,6 +30,7 @@ struct TileArgs {
   const DevState* st;
   int N, K, tb;
   int mtiles, ctiles, ks; // row tiles, column tiles, pieces of the K loop
+  int upt;                // stream kernel: 16-row weight blocks of a column tile, at most 2 NB (the rest reads as zero)
   half_t* Hout;           // GATEUP: [rows][N] fp16, fragment-major
   half_t* Q;              // QKV: [rows][N] fp16 rotated queries
   half_t* kc;             // QKV: this layer's K cache [head][max_seq][head_dim]
@@ -314,8 +315,10 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
 // The same product for few rows (or narrow tiles), where the weight stream is nearly all there is: the four
 // waves split K, so nothing is shared and nothing is staged; every operand goes straight to registers, D steps
 // of (MT + NB) KB ahead per wave, with no barrier before the partial sums meet in LDS at the end.  At 64 rows gate/up
-// takes 34.3 us this way and 36.8 us with the weights in LDS, Q/K/V 26.0 and 27.5; deeper look-ahead (D = 12) is
-// slower (37.3 us).
+// takes 34.3 us this way and 36.8 us with the weights in LDS, Q/K/V 26.0 and 27.5 (both in 192 workgroups); deeper
+// look-ahead (D = 12) is slower (37.3 us).  A CU's own fetches set the time, so `upt` lets the host make the tiles narrower
+// than 32 NB columns where that occupies CUs that would have none: Q/K/V of 50 rows 28.4 us in 192 tiles of 64
+// columns, 23.4 in 256 of 48; what is left out of a tile reads as zero, without traffic.
 #define PS_LDS_BYTES(MT, NB) (4 * ((MT) < 2 ? 1 : 2) * (NB) * 4096)
 template <int MODE, int MT, int NB, int D, bool WNT>
 __global__ __launch_bounds__(PT_THREADS, 1) void pf_stream_kernel(TileArgs a) {
@@ -329,11 +332,11 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_stream_kernel(TileArgs a) {
   const int n = a.st->n_prompt, p0 = a.st->pos;
   if (run >= a.ctiles * a.ks || m0 >= n) return;
   const int ct = run / a.ks, split = run - ct * a.ks;
-  const int ksteps = (a.K + 31) >> 5, units = skinny_units(MODE, a.N), upad = pt_units(MODE, a.N), u0 = ct * NB * 2;
+  const int ksteps = (a.K + 31) >> 5, units = skinny_units(MODE, a.N), upad = min(pt_units(MODE, a.N), (ct + 1) * a.upt), u0 = ct * a.upt;
   // K range of this wave in 16-wide steps
   const int parts = 4 * a.ks, per = (ksteps + parts - 1) / parts * 2;
   const int k_begin = (split * 4 + wave) * per, k_end = min(k_begin + per, 2 * ksteps);
-  const unsigned wbytes = (unsigned)max(min(units - u0, 2 * NB), 0) * ksteps * 1024u;
+  const unsigned wbytes = (unsigned)max(min(units - u0, a.upt), 0) * ksteps * 1024u;
   const unsigned astep = (unsigned)a.tb * 1024u;
   const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<half_t*>(a.Wf + (size_t)u0 * ksteps * 512), 0, wbytes, 0x00027000);
