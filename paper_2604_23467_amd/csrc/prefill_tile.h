@@ -191,12 +191,14 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
     const __amdgpu_buffer_rsrc_t w = w_rsrc(k32);
 #pragma unroll
     for (int idx = 0; idx < PP; ++idx) issue_piece(w, ksteps - k32, s, idx);
+    __builtin_amdgcn_sched_barrier(0);      // the waits below count loads: they hold for this order of issue only
     if (s == 0) {
       const __amdgpu_buffer_rsrc_t ar = a_rsrc(k32);
 #pragma unroll
       for (int ws = 0; ws < WS; ++ws)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) fa[ws][mt] = load_a(ar, ws, mt);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
   // the refill under way: descriptor and K steps left of the stage that is being fetched
