@@ -93,6 +93,39 @@ __device__ __forceinline__ void pt_finish(const TileArgs& a, int u, int tok, int
   }
 }
 
+// Piece idx of a refill goes out in this one of its WS slots
+__host__ __device__ constexpr int pt_slot(int idx, int WS, int PP) { return idx * WS / PP; }
+
+// How many of a wave's loads may still be in flight (they return in order) at the barriers that hand a ring stage over:
+// the kernel's own order of issue, replayed.  Prologue: pieces of stage 0, its WS * MT activation loads, pieces of stages
+// 1 .. NS - 2 and slot 0 of stage NS - 1.  K step ws of stage it: its products, behind them the pieces of one
+// refill slot and, behind a row block's last product, that block's activation load; the hand-over of stage it + 1 in front
+// of the products of the last step.  The first NS - 2 stages handed over came without activation loads between their
+// pieces, so fewer loads are younger there than later on; one count serves all (the waits for the activations
+// themselves, one stage old at that point, admit no more than that anyway).
+struct PtWaits { int first, handover; };
+__host__ __device__ constexpr PtWaits pt_waits(int NS, int PP, int WS, int MT, int NB) {
+  int issued = 0, last[16] = {};              // loads so far; number of the last piece of every stage
+  PtWaits w{63, 63};                          // vmcnt has 6 bits
+  for (int s = 0; s < NS - 1; ++s) {
+    last[s] = issued += PP;
+    if (s == 0) issued += WS * MT;
+  }
+  for (int idx = 0; idx < PP; ++idx)
+    if (pt_slot(idx, WS, PP) == 0) last[NS - 1] = ++issued;
+  if (issued - last[0] < w.first) w.first = issued - last[0];
+  for (int it = 0; it < 2 * NS; ++it)
+    for (int ws = 0; ws < WS; ++ws) {
+      if (ws == WS - 1 && issued - last[it + 1] < w.handover) w.handover = issued - last[it + 1];
+      const int stage = ws == WS - 1 ? it + NS : it + NS - 1, sl = (ws + 1) % WS, first = (sl * PP + WS - 1) / WS;
+      for (int t = 0; t < MT * NB; ++t) {
+        if (first + t < PP && pt_slot(first + t, WS, PP) == sl) last[stage] = ++issued;
+        if (t % NB == NB - 1) ++issued;
+      }
+    }
+  return w;
+}
+
 // Tile of 32 WM MT rows x 32 NB columns, four waves: WM along the rows (MT row blocks of 32 each), WK = 2
 // splitting every K step in half between two waves per row group (half the LDS reads; the two halves of the
 // accumulators are exchanged through LDS at the end).  Weights: a ring of NS stages of S32 32-wide K steps in LDS,
@@ -181,7 +214,7 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  auto slot_of = [](int idx) { return idx * WS / PP; };     // piece idx of a refill goes out in slot slot_of(idx)
+  auto slot_of = [](int idx) { return pt_slot(idx, WS, PP); };
   constexpr int N_SLOT0 = (PP + WS - 1) / WS;
 
   h8 fa[WS][MT], fb[2][NB];
@@ -214,10 +247,9 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
 #pragma unroll
     for (int j = 0; j < NB; ++j) f[j] = *reinterpret_cast<const h8*>(base + j * 1024);
   };
-  // younger than the pieces of the next stage: NS - 2 periods of PP pieces and WS * MT activation loads
-  constexpr int YOUNG = (NS - 2) * (PP + WS * MT);
+  constexpr PtWaits WAIT = pt_waits(NS, PP, WS, MT, NB);
   __builtin_amdgcn_sched_barrier(0);
-  wait_vm_at_most<(WS * MT + PP * (NS - 2) + N_SLOT0 < 63 ? WS * MT + PP * (NS - 2) + N_SLOT0 : 63)>();
+  wait_vm_at_most<WAIT.first>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
   load_b(0, 0, fb[0]);
@@ -234,7 +266,7 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
       if (ws + 1 < WS) {
         load_b(stage, ws + 1, fb[(ws + 1) & 1]);
       } else {
-        wait_vm_at_most<(YOUNG < 63 ? YOUNG : 63)>();
+        wait_vm_at_most<WAIT.handover>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         load_b(nstage, 0, fb[0]);

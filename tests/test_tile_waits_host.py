@@ -93,3 +93,13 @@ def test_first_stage_has_landed_at_the_first_barrier(kernels):
         if landed < asked:
             bad.append("pf_tile_kernel%s: %d of %d pieces" % (key, landed, asked))
     assert not bad, "\n".join(bad)
+
+
+def test_every_stage_has_landed_when_it_is_handed_over(kernels):
+    """Through the first rounds of the ring, where the prologue's loads are still counted, and on into its steady state."""
+    bad = []
+    for key, body in kernels.items():
+        for i, (landed, asked) in enumerate(_stages(key, body, 2 * key[6] + 2)):
+            if landed < asked:
+                bad.append("pf_tile_kernel%s: stage %d handed over with %d of %d pieces" % (key, i, landed, asked))
+    assert not bad, "\n".join(bad)
