@@ -59,7 +59,7 @@ __device__ __forceinline__ void pt_finish(const TileArgs& a, int u, int tok, int
   if (MODE == SK_GATEUP) {
     h4 o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = (half_t)(lo[i] * hi[i] * __builtin_amdgcn_rcpf(1.0f + __expf(-lo[i])));
+    for (int i = 0; i < 4; ++i) o[i] = (half_t)(lo[i] / (1.0f + expf(-lo[i])) * hi[i]);
     *reinterpret_cast<h4*>(a.Hout + act_offset(tok, u * 8 + 4 * half, a.N, a.tb)) = o;
   } else if (MODE == SK_RES) {
     float* c = a.C + split * a.slice_floats + (size_t)tok * a.N + u * 16 + 4 * half;
