@@ -175,39 +175,52 @@ struct TileShape {
 };
 constexpr int tile_rows(const TileShape& t) { return 32 * t.wm * t.mt; }
 
-// Which tile a projection takes at a bucket of Mb rows.  `wide_k`: the down projection's long K loop can be cut into
-// more pieces of wider tiles (512 rows: 51 us in 4 pieces of 128 columns, 62 us in 2 of 64), the O projection
-// is better off with fewer slices (25.3 against 27.3 us).  Each line is the fastest of those measured at the 7B
-// shape; the rule behind them: one round of 256 workgroups, tiles as square as that allows, K split
-// between the waves while the rows are few.  Measured there (us, Q/K/V with RoPE and cache write / O / gate/up with
+// Which tile a projection takes at a bucket of Mb rows.  What decides is the round of workgroups, one per CU: tiles are as
+// square as one round allows, with K split between the waves while the rows are few.  `alt` (tile_alt() below) selects the
+// second column of shapes:
+//  * Q/K/V with more weight rows than its own smaller tiles cover in a round takes the gate/up shapes, which hold 96 or
+//    192 columns of all the bucket's rows (d_model 8192, 50 rows: 256 tiles of 96 columns 69 us, 384 of 64 columns 89 us);
+//  * a residual projection whose K loop can be cut into more pieces takes wider tiles (down at 512 rows: 51 us in 4
+//    pieces of 128 columns, 62 us in 2 of 64; the O projection of the 7B shape is better off with fewer slices,
+//    25.3 against 27.3 us).
+// Each line is the fastest of those measured at the 7B shape (us, Q/K/V with RoPE and cache write / O / gate/up with
 // SwiGLU / down): 64 rows 23.4 / 9.9 / 34.3 / 20.3, 128: 29.9 / 12.9 / 40.4 / 25.5, 192: 37.4 / 16.5 / 50.2 / 31.1,
 // 256: 39.8 / 18.7 / 57.0 / 36.0, 384: 50.9 / 21.7 / 78.6 / 43.7, 512: 59.3 / 25.3 / 87.2 / 50.7,
 // 1024: 97.5 / 39.9 / 164.8 / 87.0.
-constexpr TileShape tile_shape(int mode, int Mb, bool wide_k) {
-  if (mode == SK_QKV) {
+constexpr TileShape tile_shape(int mode, int Mb, bool alt) {
+  if (mode == SK_QKV && !alt) {
     return Mb <= 64 ? TileShape{'S', 1, 4, 2, 2, 0, 8, true} : Mb <= 128 ? TileShape{'S', 1, 4, 2, 3, 0, 8, false}
          : Mb <= 192 ? TileShape{'S', 1, 4, 3, 3, 0, 8, false} : Mb <= 256 ? TileShape{'T', 2, 2, 2, 3, 8, 3, false}
          : Mb <= 384 ? TileShape{'T', 2, 2, 3, 3, 8, 3, false} : Mb <= 512 ? TileShape{'T', 4, 1, 2, 3, 8, 3, false}
          : TileShape{'T', 4, 1, 2, 6, 4, 3, false};
   }
-  if (mode == SK_GATEUP) {
+  if (mode != SK_RES) {
     return Mb <= 64 ? TileShape{'S', 1, 4, 2, 3, 0, 8, true} : Mb <= 128 ? TileShape{'T', 4, 1, 1, 3, 8, 3, true}
          : Mb <= 192 ? TileShape{'T', 2, 2, 3, 3, 8, 3, true} : Mb <= 256 ? TileShape{'T', 4, 1, 2, 3, 8, 3, true}
          : Mb <= 384 ? TileShape{'T', 4, 1, 3, 3, 8, 3, true} : TileShape{'T', 4, 1, 2, 6, 4, 3, false};
   }
-  if (Mb <= 64) return wide_k ? TileShape{'S', 1, 4, 2, 2, 0, 8, true} : TileShape{'S', 1, 4, 2, 1, 0, 8, true};
-  if (Mb <= 128) return wide_k ? TileShape{'T', 2, 2, 2, 2, 8, 4, true} : TileShape{'S', 1, 4, 4, 2, 0, 6, true};
+  if (Mb <= 64) return alt ? TileShape{'S', 1, 4, 2, 2, 0, 8, true} : TileShape{'S', 1, 4, 2, 1, 0, 8, true};
+  if (Mb <= 128) return alt ? TileShape{'T', 2, 2, 2, 2, 8, 4, true} : TileShape{'S', 1, 4, 4, 2, 0, 6, true};
   if (Mb <= 192) return TileShape{'T', 2, 2, 3, 2, 8, 4, true};
   if (Mb <= 256) return TileShape{'T', 4, 1, 2, 2, 8, 4, true};
-  if (Mb <= 384) return wide_k ? TileShape{'T', 2, 2, 3, 4, 4, 4, false} : TileShape{'T', 2, 2, 3, 2, 8, 4, false};
-  if (Mb <= 512 && !wide_k) return TileShape{'T', 4, 1, 2, 2, 8, 4, false};
+  if (Mb <= 384) return alt ? TileShape{'T', 2, 2, 3, 4, 4, 4, false} : TileShape{'T', 2, 2, 3, 2, 8, 4, false};
+  if (Mb <= 512 && !alt) return TileShape{'T', 4, 1, 2, 2, 8, 4, false};
   return TileShape{'T', 4, 1, 2, 4, 4, 4, false};
 }
-bool tile_wide_k(int N, int K) { return K >= 2 * N; }
+// Second shape or first?  Q/K/V: where the first takes more than one round.  Residual projections: where K is long, and
+// where the first shape leaves no CU for a second piece of the K loop (d_model above 4096).  Four layers, first tokens
+// of 50 / 100 / 350 rows, first shapes only -> this rule: d_model 5120 626 / 795 / 1340 -> 623 / 754 / 1219 us,
+// 6144 839 / 952 / 1618 -> 745 / 913 / 1479, 8192 1118 / 1273 / 2264 -> 979 / 1105 / 1932 (F = 12288).
+bool tile_alt(int mode, int N, int K, int Mb) {
+  if (mode == SK_RES && K >= 2 * N) return true;
+  const TileShape t = tile_shape(mode, Mb, false);
+  const int tiles = (skinny_units(mode, N) + 2 * t.nb - 1) / (2 * t.nb) * (Mb / tile_rows(t));
+  return tiles * (mode == SK_RES ? 2 : 1) > num_cus();
+}
 
 // Pieces the K loop of a residual projection is cut into: what fills one round of workgroups, none empty
 int tile_pieces(int N, int K, int Mb) {
-  const TileShape t = tile_shape(SK_RES, Mb, tile_wide_k(N, K));
+  const TileShape t = tile_shape(SK_RES, Mb, tile_alt(SK_RES, N, K, Mb));
   const int ctiles = (skinny_units(SK_RES, N) + 2 * t.nb - 1) / (2 * t.nb), mtiles = Mb / tile_rows(t);
   const int ksteps = (K + 31) / 32, stages = t.kind == 'T' ? (ksteps + t.s32 - 1) / t.s32 : (ksteps + 7) / 8;
   int ks = num_cus() / (ctiles * mtiles);
@@ -255,8 +268,8 @@ void tile_go(TileLaunch& L) {
   }
 }
 template <int MODE>
-void tile_dispatch(TileLaunch& L, int Mb, bool wide_k) {
-  const int i = (Mb <= 64 ? 0 : Mb <= 128 ? 1 : Mb <= 192 ? 2 : Mb <= 256 ? 3 : Mb <= 384 ? 4 : Mb <= 512 ? 5 : 6) * 2 + wide_k;
+void tile_dispatch(TileLaunch& L, int Mb, bool alt) {
+  const int i = (Mb <= 64 ? 0 : Mb <= 128 ? 1 : Mb <= 192 ? 2 : Mb <= 256 ? 3 : Mb <= 384 ? 4 : Mb <= 512 ? 5 : 6) * 2 + alt;
   switch (i) {
     case 0: return tile_go<MODE, 0>(L);
     case 1: return tile_go<MODE, 1>(L);
@@ -274,26 +287,39 @@ void tile_dispatch(TileLaunch& L, int Mb, bool wide_k) {
     default: return tile_go<MODE, 13>(L);
   }
 }
+// How a projection's tiles are dealt out at a bucket of Mb rows
+struct TilePlan {
+  TileShape shape;
+  bool alt;
+  int mtiles, ctiles, upt, ks;
+  int grid() const { return (ctiles * ks + 7) / 8 * 8 * mtiles; }       // column tiles are dealt to the 8 XCDs
+};
+TilePlan tile_plan(int mode, int N, int K, int Mb) {
+  TilePlan p{};
+  p.alt = tile_alt(mode, N, K, Mb);
+  p.shape = tile_shape(mode, Mb, p.alt);
+  p.ks = mode == SK_RES ? tile_pieces(N, K, Mb) : 1;
+  p.mtiles = Mb / tile_rows(p.shape);
+  p.upt = tile_units(mode, N, p.shape, p.mtiles * p.ks);
+  p.ctiles = (pt_units(mode, N) + p.upt - 1) / p.upt;
+  return p;
+}
 template <int MODE>
-void launch_tile(hipStream_t s, TileArgs a, int Mb, int ks) {
-  const bool wide = MODE == SK_RES && tile_wide_k(a.N, a.K);
-  const TileShape t = tile_shape(MODE, Mb, wide);
+void launch_tile(hipStream_t s, TileArgs a, int Mb) {
+  const TilePlan p = tile_plan(MODE, a.N, a.K, Mb);
   a.tb = Mb / 16;
-  a.mtiles = Mb / tile_rows(t);
-  a.upt = tile_units(MODE, a.N, t, a.mtiles * ks);
-  a.ctiles = (pt_units(MODE, a.N) + a.upt - 1) / a.upt;
-  a.ks = ks;
-  TileLaunch L{s, &a, (a.ctiles * ks + 7) / 8 * 8 * a.mtiles, hipSuccess, false};    // column tiles are dealt to the 8 XCDs
-  tile_dispatch<MODE>(L, Mb, wide);
+  a.mtiles = p.mtiles; a.upt = p.upt; a.ctiles = p.ctiles; a.ks = p.ks;
+  TileLaunch L{s, &a, p.grid(), hipSuccess, false};
+  tile_dispatch<MODE>(L, Mb, p.alt);
 }
 // Raises the dynamic LDS limit of every instantiation (before anything is captured)
 hipError_t tile_init() {
   for (int Mb : {64, 128, 192, 256, 384, 512, 1024})
-    for (int wide = 0; wide < 2; ++wide) {
+    for (int alt = 0; alt < 2; ++alt) {
       TileLaunch L{nullptr, nullptr, 0, hipSuccess, true};
-      tile_dispatch<SK_QKV>(L, Mb, wide != 0);
-      if (L.err == hipSuccess) tile_dispatch<SK_GATEUP>(L, Mb, wide != 0);
-      if (L.err == hipSuccess) tile_dispatch<SK_RES>(L, Mb, wide != 0);
+      tile_dispatch<SK_QKV>(L, Mb, alt != 0);
+      if (L.err == hipSuccess) tile_dispatch<SK_GATEUP>(L, Mb, alt != 0);
+      if (L.err == hipSuccess) tile_dispatch<SK_RES>(L, Mb, alt != 0);
       if (L.err != hipSuccess) return L.err;
     }
   return hipSuccess;
@@ -903,17 +929,17 @@ void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb
     a.st = I->state(); a.head_dim = c.head_dim; a.max_seq = c.max_seq;
     a.A = B.Xn; a.Wf = I->wfrag(l, I->L.wf_qkv); a.N = d; a.K = d;
     a.Q = B.Q; a.kc = I->kcache(l); a.vc = I->vcache(l); a.rope = I->at<float2>(I->L.rope);
-    launch_tile<SK_QKV>(s, a, Mb, 1);
+    launch_tile<SK_QKV>(s, a, Mb);
     launch_attn(I, s, B, l, Mb, tb);
     a.C = B.part; a.slice_floats = (size_t)Mb * d;
     a.A = B.O; a.Wf = I->wfrag(l, I->L.wf_o);
-    launch_tile<SK_RES>(s, a, Mb, ks_o);
+    launch_tile<SK_RES>(s, a, Mb);
     hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, B.X, (const half_t*)W.ffn_norm,
                        B.Xn, d, c.rms_eps, I->state(), B.part, slices(ks_o), tb);
     a.A = B.Xn; a.Wf = I->wfrag(l, I->L.wf_gu); a.N = F; a.Hout = B.H;
-    launch_tile<SK_GATEUP>(s, a, Mb, 1);
+    launch_tile<SK_GATEUP>(s, a, Mb);
     a.A = B.H; a.Wf = I->wfrag(l, I->L.wf_down); a.N = d; a.K = F;
-    launch_tile<SK_RES>(s, a, Mb, ks_down);
+    launch_tile<SK_RES>(s, a, Mb);
     part = B.part;
   }
   if (with_head) {             // (a chunk that is not the prompt's last needs nothing of X any more)
@@ -1945,6 +1971,16 @@ int ll_dbg_gemm_slice_count(int32_t N, int32_t K, int32_t nmat, int32_t rows, in
     return fail(LL_E_BAD_ARG, "ll_dbg_gemm_slice_count: bad argument");
   const GemmPlan p = gemm_plan(N, K, nmat, rows, nmat * N);
   return slice_count(p.map, col);
+}
+
+int ll_dbg_tile_plan(int32_t kind, int32_t N, int32_t K, int32_t rows, int32_t* out6) {
+  const bool known = rows == 64 || rows == 128 || rows == 192 || rows == 256 || rows == 384 || rows == 512 || rows == 1024;
+  if (!out6 || kind < SK_QKV || kind > SK_GATEUP || N < 16 || K < 8 || N % 8 || K % 8 || !known)
+    return fail(LL_E_BAD_ARG, "ll_dbg_tile_plan: bad argument");
+  const TilePlan p = tile_plan(kind, N, K, rows);
+  out6[0] = p.mtiles; out6[1] = p.ctiles; out6[2] = p.upt; out6[3] = p.ks;
+  out6[4] = p.shape.kind == 'T' ? p.shape.s32 : 0; out6[5] = p.grid();
+  return LL_OK;
 }
 
 int ll_dbg_graph_stats(int64_t* out4) {

@@ -97,6 +97,16 @@ int main() {
           }
           ++plans;
         }
+  // ---- the plan of the projections that read the weight copy: workgroups and pieces for any accepted width
+  CHECK(ll_dbg_tile_plan(3, 256, 256, 64, p) == LL_E_BAD_ARG && ll_dbg_tile_plan(0, 256, 256, 63, p) == LL_E_BAD_ARG);
+  CHECK(ll_dbg_tile_plan(0, 0, 256, 64, p) == LL_E_BAD_ARG && ll_dbg_tile_plan(0, 256, 256, 64, nullptr) == LL_E_BAD_ARG);
+  for (int rows : {64, 128, 192, 256, 384, 512, 1024})
+    for (int kind = 0; kind <= 2; ++kind)
+      for (int N : {64, 256, 1000, 4096, 8192, 12288})
+        for (int K : {64, 256, 1000, 4096, 8192, 12288}) {
+          CHECK(ll_dbg_tile_plan(kind, N, K, rows, p) == LL_OK);
+          CHECK(p[0] >= 1 && p[1] >= 1 && p[2] >= 1 && p[3] >= 1 && p[3] <= 8 && p[5] >= p[0] * p[1] * p[3]);
+        }
   std::printf("runtime host-logic sanitizer run ok (%ld GEMM plans)\n", plans);
   return 0;
 }
