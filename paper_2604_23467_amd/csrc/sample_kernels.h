@@ -128,14 +128,13 @@ __device__ __forceinline__ float smp_block_scan_excl(float v, float* red, int& p
 // k-th largest key over PER slots per thread (0 marks an empty slot) by bisecting the key's 32
 // bits two at a time; a wave counts with ballots, so a slot costs one compare per candidate prefix.
 // Returns 0 when fewer than k slots are filled.  low_bit > 0 stops above that bit: a lower bound whose lower bits
-// are zero, at fewer passes.
+// are zero, at fewer passes; `prefix` and high_bit go on from there.
 template <int PER>
 __device__ __forceinline__ uint32_t smp_kth_largest(const uint32_t (&key)[PER], int k, float* red, int& phase,
-                                                    int low_bit = 0) {
+                                                    int low_bit = 0, int high_bit = 31, uint32_t prefix = 0u) {
   constexpr int NW = SMP_THREADS / 64;
   const int tid = threadIdx.x;
-  uint32_t prefix = 0u;
-  for (int bit = 31; bit >= low_bit + 1; bit -= 2) {
+  for (int bit = high_bit; bit >= low_bit + 1; bit -= 2) {
     const uint32_t c1 = prefix | (1u << (bit - 1)), c2 = prefix | (2u << (bit - 1)), c3 = prefix | (3u << (bit - 1));
     int n1 = 0, n2 = 0, n3 = 0;
 #pragma unroll
@@ -409,22 +408,32 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
 
   // (1) With a top-k cut of at most one candidate per thread, almost all of the vocabulary can be
   // discarded cheaply first: the k-th largest of the threads' own maxima is a lower bound of the
-  // k-th largest key (at least k keys reach it), found with one slot per thread; its upper 16 bits (1 % of the
-  // value) are bound enough.  What reaches the bound is packed in index order, and one wave finishes up to 256
-  // candidates; more go on with one slot per thread.
+  // k-th largest key (at least k keys reach it), found with one slot per thread.  Its upper 16 bits (1 % of the
+  // value) are mostly bound enough; where more than one wave's candidates reach them (logits that share an offset much
+  // larger than their spread) the lower bits are found too (32000 logits of 100 +- 0.5 at temperature 0.8, top-k 200, a
+  // step: 95.6 us without, 66.3 with).  What reaches the bound is packed in index order, and one wave
+  // finishes up to 256 candidates; more go on with one slot per thread.
   bool done = false;
   if (top_k > 0 && top_k <= SMP_THREADS) {
     uint32_t tmax[1] = {0u};
 #pragma unroll
     for (int j = 0; j < SMP_PER; ++j) tmax[0] = key[j] > tmax[0] ? key[j] : tmax[0];
-    const uint32_t bound = smp_kth_largest<1>(tmax, top_k, red, phase, 16);
-    int reach = 0;
+    uint32_t bound = smp_kth_largest<1>(tmax, top_k, red, phase, 16);
+    int at, nreach;
+    auto count_reach = [&]() {
+      int reach = 0;
 #pragma unroll
-    for (int j = 0; j < SMP_PER; ++j) reach += key[j] >= bound;
-    float all;
-    int at = (int)(smp_block_scan_excl((float)reach, red, phase, &all) + 0.5f);
-    const int nreach = (int)(all + 0.5f);
-    if (bound != 0u && nreach <= SMP_THREADS) {            // uniform: `all` is the same in every thread
+      for (int j = 0; j < SMP_PER; ++j) reach += key[j] >= bound;
+      float all;
+      at = (int)(smp_block_scan_excl((float)reach, red, phase, &all) + 0.5f);
+      nreach = (int)(all + 0.5f);
+    };
+    count_reach();
+    if (bound != 0u && nreach > 64 * SMP_WAVE_PER) {       // uniform: `all` is the same in every thread
+      bound = smp_kth_largest<1>(tmax, top_k, red, phase, 0, 15, bound);
+      count_reach();
+    }
+    if (bound != 0u && nreach <= SMP_THREADS) {
 #pragma unroll
       for (int j = 0; j < SMP_PER; ++j) {
         if (key[j] >= bound) {

@@ -24,3 +24,23 @@ def test_sampler_matches_oracle_at_small_vocabularies(torch_cuda, vocab):  # noq
             total += len(toks)
             exact += ex
     assert exact >= 0.95 * total, (exact, total)
+
+
+@pytest.mark.parametrize("vocab", [1024, 32000])
+def test_sampler_on_logits_that_share_a_large_offset(torch_cuda, vocab):  # noqa: F811
+    """Logits around 100 within about 1: the upper half of a float's bits no longer tells the k largest from the rest, so
+    the bound of the top-k cut needs its lower bits."""
+    cfg = wl.custom_cfg(1, 2, 64, 136, vocab, 60)
+    w = wl.make_weights_numpy(cfg, seed=58, emb_std=0.3)
+    rng = np.random.default_rng(8)
+    w["tok_emb"] = w["tok_emb"] + 1.0
+    w["lm_head"] = 100.0 / 128 / 0.96 + rng.standard_normal(w["lm_head"].shape) * 0.5 / np.sqrt(128)
+    w = wl.weights_astype(w, np.float16)
+    prompt = wl.make_tokens(6, vocab, seed=3)
+    total = exact = 0
+    with _session(cfg, w) as s:
+        for j, (t, k, p) in enumerate([(0.8, 50, 0.95), (0.8, 200, 0.95), (1.0, 700, 1.0), (1.0, 1000, 0.9)]):
+            toks, ex = _run(s, prompt, 30, t, k, p, seed=3000 + j)
+            total += len(toks)
+            exact += ex
+    assert exact >= 0.95 * total, (exact, total)
