@@ -22,8 +22,8 @@ struct BatchState {
 };
 
 // Attention of slot b's new query (position pos[b], already written to the cache) for one head.
-// grid = (heads, rows of the step = 16 or 32), NT threads, four waves per SIMD (the register limit says so: left
-// alone the compiler took 145 registers and half as many workgroups fitted a CU); tb = rows / 16 selects the output's
+// grid = (heads, rows of the step = 16 or 32), NT threads, four waves per SIMD (the launch bound says so: without it
+// the compiler takes 145 registers and half as many workgroups fit a CU); tb = rows / 16 selects the output's
 // fragment-major layout.  512 threads at 16 rows; 256 at 32, where twice as many workgroups then run side by side and
 // the many short sequences of a mixed batch leave fewer lanes idle (16 sequences of 10..560 keys 12.6 -> 11.3 us per
 // layer, 32 sequences 22.9 -> 19.9; 32 sequences in 512-thread workgroups: 21.3).  Two trips of 16 keys per wave are
@@ -44,7 +44,8 @@ __global__ __launch_bounds__(NT, 4) void bt_attn_kernel(
   __shared__ float s_m[NW], s_l[NW], s_acc[NW][HD];
   extern __shared__ int s_pt[];    // this slot's page-table row: a key's address then costs no global round trip
   const int h = blockIdx.x, b = blockIdx.y;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // key positions of a trip then start from a scalar
   const int gi = lane / LPR, li = lane % LPR;
   // One round trip for everything the key loop needs: the slot's state, the query and the WHOLE page-table
   // row (entries past the sequence's end are not used; reading them saves waiting for the position first).
