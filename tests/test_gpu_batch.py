@@ -128,6 +128,23 @@ def test_32_slot_batch_on_the_tiny_model(torch_cuda, oracle32):
     print("32-slot batch worst rel-L2 %.2e" % worst)
 
 
+@pytest.mark.parametrize("heads, head_dim, slots", [(2, 128, 16), (2, 128, 32), (4, 64, 16), (4, 64, 32)])
+def test_long_sequences_over_many_trips_of_the_paged_attention(torch_cuda, oracle32, heads, head_dim, slots):
+    """A workgroup takes 64..256 keys a trip and keeps two trips in flight: sequences of no, one and several rounds of that,
+    some of them passing a border while they step, in pages of 5 positions."""
+    cfg = wl.custom_cfg(1, heads, head_dim, 688, 512, 640)
+    w = wl.make_weights_numpy(cfg, seed=9)
+    lens = (3, 62, 126, 127, 190, 254, 255, 318, 383, 510, 600, 77)
+    with _session(cfg, w) as s:
+        s.ll_batch_open(slots, 5, sum(n // 5 + 3 for n in lens) + 1)
+        seqs = [Seq(s, oracle32, cfg, w, wl.make_tokens(n, cfg["vocab"], seed=400 + n), "len%d" % n) for n in lens]
+        for _ in range(5):
+            _step_all(s, seqs)
+        s.ll_batch_close()
+    for q in seqs:
+        q.om.close()
+
+
 def test_batched_steps_are_bit_reproducible(torch_cuda):
     """The batched step sums in a fixed order too: two identical batches give identical logits."""
     cfg = wl.custom_cfg(1, 32, 128, 1024, 512, 64)

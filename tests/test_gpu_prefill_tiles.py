@@ -30,6 +30,16 @@ def session(model):
 
 @pytest.mark.parametrize("n", EDGES)
 def test_bucket_edges_against_the_oracle(session, model, oracle32, n):
+    against_the_oracle(session, model, oracle32, n)
+
+
+@pytest.mark.parametrize("n", [1025, 1056, 1057, 1099])
+def test_last_chunk_behind_a_full_one_against_the_oracle(session, model, oracle32, n):
+    """1024 rows in the first chunk; the rest as a short prompt (1, 32 rows) and as tiles (33, 75)."""
+    against_the_oracle(session, model, oracle32, n)
+
+
+def against_the_oracle(session, model, oracle32, n):
     cfg, w = model
     prompt = wl.make_tokens(n, cfg["vocab"], seed=n)
     om = oracle32.model(cfg, w)

@@ -44,3 +44,18 @@ def test_sampler_on_logits_that_share_a_large_offset(torch_cuda, vocab):  # noqa
             total += len(toks)
             exact += ex
     assert exact >= 0.95 * total, (exact, total)
+
+
+def test_equal_logits_at_a_vocabulary_that_one_wave_finishes(torch_cuda):  # noqa: F811
+    """Every candidate ties at the cut (the k lowest ids stay, token = floor(u * k)) and at the nucleus threshold (half of
+    the k stay, token = floor(u * k / 2))."""
+    from oracle import sampling as sp
+    cfg = wl.custom_cfg(1, 2, 64, 136, 40, 40)
+    w = wl.make_weights_numpy(cfg, seed=59)
+    w["lm_head"][:] = 0
+    with _session(cfg, wl.weights_astype(w, np.float16)) as s:
+        for k, p, kept in ((8, 1.0, 8), (32, 0.5, 16)):
+            s.ll_reset()
+            s.ll_set_sampling(1.0, k, p, 99)
+            toks = [s.ll_prefill([1, 2, 3])] + [s.ll_decode_step() for _ in range(20)]
+            assert toks == [int(np.float32(sp.uniform(99, i)) * np.float32(kept)) for i in range(21)]
