@@ -50,6 +50,23 @@ __host__ __device__ inline int pt_units(int mode, int N) {
 #define PT_THREADS 256
 #define PT_LDS_BYTES(NB, S32, NS) ((NS) * (NB) * (S32) * 2048)
 
+// g / (1 + expf(-g)) * u at the library functions' own error (max 2.2e-7, rms 4.6e-8 of the value against 64 bits over
+// |g| <= 86; infinities and NaN give the same), without what they spend on arguments that cannot occur here: a
+// lane of a 256 x 192 tile finishes 96 of these.  exp(-g) = 2^t 2^f with t the nearest integer to -g log2(e) and f
+// from log2(e) in two parts; past +-88.8 the exponential is infinite or nothing beside the 1.  The quotient is
+// g * rcp(d) with its remainder added once; div_fixup settles infinite operands.  Gate/up of the 7B shape at 250 /
+// 500 / 1000 rows 59.7 / 87.7 / 169.8 us with the library's functions, 59.2 / 85.5 / 165.5 this way (rcp(1 + __expf(-g)), up to
+// 3.9e-6 off: 58.0 / 83.5 / 161.9).
+__device__ __forceinline__ float pt_swiglu(float g, float u) {
+  const float x = __builtin_amdgcn_fmed3f(g, -88.8f, 88.8f);
+  const float t = __builtin_rintf(x * -1.44269502f);
+  const float f = __builtin_fmaf(x, -1.92596303e-8f, __builtin_fmaf(x, -1.44269502f, -t));
+  const float d = 1.0f + __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(f), (int)t);
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float q = g * r;
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, q, g), r, q), d, g) * u;
+}
+
 // Finishes rows 4 half .. + 3 (lo) and 8 + 4 half .. + 3 (hi) of 16-row block u for one token.  Accumulator
 // layout of the 32x32 product with the weights as its first operand: a lane holds token (lane % 32) and weight
 // rows 8 (e / 4) + 4 (lane / 32) + e % 4.  A 32-row block is two 16-row blocks of the copy, whose rows i and
@@ -59,7 +76,7 @@ __device__ __forceinline__ void pt_finish(const TileArgs& a, int u, int tok, int
   if (MODE == SK_GATEUP) {
     h4 o;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) o[i] = (half_t)(lo[i] / (1.0f + expf(-lo[i])) * hi[i]);
+    for (int i = 0; i < 4; ++i) o[i] = (half_t)pt_swiglu(lo[i], hi[i]);
     *reinterpret_cast<h4*>(a.Hout + act_offset(tok, u * 8 + 4 * half, a.N, a.tb)) = o;
   } else if (MODE == SK_RES) {
     float* c = a.C + split * a.slice_floats + (size_t)tok * a.N + u * 16 + 4 * half;

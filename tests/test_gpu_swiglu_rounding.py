@@ -31,13 +31,24 @@ def _pairs(count, rng):
 
 def _silu_times(g, u):
     g, u = g.astype(np.float64), u.astype(np.float64)
-    return -(g / (1.0 + np.exp(-g)) * u)                       # the caller negates `up`: positive values
+    with np.errstate(over="ignore"):
+        return -(g / (1.0 + np.exp(-g)) * u)                   # the caller negates `up`: positive values
+
+
+def _extremes():
+    """Gates past the clamp of the exponent on both sides, zeros of both signs, and where the exponential is near 1."""
+    gate = np.array([-60000, -200, -100, -89, -88.75, -87, -50, -1e-3, -0.0, 0.0, 1e-3, 0.5, 20, 88.75, 89, 200, 4000],
+                    np.float16)
+    up = np.where(gate > 1, -0.25, -3.0).astype(np.float16)
+    return gate, up
 
 
 @pytest.fixture(scope="module")
 def model():
     rng = np.random.default_rng(5)
     gate, up = _pairs(D, rng)
+    few = _extremes()
+    gate[:few[0].size], up[:few[0].size] = few[0], -few[1]
     cfg = wl.custom_cfg(1, D // 128, 128, D, 64, 1025, rms_eps=0.0)
     z = lambda *s: np.zeros(s, np.float16)
     at = rng.permutation(D)
