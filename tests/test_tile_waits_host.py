@@ -1,6 +1,6 @@
-"""The prefill tile kernels wait for direct global-to-LDS loads by COUNT: s_waitcnt vmcnt(n) leaves the n youngest loads
+"""The prefill projections wait for direct global-to-LDS loads by COUNT: s_waitcnt vmcnt(n) leaves the n youngest loads
 of the wave in flight, so a wait is right only for the order in which the compiler issued the loads.  These tests
-read the instructions of the built library (no GPU), replay every tile kernel's loads and waits in that order, and ask at
+read the instructions of the built library (no GPU), replay every such kernel's loads and waits in that order, and ask at
 each barrier that hands a ring stage over whether all of the wave's pieces of that stage have landed."""
 import os
 import re
@@ -11,7 +11,8 @@ import pytest
 from paper_2604_23467_amd import build as hip_build
 
 OBJDUMP = os.path.join(os.path.dirname(hip_build.HIPCC), "..", "llvm", "bin", "llvm-objdump")
-NAME = re.compile(r"^[0-9a-f]+ <_Z14pf_tile_kernelILi(\d)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)EE")
+TILE = re.compile(r"^[0-9a-f]+ <_Z14pf_tile_kernelILi(\d)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)EE")
+GEMM = re.compile(r"^[0-9a-f]+ <_Z14pf_gemm_kernelILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)EE")
 LABEL = re.compile(r"^(?:[0-9a-f]+ )?<(L\d+)>:")
 
 
@@ -23,23 +24,30 @@ def _listing(tmp):
     obj = next(f for f in os.listdir(tmp) if f.endswith("gfx950"))
     out = subprocess.run([OBJDUMP, "-d", "--symbolize-operands", "--no-show-raw-insn", obj], cwd=tmp, check=True,
                          stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
-    kernels, body = {}, None
+    kernels, body = {TILE: {}, GEMM: {}}, None
     for line in out.splitlines():
         if re.match(r"^[0-9a-f]+ <_Z", line):
-            m = NAME.match(line)
-            body = kernels.setdefault(tuple(int(x) for x in m.groups()), []) if m else None
+            body = None
+            for name, found in kernels.items():
+                m = name.match(line)
+                if m:
+                    body = found.setdefault(tuple(int(x) for x in m.groups()), [])
         elif body is not None and line.strip():
             body.append(line.split("//")[0].strip())
     return kernels
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
+def listing(tmp_path_factory):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
-    found = _listing(str(tmp_path_factory.mktemp("listing")))
-    assert len(found) >= 10
-    return found
+    return _listing(str(tmp_path_factory.mktemp("listing")))
+
+
+@pytest.fixture(scope="module")
+def kernels(listing):
+    assert len(listing[TILE]) >= 10
+    return listing[TILE]
 
 
 def replay(body, pieces_per_stage, handovers):
@@ -102,4 +110,17 @@ def test_every_stage_has_landed_when_it_is_handed_over(kernels):
         for i, (landed, asked) in enumerate(_stages(key, body, 2 * key[6] + 2)):
             if landed < asked:
                 bad.append("pf_tile_kernel%s: stage %d handed over with %d of %d pieces" % (key, i, landed, asked))
+    assert not bad, "\n".join(bad)
+
+
+def test_row_major_gemm_hands_over_landed_slabs_only(listing):
+    """Its first barrier stands in front of the ring; from the second on every barrier hands a slab over."""
+    assert len(listing[GEMM]) >= 3
+    bad = []
+    for key, body in listing[GEMM].items():
+        rows, stages, wm, wn, bk = key[:5]
+        pieces = (rows + 256) * bk * 2 // 1024 // (wm * wn)
+        for i, (landed, _) in enumerate(replay(body, pieces, 2 * stages + 3)):
+            if landed < i * pieces:
+                bad.append("pf_gemm_kernel%s: barrier %d with %d of %d pieces" % (key, i, landed, i * pieces))
     assert not bad, "\n".join(bad)
