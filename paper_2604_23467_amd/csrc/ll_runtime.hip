@@ -166,8 +166,8 @@ GemmPlan gemm_plan(int N, int K, int nmat, int Mb, int ldc) {
 }
 
 // ---- projections of 33..1024 rows from the fragment-major weight copy (prefill_tile.h) ----
-// One list of instantiations: X(kind, mode, row waves, K waves, row blocks, column blocks, K steps per stage, ring
-// stages or look-ahead, weights used once), kind T = pf_tile_kernel, S = pf_stream_kernel (four K waves).
+// Template arguments of one projection kernel.  kind: 'T' = pf_tile_kernel, 'S' = pf_stream_kernel (four K waves); then row
+// waves, K waves, row blocks and column blocks per wave, K steps per stage, ring stages ('S': steps of look-ahead), weights used once
 struct TileShape {
   char kind;
   int wm, wk, mt, nb, s32, ns;
