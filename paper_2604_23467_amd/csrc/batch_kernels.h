@@ -23,7 +23,7 @@ struct BatchState {
 
 // Attention of slot b's new query (position pos[b], already written to the cache) for one head.
 // grid = (heads, rows of the step = 16 or 32), NT threads, four waves per SIMD (the launch bound says so: without it
-// the compiler takes 145 registers and half as many workgroups fit a CU); tb = rows / 16 selects the output's
+// the compiler takes 143 registers at head_dim 64, and half as many workgroups fit a CU); tb = rows / 16 selects the output's
 // fragment-major layout.  512 threads at 16 rows; 256 at 32, where twice as many workgroups then run side by side and
 // the many short sequences of a mixed batch leave fewer lanes idle (16 sequences of 10..560 keys 12.6 -> 11.3 us per
 // layer, 32 sequences 22.9 -> 19.9; 32 sequences in 512-thread workgroups: 21.3).  Two trips of 16 keys per wave are
