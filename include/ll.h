@@ -67,7 +67,11 @@ enum {
                               barriers (needs d_model <= 4096 and one resident workgroup per
                               CU; ll_init fails with LL_E_BAD_CONFIG otherwise).  With neither
                               of the two flags the library picks the faster one it has measured
-                              for the 7B shape, currently the multi-kernel graph. */
+                              for the 7B shape, currently the multi-kernel graph; where no other
+                              decode flag is set either, models of at most 512 x 1536 (d_model x
+                              ffn_hidden) run their decode steps in one kernel on one XCD, and
+                              fall back to the multi-kernel graph, for good, should its workgroups
+                              ever not be resident together. */
   LL_FLAG_PER_LENGTH_GRAPHS = 8,
                            /* the paper's own mechanism, kept as an ablation (Alg. 1, Sec. IV-A):
                               one decode graph PER KV LENGTH in a rolling buffer of 8 with
@@ -265,6 +269,10 @@ int ll_batch_dbg_force_next_token(int32_t slot, int32_t tok);
 int ll_batch_dbg_time_steps(int32_t k, float *ms_out);
 
 /* ---- measurement and test hooks (not part of the four-call contract) ---- */
+
+/* Most polls of one hand-off in the kernel that runs small models' decode steps, before the step is given up and redone by
+ * the multi-kernel graph.  Returns 1 where that kernel is in use, 0 where it is not (nothing is changed then). */
+int ll_dbg_set_spin_limit(int32_t polls);
 
 /* Per-length graph mode: out4 = { replays that found their graph in the buffer, captures that
  * blocked a step, captures overlapped with a replay, nanoseconds spent capturing }. */

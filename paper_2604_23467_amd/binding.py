@@ -30,7 +30,7 @@ EXPORTS = ("ll_workspace_bytes", "ll_init", "ll_prefill", "ll_prefill_static", "
            "ll_set_sampling", "ll_shutdown", "ll_max_prompt", "ll_position", "ll_decode_mode", "ll_last_error", "ll_dbg_get_logits",
            "ll_batch_pool_bytes", "ll_batch_open", "ll_batch_add", "ll_batch_step", "ll_batch_remove", "ll_batch_close",
            "ll_batch_dbg_get_logits", "ll_batch_dbg_force_next_token", "ll_batch_dbg_time_steps",
-           "ll_dbg_get_hidden", "ll_dbg_graph_stats", "ll_dbg_gemm_plan", "ll_dbg_gemm_slice_count", "ll_dbg_tile_plan", "ll_dbg_force_next_token", "ll_dbg_get_kv", "ll_dbg_profile_decode",
+           "ll_dbg_get_hidden", "ll_dbg_set_spin_limit", "ll_dbg_graph_stats", "ll_dbg_gemm_plan", "ll_dbg_gemm_slice_count", "ll_dbg_tile_plan", "ll_dbg_force_next_token", "ll_dbg_get_kv", "ll_dbg_profile_decode",
            "ll_dbg_time_decode", "ll_dbg_time_kernel_class", "ll_dbg_stream_copy", "ll_dbg_stream_read", "ll_dbg_poison_scratch", "ll_dbg_trace_decode")
 
 
@@ -115,6 +115,8 @@ def load():
     L.ll_dbg_gemm_plan.argtypes = [C.c_int32] * 4 + [C.POINTER(C.c_int32)]
     L.ll_dbg_gemm_slice_count.restype = C.c_int
     L.ll_dbg_gemm_slice_count.argtypes = [C.c_int32] * 5
+    L.ll_dbg_set_spin_limit.restype = C.c_int
+    L.ll_dbg_set_spin_limit.argtypes = [C.c_int32]
     L.ll_dbg_graph_stats.restype = C.c_int
     L.ll_dbg_graph_stats.argtypes = [C.POINTER(C.c_int64)]
     L.ll_dbg_get_hidden.restype = C.c_int
@@ -349,6 +351,9 @@ class Session:
         ms = C.c_float(0)
         _check(self.lib.ll_batch_dbg_time_steps(k, C.byref(ms)))
         return float(ms.value)
+
+    def ll_dbg_set_spin_limit(self, polls):
+        return bool(_check(self.lib.ll_dbg_set_spin_limit(polls)))
 
     def ll_dbg_graph_stats(self):
         out = (C.c_int64 * 4)()

@@ -21,6 +21,7 @@
 #include "prefill_skinny.h"
 #include "prefill_gemm.h"
 #include "prefill_tile.h"
+#include "decode_small.h"
 #include "batch_kernels.h"
 
 // Scratch of ll_prefill_static(): the buffers a short prefill needs besides its inputs and outputs
@@ -329,6 +330,8 @@ struct Layout {
   size_t kv, rope, x, x_keep, q, o, m, attn_part, attn_cnt, logits, amax_val, amax_idx, state, tokens;
   size_t pf_x, pf_xn, pf_part, pf_q, pf_o, pf_h, pf_ss;
   size_t mk_layers, mk_bar, mk_amax_val, mk_amax_idx, mk_trace, zeros, sample_cfg, ao_sync;
+  size_t sm_xch, sm_epoch;  // hand-off buffers of the small-model step kernel (two sets), and its step count
+  int sm_grid, sm_splits;   // its workgroups (0: the model is not one of its kind), attention splits per head at most
   size_t wf;                // fragment-major copy of the projection weights for the short-prompt kernels (0 bytes without it)
   size_t wf_qkv, wf_o, wf_gu, wf_down, wf_layer, wf_lm;   // offsets inside a layer's part, bytes per layer, offset of the LM head's copy
   size_t total;
@@ -348,6 +351,12 @@ int gemv_grid(int pairs, int wg_threads = LL_WG) {
   for (int g = want; g >= want - want / 4; --g)
     if (pairs % (g * wpw) == 0) return g;
   return want;
+}
+
+// Workgroups of the small-model step kernel, 0 where the step is the multi-kernel chain
+int small_grid(const ll_config& c) {
+  if (c.flags & ~LL_FLAG_LEAN_WORKSPACE) return 0;          // every other flag asks for one of the other decode modes
+  return sm_grid(c.d_model, c.ffn_hidden, num_cus());
 }
 
 Layout make_layout(const ll_config& c) {
@@ -408,6 +417,12 @@ Layout make_layout(const ll_config& c) {
   L.mk_amax_val = take(1024 * 4);   // one candidate per workgroup of the persistent kernel
   L.mk_amax_idx = take(1024 * 4);
   L.mk_trace = take((size_t)(5 * c.n_layers + 2) * 8 * 8);
+  L.sm_grid = small_grid(c);
+  if (L.sm_grid > 0) {
+    L.sm_splits = sm_max_splits(L.sm_grid, c.n_heads);
+    L.sm_xch = take(2 * sm_set_floats(sm_layout(c.d_model, c.n_heads, c.head_dim, c.ffn_hidden, L.sm_splits), c.n_layers) * 4);
+    L.sm_epoch = take(4);
+  }
   // Second copy of the weights in the short-prompt kernels' operand order (see sk_shuffle_kernel):
   // [layer][q,k,v | o | gate,up | down] then the LM head, 1 KB per 16-row block and 32-wide K step.
   if (has_copy(c)) {
@@ -522,6 +537,10 @@ struct Instance {
   std::vector<hipEvent_t>* prof_events = nullptr;
   std::vector<int>* prof_class = nullptr;
   bool use_mega = false;         // decode step = one persistent kernel
+  bool small = false;            // decode steps run in the small-model kernel
+  bool sampled = false;          // ll_set_sampling: the selection kernel draws
+  int fed = 0;                   // token the next step feeds
+  int small_spin_limit = 1 << 20;   // polls of one hand-off: some two seconds, then the step is redone by the kernel chain
   bool fused_attn = false;       // attention and O projection of a layer in one launch
   int mega_grid = 0;
   size_t mega_lds = 0;
@@ -588,6 +607,16 @@ void launch_gemv(const GemvArgs& a, int pairs, int grid_override, hipStream_t s)
                      gemv_lds_bytes(a.K, MODE == GM_QKV || MODE == GM_GATEUP || MODE == GM_LMHEAD), s, a);
 }
 
+// token selection + state advance + the next step's input row
+void enqueue_select(Instance* I, hipStream_t s, const float* amax_val, const int* amax_idx, int nparts, const float* logits,
+                    int prefill) {
+  const ll_config& c = I->cfg;
+  hipLaunchKernelGGL(sample_kernel, dim3(1), dim3(SMP_THREADS), SMP_Z_WORDS * 4, s, amax_val, amax_idx, nparts, logits,
+                     c.vocab, I->at<SampleCfg>(I->L.sample_cfg), I->state(), I->dev_ring, I->ring_size, prefill,
+                     (const half_t*)I->w.tok_emb, I->use_mega ? nullptr : I->at<float>(I->L.x),
+                     I->at<float>(I->L.x_keep), c.d_model);
+}
+
 // final RMSNorm + LM head + argmax + state advance, shared by decode and prefill
 void enqueue_head(Instance* I, hipStream_t s, const PfBuffers& B, const float* xin, int from_prompt_row, int prefill) {
   const ll_config& c = I->cfg;
@@ -609,11 +638,7 @@ void enqueue_head(Instance* I, hipStream_t s, const PfBuffers& B, const float* x
   }
   if (I->runs(LL_KC_SAMPLE)) {
     ProfScope ps(I, s, LL_KC_SAMPLE);
-    hipLaunchKernelGGL(sample_kernel, dim3(1), dim3(SMP_THREADS), SMP_Z_WORDS * 4, s, B.amax_val,
-                       B.amax_idx, I->L.lm_wgs, B.logits, c.vocab,
-                       I->at<SampleCfg>(I->L.sample_cfg), I->state(), I->dev_ring, I->ring_size, prefill,
-                       (const half_t*)I->w.tok_emb, I->use_mega ? nullptr : I->at<float>(I->L.x),
-                       I->at<float>(I->L.x_keep), c.d_model);
+    enqueue_select(I, s, B.amax_val, B.amax_idx, I->L.lm_wgs, B.logits, prefill);
   }
 }
 
@@ -772,7 +797,42 @@ void enqueue_decode_mega(Instance* I, hipStream_t s, bool trace = false) {
   hipLaunchKernelGGL(decode_mega_kernel, dim3(I->mega_grid), dim3(MK_THREADS), I->mega_lds, s, a);
 }
 
+template <int HD>
+void launch_small(const SmArgs& a, int grid, hipStream_t s) {
+  if (a.F <= 1024 && a.d <= 256) hipLaunchKernelGGL((decode_small_kernel<HD, 2, true>), dim3(grid), dim3(SM_THREADS), 0, s, a);
+  else hipLaunchKernelGGL((decode_small_kernel<HD, (SM_MAX_F + 511) / 512, false>), dim3(grid), dim3(SM_THREADS), 0, s, a);
+}
+// `steps` greedy steps in one launch; 0: one step whose token the selection kernel behind it chooses
+void enqueue_decode_small(Instance* I, hipStream_t s, int steps) {
+  const ll_config& c = I->cfg;
+  SmArgs a{};
+  a.layers = I->at<MkLayer>(I->L.mk_layers);
+  a.final_norm = (const half_t*)I->w.final_norm;
+  a.lm_head = (const half_t*)I->w.lm_head;
+  a.emb = (const half_t*)I->w.tok_emb;
+  a.x = I->at<float>(I->L.x);
+  a.x_keep = I->at<float>(I->L.x_keep);
+  a.logits = I->pf.logits;
+  a.amax_val = I->at<float>(I->L.mk_amax_val);
+  a.amax_idx = I->at<int>(I->L.mk_amax_idx);
+  a.host_ring = I->dev_ring;
+  a.ring_size = I->ring_size;
+  a.rope = I->at<float2>(I->L.rope);
+  a.st = I->state();
+  a.xch = I->at<float>(I->L.sm_xch);
+  a.epoch = I->at<int>(I->L.sm_epoch);
+  a.steps = steps;
+  a.n_layers = c.n_layers; a.d = c.d_model; a.n_heads = c.n_heads; a.F = c.ffn_hidden; a.vocab = c.vocab;
+  a.max_seq = c.max_seq; a.max_splits = I->L.sm_splits; a.eps = c.rms_eps;
+  a.spin_limit = I->small_spin_limit;
+  const int grid = I->L.sm_grid * SM_XCDS;
+  if (c.head_dim == 64) launch_small<64>(a, grid, s);
+  else launch_small<128>(a, grid, s);
+  if (steps == 0) enqueue_select(I, s, a.amax_val, a.amax_idx, I->L.sm_grid, a.logits, 0);
+}
+
 void enqueue_decode(Instance* I, hipStream_t s) {
+  if (I->small && I->only_class < 0 && !I->prof_events) return enqueue_decode_small(I, s, 0);
   if (I->use_mega && I->only_class < 0 && !I->prof_events) enqueue_decode_mega(I, s);
   else enqueue_decode_multi(I, s);
 }
@@ -1111,8 +1171,51 @@ int run_decode_steps_per_length(Instance* I, int k) {
   return LL_OK;
 }
 
+// host mirror of the device state after k finished steps
+void advance(Instance* I, int k) {
+  I->pos += k;
+  I->steps += k;
+  I->fed = I->host_ring[I->steps - 1];
+  I->last_was_prefill = false;
+  I->last_logits = I->pf.logits;
+}
+
+int recapture_decode(Instance* I) {
+  if (I->dec_exec) (void)hipGraphExecDestroy(I->dec_exec);
+  if (I->dec_graph) (void)hipGraphDestroy(I->dec_graph);
+  I->dec_exec = nullptr;
+  I->dec_graph = nullptr;
+  return capture(I, &I->dec_graph, &I->dec_exec, 0);
+}
+
+// A wait between the small-model kernel's workgroups ran out (they were not resident together): the step that has no
+// token yet and all that follow are run again by the multi-kernel chain, which waits for nobody, and so is every later step.
+int run_decode_steps(Instance* I, int k);
+int small_retry(Instance* I, int k) {
+  int done = 0;
+  while (done < k && I->host_ring[I->steps + done] >= 0) ++done;
+  if (done == k) return LL_OK;
+  I->small = false;
+  int rc = recapture_decode(I);
+  if (rc != LL_OK) return rc;
+  const int fed = done ? I->host_ring[I->steps + done - 1] : I->fed;
+  if ((rc = write_state(I, I->pos + done, fed, 0, I->steps + done)) != LL_OK) return rc;
+  const int d = I->cfg.d_model;
+  hipLaunchKernelGGL(embed_kernel, dim3((d + LL_WG * 8 - 1) / (LL_WG * 8)), dim3(LL_WG), 0, I->stream,
+                     (const half_t*)I->w.tok_emb, I->state(), I->at<float>(I->L.x), d);
+  HIPCHK(hipGetLastError());
+  if ((rc = run_decode_steps(I, k - done)) != LL_OK) return rc;
+  HIPCHK(hipStreamSynchronize(I->stream));
+  return LL_OK;
+}
+
 int run_decode_steps(Instance* I, int k) {
   if (I->per_length) return run_decode_steps_per_length(I, k);
+  if (I->small && !I->sampled) {
+    enqueue_decode_small(I, I->stream, k);
+    HIPCHK(hipGetLastError());
+    return LL_OK;
+  }
   for (int i = 0; i < k; ++i) {
     if (eager(I)) enqueue_decode(I, I->stream);
     else HIPCHK(hipGraphLaunch(I->dec_exec, I->stream));
@@ -1428,6 +1531,11 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   }
   if (!hip_or_bail(hipDeviceSynchronize(), "hipDeviceSynchronize")) return bail(rc);
 
+  if (L.sm_grid > 0) {
+    if (!hip_or_bail(hipMemset(I->at<char>(L.sm_xch), 0xFF, L.sm_epoch - L.sm_xch), "hipMemset(hand-offs)") ||
+        !hip_or_bail(hipMemset(I->at<char>(L.sm_epoch), 0, 4), "hipMemset(epoch)")) return bail(rc);
+    I->small = true;
+  }
   I->skinny = skinny_ok(*cfg);
   (void)num_cus();
   for (int b : {16, 32, 64, 128, 192, 256, 384, 512, 1024})
@@ -1517,6 +1625,7 @@ int ll_set_sampling(float temperature, int32_t top_k, float top_p, uint64_t seed
   h->seed_hi = (uint32_t)(seed >> 32);
   HIPCHK(hipMemcpyAsync(I->at<SampleCfg>(I->L.sample_cfg), h, sizeof(SampleCfg), hipMemcpyHostToDevice, I->stream));
   HIPCHK(hipStreamSynchronize(I->stream));
+  I->sampled = temperature > 0.f;
   return LL_OK;
 }
 
@@ -1590,7 +1699,7 @@ int32_t ll_prefill(const int32_t* tokens, int32_t n) {
   I->last_was_prefill = true;
   I->last_logits = I->pf.logits;
   I->last_rows = I->pf.X;
-  return I->host_ring[0];
+  return I->fed = I->host_ring[0];
 }
 
 int32_t ll_prefill_static(const int32_t* tokens, int32_t n) {
@@ -1625,7 +1734,7 @@ int32_t ll_prefill_static(const int32_t* tokens, int32_t n) {
   I->last_was_prefill = true;
   I->last_logits = B.logits;
   I->last_rows = B.X;
-  return I->host_ring[0];
+  return I->fed = I->host_ring[0];
 }
 
 int32_t ll_decode_n(int32_t k, int32_t* out_tokens) {
@@ -1640,15 +1749,13 @@ int32_t ll_decode_n(int32_t k, int32_t* out_tokens) {
   int rc = run_decode_steps(I, k);
   if (rc != LL_OK) return rc;
   HIPCHK(hipStreamSynchronize(I->stream));
+  if (I->small && (rc = small_retry(I, k)) != LL_OK) return rc;
   for (int i = 0; i < k; ++i)
     if (I->host_ring[I->steps + i] < 0)
       return fail(LL_E_HIP, "ll_decode: a bounded wait between workgroups of one launch ran out (are other "
                             "kernels occupying the GPU?); call ll_reset");
   if (out_tokens) memcpy(out_tokens, I->host_ring + I->steps, (size_t)k * 4);
-  I->pos += k;
-  I->steps += k;
-  I->last_was_prefill = false;
-  I->last_logits = I->pf.logits;
+  advance(I, k);
   return I->host_ring[I->steps - 1];
 }
 
@@ -1983,6 +2090,16 @@ int ll_dbg_tile_plan(int32_t kind, int32_t N, int32_t K, int32_t rows, int32_t* 
   return LL_OK;
 }
 
+int ll_dbg_set_spin_limit(int32_t polls) {
+  if (!g) return fail(LL_E_NOT_INIT, "ll_dbg_set_spin_limit: not initialised");
+  if (polls < 0) return fail(LL_E_BAD_ARG, "ll_dbg_set_spin_limit: polls = %d < 0", polls);
+  if (!g->small) return 0;
+  HIPCHK(hipStreamSynchronize(g->stream));
+  g->small_spin_limit = polls;
+  const int rc = recapture_decode(g);          // (the sampled step's graph holds the kernel's arguments)
+  return rc == LL_OK ? 1 : rc;
+}
+
 int ll_dbg_graph_stats(int64_t* out4) {
   if (!g) return fail(LL_E_NOT_INIT, "ll_dbg_graph_stats: not initialised");
   if (!out4) return fail(LL_E_BAD_ARG, "ll_dbg_graph_stats: null output");
@@ -2016,6 +2133,7 @@ int ll_dbg_force_next_token(int32_t tok) {
   if (g->pos == 0) return fail(LL_E_STATE, "ll_dbg_force_next_token: empty context");
   int* h = g->host_stage;
   *h = tok;
+  g->fed = tok;
   HIPCHK(hipMemcpyAsync(&g->state()->next_token, h, 4, hipMemcpyHostToDevice, g->stream));
   if (!g->use_mega) {            // the step reads the token's embedding row from x, not the id
     const int d = g->cfg.d_model;
@@ -2076,10 +2194,7 @@ int ll_dbg_profile_decode(int32_t steps, float* us_out, int32_t* launches_out) {
     for (auto x : ev) (void)hipEventDestroy(x);
     if (e != hipSuccess) return fail(LL_E_HIP, "profile: %s", hipGetErrorString(e));
   }
-  I->pos += steps;
-  I->steps += steps;
-  I->last_was_prefill = false;
-  I->last_logits = I->pf.logits;
+  advance(I, steps);
   for (int i = 0; i < LL_KC_COUNT; ++i) {
     us_out[i] = cnt[i] ? (float)(sum[i] / cnt[i]) : 0.f;
     if (launches_out) launches_out[i] = (int32_t)(cnt[i] / steps);
@@ -2101,10 +2216,7 @@ int ll_dbg_trace_decode(uint64_t* ticks_out, int32_t max_phases) {
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(I->stream));
   HIPCHK(hipMemcpy(ticks_out, I->at<char>(I->L.mk_trace), (size_t)phases * 8 * 8, hipMemcpyDeviceToHost));
-  I->pos += 1;
-  I->steps += 1;
-  I->last_was_prefill = false;
-  I->last_logits = I->pf.logits;
+  advance(I, 1);
   return phases;
 }
 
@@ -2213,10 +2325,7 @@ int ll_dbg_time_decode(int32_t k, float* ms_out) {
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc != LL_OK) return rc;
-  I->pos += k;
-  I->steps += k;
-  I->last_was_prefill = false;
-  I->last_logits = I->pf.logits;
+  advance(I, k);
   return LL_OK;
 }
 
