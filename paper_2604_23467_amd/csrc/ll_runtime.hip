@@ -864,35 +864,32 @@ SliceMap launch_gemm(Instance* I, hipStream_t s, const PfBuffers& B, const half_
 }
 
 
+template <int MODE, int TB, bool FRAG>
+void launch_skinny_as(hipStream_t s, const SkinnyArgs& a) {
+  const int per_wave = (((a.K + 31) >> 5) + SK_WAVES - 1) / SK_WAVES, units = skinny_units(MODE, a.N);
+  if constexpr (MODE != SK_RES) {
+    if (per_wave <= SKP_KSTEPS) {
+      hipLaunchKernelGGL((pf_skinny_persist_kernel<MODE, TB, FRAG>), dim3(units < g_num_cus ? units : g_num_cus), dim3(SK_THREADS), 0, s, a);
+      return;
+    }
+  }
+  if constexpr (MODE != SK_LOGITS) {
+    const int nb = (per_wave + 7) / 8;
+    if constexpr (MODE == SK_RES) {       // the 7B shapes get the unrolled pipelines: K = 4096 and K = 11008
+      if (nb == 2 || nb == 6) {
+        if (nb == 2) hipLaunchKernelGGL((pf_skinny_kernel<MODE, TB, 2, FRAG>), dim3(units), dim3(SK_THREADS), 0, s, a);
+        else hipLaunchKernelGGL((pf_skinny_kernel<MODE, TB, 6, FRAG>), dim3(units), dim3(SK_THREADS), 0, s, a);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((pf_skinny_kernel<MODE, TB, 0, FRAG>), dim3(units), dim3(SK_THREADS), 0, s, a);
+  }
+}
 template <int MODE>
 void launch_skinny(hipStream_t s, const PfBuffers& B, SkinnyArgs a, int Mb) {
   a.zeros_off = B.zeros - a.X;
-  if constexpr (MODE != SK_RES) {
-    const int per_wave = (((a.K + 31) >> 5) + SK_WAVES - 1) / SK_WAVES;
-    if (per_wave <= SKP_KSTEPS) {
-      const int units = skinny_units(MODE, a.N);
-      dim3 grid(units < g_num_cus ? units : g_num_cus), block(SK_THREADS);
-      if (Mb == 16) hipLaunchKernelGGL((pf_skinny_persist_kernel<MODE, 1>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((pf_skinny_persist_kernel<MODE, 2>), grid, block, 0, s, a);
-      return;
-    }
-  }
-  dim3 grid(skinny_units(MODE, a.N)), block(SK_THREADS);
-  const int per_wave = (((a.K + 31) >> 5) + SK_WAVES - 1) / SK_WAVES, nb = (per_wave + 7) / 8;
-  if constexpr (MODE == SK_RES) {       // the 7B shapes get the unrolled pipelines: K = 4096 and K = 11008
-    if (nb == 2) {
-      if (Mb == 16) hipLaunchKernelGGL((pf_skinny_kernel<MODE, 1, 2>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((pf_skinny_kernel<MODE, 2, 2>), grid, block, 0, s, a);
-      return;
-    }
-    if (nb == 6) {
-      if (Mb == 16) hipLaunchKernelGGL((pf_skinny_kernel<MODE, 1, 6>), grid, block, 0, s, a);
-      else hipLaunchKernelGGL((pf_skinny_kernel<MODE, 2, 6>), grid, block, 0, s, a);
-      return;
-    }
-  }
-  if (Mb == 16) hipLaunchKernelGGL((pf_skinny_kernel<MODE, 1, 0>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((pf_skinny_kernel<MODE, 2, 0>), grid, block, 0, s, a);
+  if (a.Wf) Mb == 16 ? launch_skinny_as<MODE, 1, true>(s, a) : launch_skinny_as<MODE, 2, true>(s, a);
+  else Mb == 16 ? launch_skinny_as<MODE, 1, false>(s, a) : launch_skinny_as<MODE, 2, false>(s, a);
 }
 
 // First kernel of a prefill: the state block and the ids of up to Mb rows from the staging buffer
@@ -1334,11 +1331,7 @@ void enqueue_batch_step(Instance* I, hipStream_t s) {
     a.X = Xn; a.W[0] = (const half_t*)I->w.lm_head; a.N = c.vocab; a.K = d;
     a.ss_in = ss_attn; a.ss_stride = sst; a.ss_parts = parts; a.logits = B->at<float>(B->L.logits);
     a.Wf = I->wfrag_lm();
-    a.zeros_off = P.zeros - a.X;
-    const int units = skinny_units(SK_LOGITS, c.vocab);
-    dim3 grid(units < g_num_cus ? units : g_num_cus);
-    if (tb == 1) hipLaunchKernelGGL((pf_skinny_persist_kernel<SK_LOGITS, 1>), grid, dim3(SK_THREADS), 0, s, a);
-    else hipLaunchKernelGGL((pf_skinny_persist_kernel<SK_LOGITS, 2>), grid, dim3(SK_THREADS), 0, s, a);
+    launch_skinny<SK_LOGITS>(s, P, a, Mb);
   }
   hipLaunchKernelGGL(bt_select_kernel, dim3(Mb), dim3(SMP_THREADS), SMP_Z_WORDS * 4, s, B->at<float>(B->L.logits),
                      c.vocab, I->at<SampleCfg>(I->L.sample_cfg), bs, B->d_out);

@@ -129,9 +129,38 @@ __host__ __device__ inline int skinny_units(int mode, int N) {
   return mode == SK_QKV ? 3 * (N / 16) : mode == SK_GATEUP ? N / 8 : N / 16;
 }
 
+// Operands of a K step where the weights are the fragment-major copy: a wave's load is 1 KB of consecutive bytes of
+// either, so its address is a descriptor, a lane offset that never changes and a scalar.  (With 64-bit lane
+// addresses some 250 instructions stood in front of a kernel's first loads.)  A K step past the wave's range, and the
+// activations past K in the last step, lie outside the descriptors: they read as zero, without traffic.
+template <int TB>
+struct SkFrag {
+  __amdgpu_buffer_rsrc_t x;
+  int ksteps, s_end, full, tail, last;   // lane offsets: of a whole step, of the last step; index of a last step that K does not fill
+  __device__ __forceinline__ SkFrag(const SkinnyArgs& a, int lane, int send) {
+    ksteps = (a.K + 31) >> 5;
+    s_end = send;
+    x = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(a.X), 0, ksteps * TB * 1024, 0x00027000);
+    full = lane * 16;
+    last = a.K & 31 ? ksteps - 1 : -1;
+    tail = (lane >> 4) * 8 < (a.K & 31) ? full : 0x40000000;
+  }
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t block(const half_t* Wf, int u) const {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(Wf + (size_t)u * ksteps * 512), 0, ksteps * 1024, 0x00027000);
+  }
+  __device__ __forceinline__ h8 weights(__amdgpu_buffer_rsrc_t w, int step) const {
+    return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(w, step >= s_end ? 0x40000000 : full, min(step, ksteps - 1) * 1024, 2));
+  }
+  __device__ __forceinline__ h8 acts(int step, int t) const {
+    return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(
+                                      x, step >= s_end ? 0x40000000 : step == last ? tail : full,
+                                      (min(step, ksteps - 1) * TB + t) * 1024, 0));
+  }
+};
+
 // NB > 0: the host promises ceil(K steps per wave / 8) == NB and the batch pipeline is unrolled
 // with exact wait counts; NB = 0 walks any K with a loop that over-fetches one batch.
-template <int MODE, int TB, int NB>
+template <int MODE, int TB, int NB, bool FRAG>
 __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) {
   constexpr int RB = 1;
   __shared__ __attribute__((aligned(16))) float part[SK_WAVES * TB * 16 * SK_PSTRIDE];
@@ -144,9 +173,9 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
   const int units = skinny_units(MODE, N);
   const int hh = a.head_dim >> 1;
 
-  // weight row this lane streams
-  const half_t* wrow;
-  {
+  // weight row this lane streams (row-major weights)
+  const half_t* wrow = nullptr;
+  if constexpr (!FRAG) {
     const int u = blockIdx.x;
     if (MODE == SK_RES) {
       wrow = a.W[0] + (size_t)(u * 16 + r) * K;
@@ -164,10 +193,6 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
       wrow = a.W[z] + (size_t)row * K;
     }
   }
-
-  // with a fragment-major copy a wave's load is 1 KB of consecutive bytes instead of 16 rows x 64 bytes
-  const bool frag = a.Wf != nullptr;
-  const half_t* wfrag = frag ? a.Wf + ((size_t)blockIdx.x * ((K + 31) >> 5) * 64 + lane) * 8 : nullptr;
 
   f4 acc[TB];
 #pragma unroll
@@ -202,12 +227,20 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
   const int s_begin = wave * per_wave, s_end = min(s_begin + per_wave, ksteps);
   constexpr int U = 8;
   h8 fa[2][U], fb[2][U][TB];
+  const SkFrag<TB> frag(a, lane, s_end);
+  const __amdgpu_buffer_rsrc_t wr = frag.block(a.Wf, blockIdx.x);
   auto issue = [&](int s0, h8 (&A)[U], h8 (&B)[U][TB]) {
 #pragma unroll
     for (int i = 0; i < U; ++i) {
       const int st = s0 + i, k = st * 32 + g * 8;
+      if constexpr (FRAG) {
+        A[i] = frag.weights(wr, st);
+#pragma unroll
+        for (int t = 0; t < TB; ++t) B[i][t] = frag.acts(st, t);
+        continue;
+      }
       const bool in = st < s_end && k < K;           // K % 8 == 0: 8 halves are all in or all out
-      A[i] = load_stream(frag ? wfrag + (in ? (long)st * 512 : 0) : wrow + (in ? k : 0));
+      A[i] = load_stream(wrow + (in ? k : 0));
 #pragma unroll
       for (int t = 0; t < TB; ++t)
         B[i][t] = load_h8(a.X + (in ? (long)(st * TB + t) * 512 + lane * 8 : a.zeros_off));
@@ -341,24 +374,27 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
   }
 }
 
-// Persistent form of the two wide projections (SK_QKV, SK_GATEUP) for K <= 4096 and at most 32
+// Persistent form of the wide projections (SK_QKV, SK_GATEUP, SK_LOGITS) for K <= 4096 and at most 32
 // tokens: one workgroup per CU walks row blocks u = blockIdx.x, + gridDim.x, ...  A wave keeps
 // the same K range for every block, so its B fragments (16 K steps x TB) are loaded ONCE into
 // registers and the activations cause no further traffic; and the first half of the next
 // block's weights is requested before the current block's partials are exchanged, so the
-// weight stream never drains while a block is being finished.  The finishing (8 partials ->
-// epilogue) rotates over the waves, one block each, on all 64 lanes (2 or 4 row pairs of a token per
-// lane); partials are double-buffered in LDS so a single barrier per block orders writers and the
-// finishing wave.  The other waves meet the finishing wave again at the next block's barrier, so what
-// its epilogue costs is on every block's path: spread over 64 lanes instead of one lane per token, and
-// with the RoPE factors fetched when the block starts, Q/K/V went from 20.6 to 19.3 us and gate/up from
-// 32.2 to 31.3 us at 16 rows (without any epilogue: 18.6 / 30.4 us).
+// weight stream never drains while a block is being finished.  Partials are double-buffered in LDS so a single barrier
+// per block orders writers and finishers; all waves finish a block together (8 partials -> epilogue), behind the
+// request for the other half of the next block.
+//
+// Where the time goes (us, Q/K/V and gate/up at 16 rows; timing-only builds): the weights alone 16.6 / 29.0, the
+// tokens' norm factors 0.3 / 0.2, the activations' way into registers 1.1 / 0.9, barriers 0.2 / 0.3, epilogues 1.6 / 1.1
+// when one wave finished a block and the others met it at the next barrier.  Finishing together, descriptors instead of
+// 64-bit lane addresses, factors summed behind the first block's requests without a branch, and no request behind the last
+// block (a wave cannot end before its loads have come): Q/K/V 19.9 -> 18.7 us, gate/up 31.5 -> 30.1 at 16 rows, 22.3 -> 20.9
+// and 32.6 -> 31.8 at 32.
+template <bool V> struct SkMore { static constexpr bool value = V; };
 #define SKP_KSTEPS 16     // K steps per wave held in registers: K <= 8 waves * 16 * 32
-template <int MODE, int TB>
+template <int MODE, int TB, bool FRAG>
 __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(SkinnyArgs a) {
   static_assert(MODE != SK_RES, "wide projections only");
   __shared__ __attribute__((aligned(16))) float part[2][SK_WAVES * TB * 16 * SK_PSTRIDE];
-  __shared__ float s_scale[TB * 16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, g = lane >> 4;
@@ -370,10 +406,6 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
   const int per_wave = (ksteps + SK_WAVES - 1) / SK_WAVES;      // <= SKP_KSTEPS (host checked)
   const int s_begin = wave * per_wave, s_end = min(s_begin + per_wave, ksteps);
   constexpr int HALF = SKP_KSTEPS / 2;
-
-  bool in[SKP_KSTEPS];
-#pragma unroll
-  for (int i = 0; i < SKP_KSTEPS; ++i) in[i] = (s_begin + i < s_end) && ((s_begin + i) * 32 + g * 8 < K);
 
   // weight row of this lane in row block u
   auto row_ptr = [&](int u) -> const half_t* {
@@ -389,69 +421,83 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
     }
     return a.W[z] + (size_t)row * K;
   };
-  // element offset of K step i in a weight row; steps outside the wave's range re-read the row
-  // start instead (always valid memory) and meet a zero B fragment
-  // (with a fragment-major copy: its 1 KB pieces, 512 halves per K step, instead of 16 rows x 64 bytes)
-  const bool frag = a.Wf != nullptr;
-  int koff[SKP_KSTEPS];
+  // Half a row block's weights, K steps h0 .. h0 + HALF - 1 of this wave.  Row-major: steps outside the wave's range
+  // re-read the row start instead (always valid memory) and meet a zero B fragment.
+  const SkFrag<TB> frag(a, lane, s_end);
+  auto load_half = [&](int u, int h0, h8 (&f)[HALF]) {
+    if constexpr (FRAG) {
+      const __amdgpu_buffer_rsrc_t w = frag.block(a.Wf, u);
 #pragma unroll
-  for (int i = 0; i < SKP_KSTEPS; ++i) koff[i] = !in[i] ? 0 : frag ? (s_begin + i) * 512 : (s_begin + i) * 32 + g * 8;
-  auto blk_ptr = [&](int u) -> const half_t* {
-    return frag ? a.Wf + ((size_t)u * ksteps * 64 + lane) * 8 : row_ptr(u);
+      for (int i = 0; i < HALF; ++i) f[i] = frag.weights(w, s_begin + h0 + i);
+    } else {
+      const half_t* wp = row_ptr(u);
+#pragma unroll
+      for (int i = 0; i < HALF; ++i) {
+        const int st = s_begin + h0 + i, k = st * 32 + g * 8;
+        f[i] = load_stream(wp + (st < s_end && k < K ? k : 0));
+      }
+    }
   };
 
-  // a few small loads for the tokens' norm factors, then the weight stream, then the (cached) activations
-  SkSsLoads sl;
-  sk_ss_issue<TB>(a.ss_in, a.ss_stride, a.ss_parts, tid, sl);
+  // First the partial sums of squares of the tokens this wave finishes (2 TB wave, ..): K <= 4096 leaves at most 256
+  // slots of 16 columns, one 16-byte piece per lane, with no branch, so that the wait for them below leaves everything
+  // younger in flight.  Then the weight stream's first row block and the (cached) activations.
+  constexpr int WT = 2 * TB;
+  f4 ssv[WT];
+#pragma unroll
+  for (int t = 0; t < WT; ++t)
+    ssv[t] = *as_global(reinterpret_cast<const f4*>(a.ss_in + (size_t)(wave * WT + t) * a.ss_stride + min(lane * 4, a.ss_stride - 4)));
   __builtin_amdgcn_sched_barrier(0);
   int u = blockIdx.x;
   h8 fa0[HALF], fa1[HALF];
-  {
-    const half_t* wp = blk_ptr(u < units ? u : 0);
-#pragma unroll
-    for (int i = 0; i < HALF; ++i) fa0[i] = load_stream(wp + koff[i]);
-  }
+  load_half(u < units ? u : 0, 0, fa0);
   __builtin_amdgcn_sched_barrier(0);
   h8 fb[SKP_KSTEPS][TB];
 #pragma unroll
   for (int i = 0; i < SKP_KSTEPS; ++i)
 #pragma unroll
-    for (int t = 0; t < TB; ++t)
-      fb[i][t] = load_h8(a.X + (in[i] ? ((long)((s_begin + i) * TB + t) * 64 + lane) * 8 : a.zeros_off));
+    for (int t = 0; t < TB; ++t) {
+      const int st = s_begin + i;
+      if constexpr (FRAG) fb[i][t] = frag.acts(st, t);
+      else fb[i][t] = load_h8(a.X + (st < s_end && st * 32 + g * 8 < K ? ((long)(st * TB + t) * 64 + lane) * 8 : a.zeros_off));
+    }
   __builtin_amdgcn_sched_barrier(0);
-  sk_ss_finish<TB>(sl, K, a.eps, s_scale, tid);   // published by the first block's barrier
+  float ssum[WT];
+#pragma unroll
+  for (int t = 0; t < WT; ++t) {
+    ssum[t] = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ssum[t] += lane * 4 + e < a.ss_parts ? ssv[t][e] : 0.f;      // (slots past the last hold anything)
+  }
   __builtin_amdgcn_sched_barrier(0);
-  // The epilogue of a block runs on all 64 lanes of the wave whose turn it is: lane = (eq, etok) finishes NP
-  // of the 8 (lo, hi) row pairs of token etok.  What it needs from memory besides the sums (the token's
-  // position and cache row, its RoPE factors) is fetched when the block starts, so that the block ends
-  // without a memory round trip.
-  constexpr int ET = TB * 16, NP = 8 * ET / 64;              // tokens; pairs per lane (2 or 4)
-  typedef float EV __attribute__((ext_vector_type(NP)));
-  typedef half_t EH __attribute__((ext_vector_type(NP)));
-  const int etok = lane % ET, eq = lane / ET;
+  // The epilogue of a block is shared by all waves: lane < 16 TB of wave w finishes (lo, hi) row pair lane % 8 of token
+  // 2 TB w + lane / 8, so what is stored next to each other comes from neighbouring lanes.  What it needs from memory
+  // besides the sums (the token's position and cache row, its RoPE factor) is fetched when the block starts.
+  const bool elane = lane < 16 * TB;
+  const int etok = wave * WT + ((lane >> 3) & (WT - 1)), ej = lane & 7;
+  const bool efin = elane && etok < n;
   int epos = 0, ecrow = 0;
-  if (MODE == SK_QKV && etok < n) {
+  if (MODE == SK_QKV && efin) {
     epos = sk_row_pos(a, p0, etok);
     ecrow = sk_cache_row(a, etok, epos);
   }
-  constexpr bool EPRE = TB == 1;      // 32 token rows leave no registers for the early RoPE factors
-  float2 ecs[NP];
+  load_half(u < units ? u : 0, HALF, fa1);
+  __builtin_amdgcn_sched_barrier(0);
+  float ss_tok = 0.f;
+#pragma unroll
+  for (int t = 0; t < WT; ++t) {
+    const float v = wave_sum(ssum[t]);
+    if (((lane >> 3) & (WT - 1)) == t) ss_tok = v;
+  }
+  const float scale = 1.0f / sqrtf(ss_tok / (float)K + a.eps);
+  // One row block; the last one of a workgroup requests nothing any more (a wave cannot end before its loads have come)
   int round = 0;
-  for (; u < units; u += gridDim.x, ++round) {
-    {
-      const half_t* wp = blk_ptr(u);
-#pragma unroll
-      for (int i = 0; i < HALF; ++i) fa1[i] = load_stream(wp + koff[HALF + i]);
-    }
-    if (MODE == SK_QKV && EPRE && wave == (round & (SK_WAVES - 1)) && etok < n) {
-      const int per = N / 16, z = u / per, v = u - z * per;
-      if (z < 2) {
-        const int bph = hh / 8, head = v / bph, j0 = (v - head * bph) * 8 + eq * NP;
-        const float2* cs = a.rope + (size_t)epos * hh + j0;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) ecs[j] = cs[j];
-      }
-    }
+  auto row_block = [&](auto more) {
+    const int un = u + gridDim.x;
+    float2 ecs = make_float2(1.f, 0.f);
+    const int per = N / 16, z = MODE == SK_QKV ? u / per : 0, v = u - z * per;
+    const int bph = hh / 8, head = v / max(bph, 1), j0 = (v - head * bph) * 8;       // z < 2: RoPE pairs j0 .. + 7 of a head
+    if (MODE == SK_QKV && z < 2 && efin) ecs = a.rope[(size_t)epos * hh + j0 + ej];
     f4 acc[TB];
 #pragma unroll
     for (int t = 0; t < TB; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
@@ -460,14 +506,7 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
 #pragma unroll
       for (int t = 0; t < TB; ++t)
         acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa0[i], fb[i][t], acc[t], 0, 0, 0);
-    // always issued, so that the waits below are exact: after the last block the target is
-    // row block 0, which every workgroup re-reads from cache
-    {
-      const int un = u + gridDim.x;
-      const half_t* wp = blk_ptr(un < units ? un : 0);
-#pragma unroll
-      for (int i = 0; i < HALF; ++i) fa0[i] = load_stream(wp + koff[i]);
-    }
+    if constexpr (more.value) load_half(un, 0, fa0);
 #pragma unroll
     for (int i = 0; i < HALF; ++i)
 #pragma unroll
@@ -482,64 +521,41 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
+    if constexpr (more.value) load_half(un, HALF, fa1);
+    __builtin_amdgcn_sched_barrier(0);
 
-    if (wave == (round & (SK_WAVES - 1)) && etok < n) {
-      // lane (eq, etok): pairs eq * NP .. + NP - 1 of token etok, i.e. rows eq * NP .. (lo) and 8 + eq * NP .. (hi)
-      const float scale = s_scale[etok];
-      float lo[NP], hi[NP];
-#pragma unroll
-      for (int j = 0; j < NP; ++j) lo[j] = hi[j] = 0.f;
+    if (efin) {
+      float lo = 0.f, hi = 0.f;
 #pragma unroll
       for (int w = 0; w < SK_WAVES; ++w) {
-        const float* pp = pb + ((w * TB) * 16 + etok) * SK_PSTRIDE + eq * NP;
-        const EV a0 = *reinterpret_cast<const EV*>(pp), a1 = *reinterpret_cast<const EV*>(pp + 8);
-#pragma unroll
-        for (int j = 0; j < NP; ++j) { lo[j] += a0[j]; hi[j] += a1[j]; }
+        const float* pp = pb + (w * TB * 16 + etok) * SK_PSTRIDE + ej;
+        lo += pp[0];
+        hi += pp[8];
       }
-#pragma unroll
-      for (int j = 0; j < NP; ++j) { lo[j] *= scale; hi[j] *= scale; }
-      EH o0, o1;
+      lo *= scale;
+      hi *= scale;
       if (MODE == SK_GATEUP) {
-#pragma unroll
-        for (int j = 0; j < NP; ++j) o0[j] = (half_t)(lo[j] / (1.0f + expf(-lo[j])) * hi[j]);
-        *reinterpret_cast<EH*>(a.Hout + act_offset(etok, u * 8 + eq * NP, N, TB)) = o0;
+        a.Hout[act_offset(etok, u * 8 + ej, N, TB)] = (half_t)(lo / (1.0f + expf(-lo)) * hi);
       } else if (MODE == SK_LOGITS) {
-        float* lp = a.logits + (size_t)etok * N + u * 16 + eq * NP;
-        EV v0, v1;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) { v0[j] = lo[j]; v1[j] = hi[j]; }
-        *reinterpret_cast<EV*>(lp) = v0;
-        *reinterpret_cast<EV*>(lp + 8) = v1;
+        float* lp = a.logits + (size_t)etok * N + u * 16 + ej;
+        lp[0] = lo;
+        lp[8] = hi;
+      } else if (z == 2) {
+        const int c0 = v * 16, vhead = c0 / a.head_dim, e = c0 - vhead * a.head_dim;
+        half_t* vr = a.vc + ((size_t)vhead * a.max_seq + ecrow) * a.head_dim + e + ej;
+        vr[0] = (half_t)lo;
+        vr[8] = (half_t)hi;
       } else {
-        const int per = N / 16, z = u / per, v = u - z * per;
-        if (z == 2) {
-          const int c0 = v * 16, head = c0 / a.head_dim, e = c0 - head * a.head_dim;
-#pragma unroll
-          for (int j = 0; j < NP; ++j) { o0[j] = (half_t)lo[j]; o1[j] = (half_t)hi[j]; }
-          half_t* vr = a.vc + ((size_t)head * a.max_seq + ecrow) * a.head_dim + e + eq * NP;
-          *reinterpret_cast<EH*>(vr) = o0;
-          *reinterpret_cast<EH*>(vr + 8) = o1;
-        } else {
-          const int bph = hh / 8, head = v / bph, j0 = (v - head * bph) * 8 + eq * NP;
-          if (!EPRE) {
-            const float2* cs = a.rope + (size_t)epos * hh + j0;
-#pragma unroll
-            for (int j = 0; j < NP; ++j) ecs[j] = cs[j];
-          }
-#pragma unroll
-          for (int j = 0; j < NP; ++j) {
-            const float2 t2 = ecs[j];
-            o0[j] = (half_t)(lo[j] * t2.x - hi[j] * t2.y);
-            o1[j] = (half_t)(hi[j] * t2.x + lo[j] * t2.y);
-          }
-          half_t* dst = z == 0 ? a.Q + (size_t)etok * N + head * a.head_dim
-                               : a.kc + ((size_t)head * a.max_seq + ecrow) * a.head_dim;
-          *reinterpret_cast<EH*>(dst + j0) = o0;
-          *reinterpret_cast<EH*>(dst + j0 + hh) = o1;
-        }
+        half_t* dst = z == 0 ? a.Q + (size_t)etok * N + head * a.head_dim
+                             : a.kc + ((size_t)head * a.max_seq + ecrow) * a.head_dim;
+        dst[j0 + ej] = (half_t)(lo * ecs.x - hi * ecs.y);
+        dst[j0 + ej + hh] = (half_t)(hi * ecs.x + lo * ecs.y);
       }
     }
-  }
+  };
+  if (u >= units) return;
+  for (; u + (int)gridDim.x < units; u += gridDim.x, ++round) row_block(SkMore<true>());
+  row_block(SkMore<false>());
 }
 
 // One-off re-layout of a projection's weights into the short-prompt kernels' operand order (run once
