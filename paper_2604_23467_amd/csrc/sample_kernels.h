@@ -272,104 +272,104 @@ __device__ __forceinline__ int smp_nucleus_and_draw(uint32_t (&key)[PER], float 
   return *found < 0 ? 0 : *found;
 }
 
-// Top-k cut, nucleus cut and draw by ONE wave over at most 64 PER candidates (lane order = index order, key 0 = no
-// candidate): the same steps as smp_apply_topk and smp_nucleus_and_draw, but every count is a handful of ballots
-// and every sum stays inside the wave, so none of its ~70 passes costs a workgroup barrier (a step that
-// draws with top-k 50 and top-p 0.95 takes 23 us longer than a greedy one over 32000 tokens, 43 us with one
-// barrier per pass, and 14 against 107 us over 1024).  Returns the token, the same in every lane.
-template <int PER>
-__device__ __forceinline__ int smp_wave_pick(uint32_t (&key)[PER], const int (&id)[PER], int top_k, float zmax,
-                                             float top_p, float u) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t below = ((uint64_t)1 << lane) - 1;
-  auto count = [&](uint32_t at) {                // candidates with key >= at
-    int c = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) c += __builtin_popcountll(__ballot(key[j] >= at));
-    return c;
-  };
-  auto ties_before = [&](uint32_t at) {          // candidates equal to `at` in the lanes below
-    int c = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) c += __builtin_popcountll(__ballot(key[j] == at) & below);
-    return c;
-  };
-  uint32_t cut = 1u;
-  int tie_take = 0x7fffffff, seen = 0;
-  if (top_k > 0) {
-    uint32_t prefix = 0u;
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t c = prefix | (1u << bit);
-      if (count(c) >= top_k) prefix = c;
+// Top-k cut, nucleus cut and draw over n <= SMP_THREADS / TPC candidates (sk: keys, si: tokens, in index order; LDS).  All
+// threads find every candidate's rank in the order (key descending, index ascending) by comparing it with all others, TPC
+// threads to a candidate; the ranks ARE the top-k cut, and one wave finds the nucleus by one prefix sum over the masses in
+// rank order and draws: no serial chain of one pass per key bit is left.  What bounded it was that chain.  The selection
+// kernel with top-p 0.95, us, with this and the bound that each wave finds by itself (below); in brackets with the bits
+// bisected by one wave (up to 256 candidates) or by all with a barrier per pass: vocabulary 500 and 1024, top-k 50 13.4 and
+// 11.1 (16.6, 16.8), 1024, top-k 300 21.1 (38.9); 32000, top-k 50 22.1 (26.6).  Not gained: 32000, top-k 200 27.0 (26.7);
+// 1024, top-k 600, which takes the steps it took, 39.6 (38.9).  With one thread to each of up to 1024 candidates the last wave
+// holds 16 a lane, which spill: top-k 600 45.9.  scratch: SMP_THREADS words of LDS nobody reads any more.
+// Returns the token in every thread.
+template <int TPC>
+__device__ __forceinline__ int smp_ranked_pick(const uint32_t* sk, const int* si, int n, int top_k, float zmax, float top_p,
+                                               float u, float* scratch, int* found) {
+  static_assert(TPC == 2 || TPC == 4, "a candidate's threads lie in one quad");
+  constexpr int PER = SMP_THREADS / TPC / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  int* rank_of = reinterpret_cast<int*>(scratch);
+  float* sorted = scratch + SMP_THREADS / TPC;
+  {
+    const int c = tid / TPC, q = tid & (TPC - 1);
+    const uint32_t key = c < n ? sk[c] : 0u;
+    int r = 0;
+#pragma unroll 4
+    for (int j = q; j < n; j += TPC) {
+      const uint32_t other = sk[j];
+      r += other > key || (other == key && j < c);
     }
-    cut = prefix;
-    tie_take = top_k - (cut == 0xffffffffu ? 0 : count(cut + 1u));
-    seen = ties_before(cut);
+    r += __builtin_amdgcn_update_dpp(0, r, 0xB1, 0xf, 0xf, true);
+    if (TPC == 4) r += __builtin_amdgcn_update_dpp(0, r, 0x4E, 0xf, 0xf, true);
+    if (q == 0 && c < n) rank_of[c] = r;
   }
-  float e[PER], mine = 0.f;
+  __syncthreads();
+  if (tid < 64) {
+    int rank[PER], id[PER];
+    float e[PER];
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    bool in = key[j] > cut;
-    if (key[j] == cut && key[j] != 0u) { in = seen < tie_take; ++seen; }
-    if (!in) key[j] = 0u;
-    e[j] = in ? expf(key_to_float(key[j]) - zmax) : 0.f;
-    mine += e[j];
-  }
-  if (top_p < 1.f) {
-    const float want = top_p * wave_sum(mine);
-    uint32_t prefix = 0u;
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t c = prefix | (1u << bit);
-      float m = 0.f;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) m += key[j] >= c ? e[j] : 0.f;
-      if (wave_sum(m) >= want) prefix = c;
+    for (int j = 0; j < PER; ++j) {
+      const int c = lane * PER + j;
+      const bool have = c < n;
+      rank[j] = have ? rank_of[c] : c;              // (places n .. of the sorted order are empty)
+      id[j] = have ? si[c] : 0;
+      e[j] = have && rank[j] < top_k ? expf(key_to_float(sk[c]) - zmax) : 0.f;
+      sorted[rank[j]] = e[j];
     }
-    if (prefix != 0u) {                            // prefix = 0: rounding left the total below the target, keep all
-      float above = 0.f;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // read back by other lanes of this wave
+    __builtin_amdgcn_wave_barrier();
+    auto scan = [&](float mine) {                   // running sum over the lanes, this one included
 #pragma unroll
-      for (int j = 0; j < PER; ++j) above += key[j] > prefix ? e[j] : 0.f;
-      const float etau = expf(key_to_float(prefix) - zmax);     // (some candidate has this key)
-      int n_tie = (int)ceilf((want - wave_sum(above)) / etau);
-      if (n_tie < 1) n_tie = 1;
-      int before = ties_before(prefix);
-      mine = 0.f;
+      for (int off = 1; off < 64; off <<= 1) {
+        const float up = __shfl_up(mine, off);
+        if (lane >= off) mine += up;
+      }
+      return mine;
+    };
+    if (top_p < 1.f) {
+      // smallest prefix of the rank order that holds top_p of the mass; rounding may leave the total below it: keep all
+      float v[PER], mine = 0.f;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) mine += v[j] = sorted[lane * PER + j];
+      const float incl = scan(mine), want = top_p * __shfl(incl, 63);
+      float run = __shfl_up(incl, 1);
+      if (lane == 0) run = 0.f;
+      int last = 0x7fffffff;
 #pragma unroll
       for (int j = 0; j < PER; ++j) {
-        bool in = key[j] > prefix;
-        if (key[j] == prefix) { in = before < n_tie; ++before; }
-        if (!in) e[j] = 0.f;
-        mine += e[j];
+        run += v[j];
+        if (last == 0x7fffffff && run >= want) last = lane * PER + j;
+      }
+      const unsigned long long hit = __ballot(last != 0x7fffffff);
+      last = hit ? __builtin_amdgcn_readlane(last, __builtin_ctzll(hit)) : n;
+#pragma unroll
+      for (int j = 0; j < PER; ++j)
+        if (rank[j] > last) e[j] = 0.f;
+    }
+    // the draw: running sum of e in index order against u * total; the lowest token past it, or the last kept one
+    float mine = 0.f;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) mine += e[j];
+    const float incl = scan(mine), target = u * __shfl(incl, 63);
+    float run = __shfl_up(incl, 1);
+    if (lane == 0) run = 0.f;
+    int pick = 0x7fffffff, last = -1;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (e[j] > 0.f) {
+        run += e[j];
+        if (pick == 0x7fffffff && run > target) pick = id[j];
+        last = id[j];
       }
     }
+    const unsigned long long hit = __ballot(pick != 0x7fffffff), kept = __ballot(last >= 0);
+    const int t = hit ? __builtin_amdgcn_readlane(pick, __builtin_ctzll(hit))
+                      : kept ? __builtin_amdgcn_readlane(last, 63 - __builtin_clzll(kept)) : 0;
+    if (tid == 0) *found = t;
   }
-  // the draw: running sum of e in index order against u * total; the lowest token past it, or the last kept one
-  float incl = mine;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const float up = __shfl_up(incl, off);
-    if (lane >= off) incl += up;
-  }
-  const float target = u * __shfl(incl, 63);
-  float run = __shfl_up(incl, 1);
-  if (lane == 0) run = 0.f;
-  int pick = 0x7fffffff, last = -1;
-#pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    if (e[j] > 0.f) {
-      run += e[j];
-      if (pick == 0x7fffffff && run > target) pick = id[j];
-      last = id[j];
-    }
-  }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    pick = min(pick, __shfl_xor(pick, off));
-    last = max(last, __shfl_xor(last, off));
-  }
-  return pick != 0x7fffffff ? pick : last < 0 ? 0 : last;
+  __syncthreads();
+  return *found;
 }
-#define SMP_WAVE_PER 4      // candidates per lane of smp_wave_pick
 
 // One draw from logits[0 .. vocab) by a workgroup of SMP_THREADS threads (all of them call this;
 // vocab <= SMP_MAX_VOCAB, cfg->inv_temp != 0).  smp_z: SMP_Z_WORDS words of LDS; si, sk: SMP_THREADS
@@ -411,15 +411,17 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
   // k-th largest key (at least k keys reach it), found with one slot per thread.  Its upper 16 bits (1 % of the
   // value) are mostly bound enough; where more than one wave's candidates reach them (logits that share an offset much
   // larger than their spread) the lower bits are found too (32000 logits of 100 +- 0.5 at temperature 0.8, top-k 200, a
-  // step: 95.6 us without, 66.3 with).  What reaches the bound is packed in index order, and one wave
-  // finishes up to 256 candidates; more go on with one slot per thread.
+  // step: 95.6 us without, 66.3 with).  What reaches the bound is packed in index order, and up to 512 candidates
+  // are ranked; more go on with one slot per thread.
   bool done = false;
   if (top_k > 0 && top_k <= SMP_THREADS) {
     uint32_t tmax[1] = {0u};
 #pragma unroll
     for (int j = 0; j < SMP_PER; ++j) tmax[0] = key[j] > tmax[0] ? key[j] : tmax[0];
-    uint32_t bound = smp_kth_largest<1>(tmax, top_k, red, phase, 16);
-    int at, nreach;
+    uint32_t bound = 0u;
+    // candidates to go on with: as many as the smallest split of the ranking that holds top_k of them
+    const int enough = top_k <= SMP_THREADS / 4 ? SMP_THREADS / 4 : SMP_THREADS / 2;
+    int at, nreach = SMP_THREADS + 1;
     auto count_reach = [&]() {
       int reach = 0;
 #pragma unroll
@@ -428,8 +430,32 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
       at = (int)(smp_block_scan_excl((float)reach, red, phase, &all) + 0.5f);
       nreach = (int)(all + 0.5f);
     };
-    count_reach();
-    if (bound != 0u && nreach > 64 * SMP_WAVE_PER) {       // uniform: `all` is the same in every thread
+    if (top_k <= SMP_THREADS / 8 && vocab > per * (SMP_THREADS - 64)) {
+      // cheaper still: every wave finds the ceil(k / 16)-th largest of its own threads' maxima, and the smallest of the 16
+      // is reached by at least k keys: ballots and one barrier in place of one barrier per pass.  Only where every wave holds
+      // tokens (a wave without them would make the bound 0), and up to top-k 128: past it more than 256 reach this bound, and
+      // ranking those costs more than the passes (32000 tokens, top-k 200: 30.7 us against 27.0)
+      constexpr int NW = SMP_THREADS / 64;
+      const int kw = (top_k + NW - 1) / NW;
+      uint32_t prefix = 0u;
+      for (int bit = 31; bit >= 16; --bit) {
+        const uint32_t c = prefix | (1u << bit);
+        if (__builtin_popcountll(__ballot(tmax[0] >= c)) >= kw) prefix = c;
+      }
+      uint32_t* bank = reinterpret_cast<uint32_t*>(red) + (phase & 1) * 3 * NW;
+      ++phase;
+      if ((tid & 63) == 0) bank[tid >> 6] = prefix;
+      __syncthreads();
+      bound = bank[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) bound = bank[w] < bound ? bank[w] : bound;
+      if (bound != 0u) count_reach();
+    }
+    if (nreach > enough) {                                 // uniform: what counts is the same in every thread
+      bound = smp_kth_largest<1>(tmax, top_k, red, phase, 16);
+      count_reach();
+    }
+    if (bound != 0u && nreach > enough) {
       bound = smp_kth_largest<1>(tmax, top_k, red, phase, 0, 15, bound);
       count_reach();
     }
@@ -443,22 +469,8 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
         }
       }
       __syncthreads();
-      if (nreach <= 64 * SMP_WAVE_PER) {
-        if (tid < 64) {
-          uint32_t kw[SMP_WAVE_PER];
-          int iw[SMP_WAVE_PER];
-#pragma unroll
-          for (int j = 0; j < SMP_WAVE_PER; ++j) {
-            const int c = tid * SMP_WAVE_PER + j;
-            kw[j] = c < nreach ? sk[c] : 0u;
-            iw[j] = c < nreach ? si[c] : 0;
-          }
-          const int t = smp_wave_pick<SMP_WAVE_PER>(kw, iw, top_k, zmax, cfg->top_p, u);
-          if (tid == 0) *found = t;
-        }
-        __syncthreads();
-        return *found;
-      }
+      if (nreach <= SMP_THREADS / 4) return smp_ranked_pick<4>(sk, si, nreach, top_k, zmax, cfg->top_p, u, smp_z, found);
+      if (nreach <= SMP_THREADS / 2) return smp_ranked_pick<2>(sk, si, nreach, top_k, zmax, cfg->top_p, u, smp_z, found);
       uint32_t k1[1] = {tid < nreach ? sk[tid] : 0u};
       float e1[1];
       const int id = tid < nreach ? si[tid] : 0;

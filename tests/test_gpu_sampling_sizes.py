@@ -59,3 +59,23 @@ def test_equal_logits_at_a_vocabulary_that_one_wave_finishes(torch_cuda):  # noq
             s.ll_set_sampling(1.0, k, p, 99)
             toks = [s.ll_prefill([1, 2, 3])] + [s.ll_decode_step() for _ in range(20)]
             assert toks == [int(np.float32(sp.uniform(99, i)) * np.float32(kept)) for i in range(21)]
+
+
+@pytest.mark.parametrize("vocab", [960, 961, 1024, 1920, 1921, 31700])
+def test_top_k_where_the_bound_and_the_ranking_change(torch_cuda, vocab):  # noqa: F811
+    """The bound comes from each wave by itself up to top-k 128 where all 16 waves hold tokens (over 960 of one a thread,
+    1920 of two); up to 256 and 512 candidates are ranked by four and two threads each, more have one slot per
+    thread.  Either side of each line, and ~100 tokens that tie at the cut."""
+    cfg = wl.custom_cfg(1, 2, 64, 136, vocab, 60)
+    w = wl.make_weights_numpy(cfg, seed=61, emb_std=1.0)
+    w["lm_head"] = (w["lm_head"] * 30.0).astype(w["lm_head"].dtype)     # logits a few units wide
+    w["lm_head"][5::max(7, vocab // 100)] = w["lm_head"][0]
+    w = wl.weights_astype(w, np.float16)
+    prompt = wl.make_tokens(6, vocab, seed=3)
+    total = exact = 0
+    with _session(cfg, w) as s:
+        for j, (k, p) in enumerate([(1, 1.0), (16, 0.9), (17, 1.0), (128, 0.95), (129, 1.0), (255, 1.0), (256, 0.95), (257, 0.5), (511, 1.0), (513, 0.95), (900, 0.9)]):
+            toks, ex = _run(s, prompt, 20, 1.5, k, p, seed=4000 + j)
+            total += len(toks)
+            exact += ex
+    assert exact >= 0.95 * total, (exact, total)
