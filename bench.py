@@ -240,7 +240,8 @@ def main():
         return 0
     if args.launch_gaps:
         shape, how = args.launch_gaps.split("-")
-        flags = binding.LL_FLAG_EAGER if how == "eager" else 0
+        # the same kernels either way (with no flag the tiny model takes all its steps in one kernel)
+        flags = binding.LL_FLAG_EAGER if how == "eager" else binding.LL_FLAG_MULTIKERNEL
         if shape == "tiny":
             gcfg = wl.tiny_cfg(max_seq=1024)
             gw = wl.weights_to_torch(wl.make_weights_numpy(gcfg, seed=0), device="cuda:0", dtype=torch.float16)
