@@ -439,14 +439,16 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
     }
   };
 
-  // First the partial sums of squares of the tokens this wave finishes (2 TB wave, ..): K <= 4096 leaves at most 256
-  // slots of 16 columns, one 16-byte piece per lane, with no branch, so that the wait for them below leaves everything
-  // younger in flight.  Then the weight stream's first row block and the (cached) activations.
+  // First the partial sums of squares of the tokens this wave finishes (2 TB wave, ..), 16 lanes to a token and slots
+  // j, j + 16, .. to lane j, as in sk_ss_issue: K <= 4096 leaves at most 256.  One lane offset and constants, no branch, so
+  // that the wait for them below leaves everything younger in flight.  Then the weight stream's first row block and the
+  // (cached) activations.
   constexpr int WT = 2 * TB;
-  f4 ssv[WT];
+  float ssv[16];
+  const __amdgpu_buffer_rsrc_t ssr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.ss_in), 0, TB * 16 * a.ss_stride * 4, 0x00027000);
+  const int ss_off = ((wave * WT + (g & (WT - 1))) * a.ss_stride + r) * 4;
 #pragma unroll
-  for (int t = 0; t < WT; ++t)
-    ssv[t] = *as_global(reinterpret_cast<const f4*>(a.ss_in + (size_t)(wave * WT + t) * a.ss_stride + min(lane * 4, a.ss_stride - 4)));
+  for (int i = 0; i < 16; ++i) ssv[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ssr, ss_off + i * 64, 0, 0));
   __builtin_amdgcn_sched_barrier(0);
   int u = blockIdx.x;
   h8 fa0[HALF], fa1[HALF];
@@ -462,13 +464,10 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
       else fb[i][t] = load_h8(a.X + (st < s_end && st * 32 + g * 8 < K ? ((long)(st * TB + t) * 64 + lane) * 8 : a.zeros_off));
     }
   __builtin_amdgcn_sched_barrier(0);
-  float ssum[WT];
+  float ssum = 0.f;
 #pragma unroll
-  for (int t = 0; t < WT; ++t) {
-    ssum[t] = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) ssum[t] += lane * 4 + e < a.ss_parts ? ssv[t][e] : 0.f;      // (slots past the last hold anything)
-  }
+  for (int i = 0; i < 16; ++i) ssum += r + 16 * i < a.ss_parts ? ssv[i] : 0.f;      // (slots past the last hold anything)
+  ssum = group_sum<16>(ssum);
   __builtin_amdgcn_sched_barrier(0);
   // The epilogue of a block is shared by all waves: lane < 16 TB of wave w finishes (lo, hi) row pair lane % 8 of token
   // 2 TB w + lane / 8, so what is stored next to each other comes from neighbouring lanes.  What it needs from memory
@@ -486,7 +485,7 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
   float ss_tok = 0.f;
 #pragma unroll
   for (int t = 0; t < WT; ++t) {
-    const float v = wave_sum(ssum[t]);
+    const float v = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ssum), 16 * t));
     if (((lane >> 3) & (WT - 1)) == t) ss_tok = v;
   }
   const float scale = 1.0f / sqrtf(ss_tok / (float)K + a.eps);
