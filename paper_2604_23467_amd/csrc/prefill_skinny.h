@@ -124,6 +124,13 @@ __device__ __forceinline__ void sk_ss_finish(const SkSsLoads& L, int K, float ep
   if (tid < TB * 256 && (tid & 15) == 0) s_scale[tid >> 4] = 1.0f / sqrtf(s / (float)K + eps);
 }
 
+// A result that is to be rounded to fp32 before it is rounded to fp16: without this a product or sum and its conversion
+// become one instruction (v_fma_mix) that rounds once
+__device__ __forceinline__ float sk_fp32(float v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 // number of 16-row blocks the kernel's grid has to cover
 __host__ __device__ inline int skinny_units(int mode, int N) {
   return mode == SK_QKV ? 3 * (N / 16) : mode == SK_GATEUP ? N / 8 : N / 16;
@@ -547,8 +554,12 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
       } else {
         half_t* dst = z == 0 ? a.Q + (size_t)etok * N + head * a.head_dim
                              : a.kc + ((size_t)head * a.max_seq + ecrow) * a.head_dim;
-        dst[j0 + ej] = (half_t)(lo * ecs.x - hi * ecs.y);
-        dst[j0 + ej + hh] = (half_t)(hi * ecs.x + lo * ecs.y);
+        // Which product is fused, and that up to 16 rows the second sum is rounded to fp32 on its way to fp16, is fixed here:
+        // left to the compiler, cached keys changed their last bits with the code around these lines.
+        float second = __builtin_fmaf(hi, ecs.x, lo * ecs.y);
+        if (TB == 1) second = sk_fp32(second);
+        dst[j0 + ej] = (half_t)__builtin_fmaf(lo, ecs.x, -(hi * ecs.y));
+        dst[j0 + ej + hh] = (half_t)second;
       }
     }
   };
