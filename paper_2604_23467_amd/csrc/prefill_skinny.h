@@ -541,7 +541,7 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
       lo *= scale;
       hi *= scale;
       if (MODE == SK_GATEUP) {
-        a.Hout[act_offset(etok, u * 8 + ej, N, TB)] = (half_t)(lo / (1.0f + expf(-lo)) * hi);
+        a.Hout[act_offset(etok, u * 8 + ej, N, TB)] = (half_t)sk_fp32(lo / (1.0f + expf(-lo)) * hi);
       } else if (MODE == SK_LOGITS) {
         float* lp = a.logits + (size_t)etok * N + u * 16 + ej;
         lp[0] = lo;

@@ -62,3 +62,29 @@ def test_key_rows_show_the_rounding_of_the_rotation(n):
             assert np.array_equal(got[:, :, 0], first.astype(F32)), int((got[:, :, 0] != first.astype(F32)).sum())
             assert np.array_equal(got[:, :, 1], second.astype(F32)), int((got[:, :, 1] != second.astype(F32)).sum())
     assert one > 0 and two > 0                # the keys tell all three forms apart
+
+
+@pytest.mark.parametrize("n", [16, 32, 1, 17])
+def test_hidden_state_shows_the_rounding_of_swiglu(n):
+    """Gates of 20 and more, where silu(g) is g itself: the SwiGLU output is g u, rounded to fp32 and then to fp16.  Down
+    is the identity, and the residual row it is added to has few enough bits for the sum to be exact."""
+    rng = np.random.default_rng(100 + n)
+    emb = (rng.integers(64, 128, (VOCAB, D)) / 64).astype(F16)
+    gain = rng.uniform(0.5, 2.0, D).astype(F16)
+    eye = np.eye(D, dtype=F16)
+    s, cfg = _session(emb, gain, D, w_gate=eye * F16(128), w_up=eye, w_down=eye)
+    told = 0
+    with s:
+        for r in range(96):
+            p = rng.integers(0, VOCAB, n).astype(np.int32)
+            s.ll_reset()
+            s.ll_prefill(p)
+            u = _normalised(emb[p[-1:]], gain, cfg["rms_eps"], _strided)[0]
+            g = u * F32(128)
+            assert g.min() >= 20.0 and (g.astype(np.float64) * u).max() < 2048.0
+            h = (g * u).astype(F16)
+            told += int((h != (g.astype(np.float64) * u).astype(F16)).sum())
+            want = emb[p[-1]].astype(F32) + h.astype(F32)
+            got = s.ll_dbg_get_hidden()
+            assert np.array_equal(got, want), int((got != want).sum())
+    assert told > 0                           # the rows tell one rounding from two
