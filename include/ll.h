@@ -273,6 +273,13 @@ int ll_batch_dbg_time_steps(int32_t k, float *ms_out);
 /* Most polls of one hand-off in the kernel that runs small models' decode steps, before the step is given up and redone by
  * the multi-kernel graph.  Returns 1 where that kernel is in use, 0 where it is not (nothing is changed then). */
 int ll_dbg_set_spin_limit(int32_t polls);
+/* Lets that kernel give up at a token (counted from the reset: the prefill's is 0), as if every wait had run out there;
+ * negative: never.  Returns as ll_dbg_set_spin_limit does. */
+int ll_dbg_give_up_at(int32_t token);
+/* That kernel's plan for a configuration (host arithmetic only, needs no instance and no GPU): out2 = { workgroups (0: the
+ * configuration's steps are the multi-kernel graph), first position of a launch of `steps` steps (0: one step in front of
+ * the selection kernel) where the device state says `pos` }. */
+int ll_dbg_small_plan(const ll_config *cfg, int32_t pos, int32_t steps, int32_t *out2);
 
 /* Per-length graph mode: out4 = { replays that found their graph in the buffer, captures that
  * blocked a step, captures overlapped with a replay, nanoseconds spent capturing }. */

@@ -30,7 +30,7 @@ EXPORTS = ("ll_workspace_bytes", "ll_init", "ll_prefill", "ll_prefill_static", "
            "ll_set_sampling", "ll_shutdown", "ll_max_prompt", "ll_position", "ll_decode_mode", "ll_last_error", "ll_dbg_get_logits",
            "ll_batch_pool_bytes", "ll_batch_open", "ll_batch_add", "ll_batch_step", "ll_batch_remove", "ll_batch_close",
            "ll_batch_dbg_get_logits", "ll_batch_dbg_force_next_token", "ll_batch_dbg_time_steps",
-           "ll_dbg_get_hidden", "ll_dbg_set_spin_limit", "ll_dbg_graph_stats", "ll_dbg_gemm_plan", "ll_dbg_gemm_slice_count", "ll_dbg_tile_plan", "ll_dbg_force_next_token", "ll_dbg_get_kv", "ll_dbg_profile_decode",
+           "ll_dbg_get_hidden", "ll_dbg_set_spin_limit", "ll_dbg_give_up_at", "ll_dbg_small_plan", "ll_dbg_graph_stats", "ll_dbg_gemm_plan", "ll_dbg_gemm_slice_count", "ll_dbg_tile_plan", "ll_dbg_force_next_token", "ll_dbg_get_kv", "ll_dbg_profile_decode",
            "ll_dbg_time_decode", "ll_dbg_time_kernel_class", "ll_dbg_stream_copy", "ll_dbg_stream_read", "ll_dbg_poison_scratch", "ll_dbg_trace_decode")
 
 
@@ -117,6 +117,10 @@ def load():
     L.ll_dbg_gemm_slice_count.argtypes = [C.c_int32] * 5
     L.ll_dbg_set_spin_limit.restype = C.c_int
     L.ll_dbg_set_spin_limit.argtypes = [C.c_int32]
+    L.ll_dbg_give_up_at.restype = C.c_int
+    L.ll_dbg_give_up_at.argtypes = [C.c_int32]
+    L.ll_dbg_small_plan.restype = C.c_int
+    L.ll_dbg_small_plan.argtypes = [C.POINTER(LLConfig), C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
     L.ll_dbg_graph_stats.restype = C.c_int
     L.ll_dbg_graph_stats.argtypes = [C.POINTER(C.c_int64)]
     L.ll_dbg_get_hidden.restype = C.c_int
@@ -194,6 +198,13 @@ def ll_dbg_tile_plan(kind, N, K, rows):
     out = (C.c_int32 * 6)()
     _check(load().ll_dbg_tile_plan(kind, N, K, rows, out))
     return dict(zip(("row_tiles", "col_tiles", "blocks", "pieces", "stage_steps", "workgroups"), out))
+
+
+def ll_dbg_small_plan(cfg, pos, steps, flags=0):
+    """How a small model's decode steps run in one kernel (host arithmetic, no GPU needed)."""
+    out = (C.c_int32 * 2)()
+    _check(load().ll_dbg_small_plan(C.byref(make_config(cfg, flags)), pos, steps, out))
+    return dict(zip(("workgroups", "first_pos"), out))
 
 
 def ll_dbg_gemm_slice_count(N, K, nmat, rows, col):
@@ -354,6 +365,9 @@ class Session:
 
     def ll_dbg_set_spin_limit(self, polls):
         return bool(_check(self.lib.ll_dbg_set_spin_limit(polls)))
+
+    def ll_dbg_give_up_at(self, token):
+        return bool(_check(self.lib.ll_dbg_give_up_at(token)))
 
     def ll_dbg_graph_stats(self):
         out = (C.c_int64 * 4)()

@@ -35,9 +35,11 @@
 // its poll, whose round trip covers theirs; loads return in order.  A wave owns the same two rows of the residual stream
 // throughout and keeps them in registers.
 //
-// Every poll is bounded: past `spin_limit` rounds the wave raises DevState::fault, polls no more and stores no
-// more, so whoever depends on it runs out as well and the grid drains (no index depends on the values); the steps without
-// a token report -1 and the host takes the multi-kernel path from there.
+// Every poll is bounded: past `spin_limit` rounds the wave raises DevState::fault, polls no more and stores no hand-off and no
+// cache row any more, so whoever depends on it runs out as well and the grid drains.  No index depends on a value that was
+// waited for, and the position and epoch that indexes do depend on are advanced only by a wave that nobody let down: a
+// workgroup that starts after the others gave up works at the position they worked at.  The steps without a token report
+// -1 and the host takes the multi-kernel path from there.
 #pragma once
 #include "ll_device.h"
 
@@ -68,6 +70,7 @@ struct SmArgs {
   int* epoch;                   // steps run so far; its parity selects the set
   int steps;                    // greedy steps of this launch; 0: one step, its token left to the selection kernel
   int ring_size, n_layers, d, n_heads, F, vocab, max_seq, max_splits, spin_limit;
+  int give_up;                  // token (counted from the reset) from which on no wave waits any more; past the ring: none
   float eps;
 };
 
@@ -103,6 +106,12 @@ inline int sm_max_splits(int grid, int n_heads) {
   return s;
 }
 
+// First position of a launch: the state's, but never one from which its steps would run past the cache
+__host__ __device__ inline int sm_first_pos(int pos, int steps, int max_seq) {
+  const int last = max_seq - (steps > 1 ? steps : 1);
+  return pos < last ? pos : last;
+}
+
 // Stores that other CUs of the XCD wait for: workgroup scope is through the L1 into the L2 they share
 __device__ __forceinline__ unsigned sm_word(float v) {
   const unsigned u = __builtin_bit_cast(unsigned, v);
@@ -116,6 +125,10 @@ struct SmWait {                 // a wave's state of its bounded waits
   DevState* st;
   int limit;
   bool dead;                    // wave-uniform
+  __device__ __forceinline__ void give_up() {
+    dead = true;
+    if ((threadIdx.x & 63) == 0) st_dev_i(&st->fault, 1);
+  }
 };
 
 // Polls of 16 bytes per lane and item at byte offsets `off` from a buffer of `bytes` bytes, past the L1, until no word
@@ -135,8 +148,7 @@ __device__ __forceinline__ void sm_poll(SmWait& w, const float* base, int bytes,
     for (int i = 0; i < N; ++i) top = max(max(top, max(v[i][0], v[i][1])), max(v[i][2], v[i][3]));
     if (w.dead || !__any(top == SM_EMPTY)) break;
     if (spins >= w.limit) {
-      w.dead = true;
-      if ((threadIdx.x & 63) == 0) st_dev_i(&w.st->fault, 1);
+      w.give_up();
       break;
     }
     if (spins < 64) __builtin_amdgcn_s_sleep(4);
@@ -270,7 +282,7 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
   const int d = a.d, F = a.F, nch_d = d >> 3, nch_f = F >> 3;
   const int n_qkv = 3 * (d >> 1), n_lm = (a.vocab + 1) >> 1;
   const bool owner = 2 * gw < d;                   // of residual rows 2 gw and 2 gw + 1
-  const int epoch0 = ld_dev_i(a.epoch), pos0 = a.st->pos, ring0 = a.st->steps;
+  const int epoch0 = ld_dev_i(a.epoch), pos0 = sm_first_pos(a.st->pos, a.steps, a.max_seq), ring0 = a.st->steps;
   const SmLayout L = sm_layout(d, a.n_heads, HD, F, a.max_splits);
   const LL_GLOBAL MkLayer* table = as_global(a.layers);
   const int piece = HALF ? lane & 31 : lane;       // this lane's 8 columns of a d-vector
@@ -334,6 +346,7 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
 
   int tok = 0;
   for (int step = 0; step == 0 || step < a.steps; ++step) {
+    if (ring0 + step >= a.give_up) wait.give_up();
     const int epoch = epoch0 + step, pos = pos0 + step, n_keys = pos + 1;
     float* set = a.xch + (size_t)(epoch & 1) * sm_set_floats(L, a.n_layers);
     auto empty_other = [&]() {
@@ -390,7 +403,7 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
         const int row = second ? r.b : r.a;
         if (r.sec > 0) {
           const half_t h = (half_t)v;
-          ((r.sec == 1 ? kc : vc) + ((size_t)(row / HD) * a.max_seq + pos) * HD)[row % HD] = h;
+          if (!wait.dead) ((r.sec == 1 ? kc : vc) + ((size_t)(row / HD) * a.max_seq + pos) * HD)[row % HD] = h;
           v = (float)h;
         }
         if (!wait.dead) sm_put(B, L.q + r.sec * d + row, v);
@@ -652,7 +665,7 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
       s_bv[wave] = bv;
       s_bi[wave] = wait.dead ? -1 : bi;
     }
-    if (wg == 0 && wave == 0 && lane == piece && piece < nch_d) {
+    if (wg == 0 && wave == 0 && !wait.dead && lane == piece && piece < nch_d) {
       float* keep = (a.steps > 0 ? a.x_keep : a.x) + piece * 8;
       *as_global(reinterpret_cast<f4*>(keep)) = x[0][0];
       *as_global(reinterpret_cast<f4*>(keep + 4)) = x[0][1];
@@ -697,8 +710,9 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
       res1 = (float)*as_global(e + 2 * gw + 1);
     }
   }
-  // (every workgroup has read the state by now: each one stored a part of a SwiGLU output that this one waited for)
-  if (wg == 0 && wave == 0) {
+  // Only where no wait ran out: then every workgroup has read the state, each one having stored a part of a SwiGLU output
+  // that this wave waited for.  Otherwise one may still be to come, and the host writes the state anew.
+  if (wg == 0 && wave == 0 && !wait.dead) {
     if (a.steps > 0 && lane == piece && piece < nch_d) {
       *as_global(reinterpret_cast<f4*>(a.x + piece * 8)) = x[0][0];
       *as_global(reinterpret_cast<f4*>(a.x + piece * 8 + 4)) = x[0][1];

@@ -2,6 +2,7 @@
 // kernel chains, hipGraph capture and replay, device-resident step state.
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -541,6 +542,7 @@ struct Instance {
   bool sampled = false;          // ll_set_sampling: the selection kernel draws
   int fed = 0;                   // token the next step feeds
   int small_spin_limit = 1 << 20;   // polls of one hand-off: some two seconds, then the step is redone by the kernel chain
+  int small_give_up = INT_MAX;      // test hook: token at which the small-model kernel gives up
   bool fused_attn = false;       // attention and O projection of a layer in one launch
   int mega_grid = 0;
   size_t mega_lds = 0;
@@ -825,6 +827,7 @@ void enqueue_decode_small(Instance* I, hipStream_t s, int steps) {
   a.n_layers = c.n_layers; a.d = c.d_model; a.n_heads = c.n_heads; a.F = c.ffn_hidden; a.vocab = c.vocab;
   a.max_seq = c.max_seq; a.max_splits = I->L.sm_splits; a.eps = c.rms_eps;
   a.spin_limit = I->small_spin_limit;
+  a.give_up = I->small_give_up;
   const int grid = I->L.sm_grid * SM_XCDS;
   if (c.head_dim == 64) launch_small<64>(a, grid, s);
   else launch_small<128>(a, grid, s);
@@ -2091,6 +2094,24 @@ int ll_dbg_set_spin_limit(int32_t polls) {
   g->small_spin_limit = polls;
   const int rc = recapture_decode(g);          // (the sampled step's graph holds the kernel's arguments)
   return rc == LL_OK ? 1 : rc;
+}
+
+int ll_dbg_give_up_at(int32_t token) {
+  if (!g) return fail(LL_E_NOT_INIT, "ll_dbg_give_up_at: not initialised");
+  if (!g->small) return 0;
+  HIPCHK(hipStreamSynchronize(g->stream));
+  g->small_give_up = token < 0 ? INT_MAX : token;
+  const int rc = recapture_decode(g);
+  return rc == LL_OK ? 1 : rc;
+}
+
+int ll_dbg_small_plan(const ll_config* cfg, int32_t pos, int32_t steps, int32_t* out2) {
+  const char* why = nullptr;
+  if (!config_ok(cfg, &why)) return fail(LL_E_BAD_CONFIG, "ll_dbg_small_plan: %s", why);
+  if (!out2 || pos < 0 || steps < 0 || steps > cfg->max_seq) return fail(LL_E_BAD_ARG, "ll_dbg_small_plan: bad argument");
+  out2[0] = small_grid(*cfg);
+  out2[1] = sm_first_pos(pos, steps, cfg->max_seq);
+  return LL_OK;
 }
 
 int ll_dbg_graph_stats(int64_t* out4) {
