@@ -286,7 +286,8 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
   const SmLayout L = sm_layout(d, a.n_heads, HD, F, a.max_splits);
   const LL_GLOBAL MkLayer* table = as_global(a.layers);
   const int piece = HALF ? lane & 31 : lane;       // this lane's 8 columns of a d-vector
-  SmWait wait{a.st, a.spin_limit, false};
+  // (where an earlier step of the call gave up, this one does at once; the flag from memory, not from a scalar cache)
+  SmWait wait{a.st, a.spin_limit, __builtin_amdgcn_readfirstlane(ld_dev_i(&a.st->fault)) != 0};
 
   SmRows rows[RQ];
 #pragma unroll

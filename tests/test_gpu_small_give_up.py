@@ -81,6 +81,22 @@ def test_a_launch_that_gave_up_stores_no_row(weights, sampled):
             assert r[keep].tobytes() == q[keep].tobytes()
 
 
+def test_steps_queued_behind_a_give_up_do_not_begin(weights):
+    """A sampled call queues one launch per step.  With no poll allowed to miss, the first one gives up after its layer 0
+    has stored a row; those behind it give up before."""
+    with _open(weights, True) as s:
+        s.ll_prefill(wl.make_tokens(N, 1024, seed=5))
+        s.ll_decode_n(K)
+        s.ll_reset()
+        s.ll_prefill(wl.make_tokens(N, 1024, seed=7))
+        before = _rows(s, N + K)
+        assert s.ll_dbg_set_spin_limit(0)
+        with contextlib.suppress(b.LLError):
+            s.ll_dbg_time_decode(K)
+        for r, q in zip(_rows(s, N + K), before):
+            assert r[:N].tobytes() == q[:N].tobytes() and r[N + 1:].tobytes() == q[N + 1:].tobytes()
+
+
 def test_calls_that_take_no_give_up(weights):
     with _open(weights, False, b.LL_FLAG_EAGER) as s:
         assert not s.ll_dbg_give_up_at(3)
