@@ -365,7 +365,8 @@ int ll_dbg_poison_scratch(void);
 int ll_dbg_stream_read(const void *src, size_t bytes, int32_t reps, void *sink, float *gbps_out);
 
 /* Device time of `k` decode-step replays measured with one hipEvent pair on
- * the library's stream (milliseconds for all k steps), tokens discarded. */
+ * the library's stream (milliseconds for all k steps), tokens discarded.
+ * LL_E_HIP, and no time, where a step gave up on a wait inside a kernel. */
 int ll_dbg_time_decode(int32_t k, float *ms_out);
 
 #ifdef __cplusplus

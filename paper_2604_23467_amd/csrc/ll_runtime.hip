@@ -1209,6 +1209,15 @@ int small_retry(Instance* I, int k) {
   return LL_OK;
 }
 
+// Whether each of the last k steps brought a token (a kernel whose wait for another workgroup ran out reports -1)
+int check_tokens(Instance* I, int k, const char* who) {
+  for (int i = 0; i < k; ++i)
+    if (I->host_ring[I->steps + i] < 0)
+      return fail(LL_E_HIP, "%s: a bounded wait between workgroups of one launch ran out (are other kernels occupying the GPU?); "
+                            "call ll_reset", who);
+  return LL_OK;
+}
+
 int run_decode_steps(Instance* I, int k) {
   if (I->per_length) return run_decode_steps_per_length(I, k);
   if (I->small && !I->sampled) {
@@ -1746,10 +1755,7 @@ int32_t ll_decode_n(int32_t k, int32_t* out_tokens) {
   if (rc != LL_OK) return rc;
   HIPCHK(hipStreamSynchronize(I->stream));
   if (I->small && (rc = small_retry(I, k)) != LL_OK) return rc;
-  for (int i = 0; i < k; ++i)
-    if (I->host_ring[I->steps + i] < 0)
-      return fail(LL_E_HIP, "ll_decode: a bounded wait between workgroups of one launch ran out (are other "
-                            "kernels occupying the GPU?); call ll_reset");
+  if ((rc = check_tokens(I, k, "ll_decode")) != LL_OK) return rc;
   if (out_tokens) memcpy(out_tokens, I->host_ring + I->steps, (size_t)k * 4);
   advance(I, k);
   return I->host_ring[I->steps - 1];
@@ -2339,6 +2345,14 @@ int ll_dbg_time_decode(int32_t k, float* ms_out) {
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc != LL_OK) return rc;
+  if ((rc = check_tokens(I, k, "ll_dbg_time_decode")) != LL_OK) {      // what was timed is no step
+    if (I->small) {
+      I->small = false;                                                 // (as after ll_decode_n: its hand-offs are used up)
+      const int again = recapture_decode(I);
+      if (again != LL_OK) return again;
+    }
+    return rc;
+  }
   advance(I, k);
   return LL_OK;
 }

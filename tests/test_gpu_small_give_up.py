@@ -97,6 +97,25 @@ def test_steps_queued_behind_a_give_up_do_not_begin(weights):
             assert r[:N].tobytes() == q[:N].tobytes() and r[N + 1:].tobytes() == q[N + 1:].tobytes()
 
 
+@pytest.mark.parametrize("sampled", [False, True])
+def test_a_timed_run_that_gave_up_has_no_time(weights, sampled):
+    prompt, out = wl.make_tokens(N, 1024, seed=8), []
+    for flags in (b.LL_FLAG_MULTIKERNEL, 0):
+        with _open(weights, sampled, flags) as s:
+            s.ll_prefill(prompt)
+            if flags == 0:
+                assert s.ll_dbg_give_up_at(3)
+                with pytest.raises(b.LLError) as e:
+                    s.ll_dbg_time_decode(K)
+                assert e.value.code == b.LL_E_HIP and s.ll_position() == N
+                assert not s.ll_dbg_give_up_at(-1)    # the kernel chain from there on
+            else:
+                assert s.ll_dbg_time_decode(K) > 0
+            s.ll_reset()
+            out.append(([s.ll_prefill(prompt)] + list(s.ll_decode_n(K)), s.ll_dbg_get_logits().tobytes()))
+    assert out[0] == out[1]
+
+
 def test_calls_that_take_no_give_up(weights):
     with _open(weights, False, b.LL_FLAG_EAGER) as s:
         assert not s.ll_dbg_give_up_at(3)
