@@ -274,7 +274,8 @@ int ll_batch_dbg_time_steps(int32_t k, float *ms_out);
  * the multi-kernel graph.  Returns 1 where that kernel is in use, 0 where it is not (nothing is changed then). */
 int ll_dbg_set_spin_limit(int32_t polls);
 /* Lets that kernel give up at a token (counted from the reset: the prefill's is 0), as if every wait had run out there;
- * negative: never.  Returns as ll_dbg_set_spin_limit does. */
+ * negative: never.  Returns as ll_dbg_set_spin_limit does.  Without an instance: in the one step with which the next
+ * ll_init warms up (token 0), returning 0. */
 int ll_dbg_give_up_at(int32_t token);
 /* That kernel's plan for a configuration (host arithmetic only, needs no instance and no GPU): out2 = { workgroups (0: the
  * configuration's steps are the multi-kernel graph), first position of a launch of `steps` steps (0: one step in front of

@@ -680,7 +680,7 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
       sm_argmax(bv, bi);
       if (a.steps == 0 && lane == 0) {
         a.amax_val[wg] = bv;
-        a.amax_idx[wg] = bi;
+        a.amax_idx[wg] = wait.dead ? 0x7fffffff : bi;   // (no candidate)
       }
       if (a.steps > 0) {
         put2(cand, 2 * wg, 2 * wg + 1, bv, __builtin_bit_cast(float, bi));

@@ -572,6 +572,7 @@ struct Instance {
 };
 
 Instance* g = nullptr;
+int g_warm_up_give_up = INT_MAX;   // test hook: the same for the warm-up of the next ll_init
 
 size_t gemv_lds_bytes(int K, bool norm) {
   const int nch = (K + 511) / 512;
@@ -1396,6 +1397,7 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   Instance* I = new Instance();
   I->cfg = *cfg;
   I->L = L;
+  std::swap(I->small_give_up, g_warm_up_give_up);       // (INT_MAX again for whoever comes next)
   I->layers.assign(w->layers, w->layers + cfg->n_layers);
   I->w = *w;
   I->w.layers = I->layers.data();
@@ -1561,6 +1563,19 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   // afterwards.  Token 0 at position 0 / a one-token prompt touch only valid memory.
   if ((rc = write_state(I, 0, 0, 1, 0)) != LL_OK) return bail(rc);
   enqueue_decode(I, I->stream);
+  if (I->small) {
+    // A wait may run out here too (the GPU is busy, its workgroups not resident together): what that leaves in the hand-offs
+    // must not be taken for values of a later step.  Looked at now: the prefills below start from a state of their own.
+    int fault = 0;
+    if (!hip_or_bail(hipStreamSynchronize(I->stream), "warm-up") ||
+        !hip_or_bail(hipMemcpy(&fault, &I->state()->fault, 4, hipMemcpyDeviceToHost), "hipMemcpy(fault)")) return bail(rc);
+    I->small_give_up = INT_MAX;
+    if (fault) {
+      I->small = false;
+      if ((rc = write_state(I, 0, 0, 1, 0)) != LL_OK) return bail(rc);
+      enqueue_decode(I, I->stream);
+    }
+  }
   for (int b : I->pf_buckets) enqueue_prefill(I, I->stream, b);      // (each starts from the staged state: one token)
   if (!hip_or_bail(hipStreamSynchronize(I->stream), "warm-up")) return bail(rc);
   if (!hip_or_bail(hipGetLastError(), "warm-up launch")) return bail(rc);
@@ -2103,8 +2118,8 @@ int ll_dbg_set_spin_limit(int32_t polls) {
 }
 
 int ll_dbg_give_up_at(int32_t token) {
-  if (!g) return fail(LL_E_NOT_INIT, "ll_dbg_give_up_at: not initialised");
-  if (!g->small) return 0;
+  if (!g) g_warm_up_give_up = token < 0 ? INT_MAX : token;
+  if (!g || !g->small) return 0;
   HIPCHK(hipStreamSynchronize(g->stream));
   g->small_give_up = token < 0 ? INT_MAX : token;
   const int rc = recapture_decode(g);

@@ -540,7 +540,7 @@ __global__ __launch_bounds__(SMP_THREADS) void sample_kernel(const float* __rest
       __syncthreads();
     }
     tok = si[0];
-    if (tok == 0x7fffffff) tok = 0;   // every logit NaN: still a valid id
+    if ((unsigned)tok >= (unsigned)vocab) tok = 0;   // no candidate (every logit NaN): still a valid id
   } else {
     tok = smp_draw_token(logits, vocab, cfg, (uint32_t)(prefill ? 0 : st->steps), smp_z, si, sk, red, &found);
   }

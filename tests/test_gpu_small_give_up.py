@@ -116,6 +116,20 @@ def test_a_timed_run_that_gave_up_has_no_time(weights, sampled):
     assert out[0] == out[1]
 
 
+@pytest.mark.parametrize("sampled", [False, True])
+def test_a_warm_up_that_gave_up_leaves_the_kernel_chain(weights, sampled):
+    prompt, out = wl.make_tokens(N, 1024, seed=8), []
+    for flags in (b.LL_FLAG_MULTIKERNEL, 0):
+        assert b.load().ll_dbg_give_up_at(0 if flags == 0 else -1) == 0
+        with _open(weights, sampled, flags) as s:
+            assert not s.ll_dbg_give_up_at(-1)
+            out.append(([s.ll_prefill(prompt)] + list(s.ll_decode_n(K)), s.ll_dbg_get_logits().tobytes()))
+    assert out[0] == out[1]
+    with _open(weights, sampled) as s:                # the next instance's warm-up is its own
+        assert s.ll_dbg_give_up_at(-1)
+        assert [s.ll_prefill(prompt)] + list(s.ll_decode_n(K)) == out[0][0]
+
+
 def test_calls_that_take_no_give_up(weights):
     with _open(weights, False, b.LL_FLAG_EAGER) as s:
         assert not s.ll_dbg_give_up_at(3)
