@@ -69,9 +69,12 @@ enum {
                               of the two flags the library picks the faster one it has measured
                               for the 7B shape, currently the multi-kernel graph; where no other
                               decode flag is set either, models of at most 512 x 1536 (d_model x
-                              ffn_hidden) run their decode steps in one kernel on one XCD, and
-                              fall back to the multi-kernel graph, for good, should its workgroups
-                              ever not be resident together. */
+                              ffn_hidden), with a wave for every two elements of the residual
+                              stream (16 min(32, CUs / 8, ffn_hidden / 8) >= d_model), run their
+                              decode steps in one kernel on one XCD, up to as many cached positions
+                              as the vocabulary and the number of layers leave that the faster way
+                              (ll_dbg_small_plan), and fall back to the multi-kernel graph, for
+                              good, should its workgroups ever not be resident together. */
   LL_FLAG_PER_LENGTH_GRAPHS = 8,
                            /* the paper's own mechanism, kept as an ablation (Alg. 1, Sec. IV-A):
                               one decode graph PER KV LENGTH in a rolling buffer of 8 with
@@ -277,10 +280,11 @@ int ll_dbg_set_spin_limit(int32_t polls);
  * negative: never.  Returns as ll_dbg_set_spin_limit does.  Without an instance: in the one step with which the next
  * ll_init warms up (token 0), returning 0. */
 int ll_dbg_give_up_at(int32_t token);
-/* That kernel's plan for a configuration (host arithmetic only, needs no instance and no GPU): out2 = { workgroups (0: the
+/* That kernel's plan for a configuration (host arithmetic only, needs no instance and no GPU): out4 = { workgroups (0: the
  * configuration's steps are the multi-kernel graph), first position of a launch of `steps` steps (0: one step in front of
- * the selection kernel) where the device state says `pos` }. */
-int ll_dbg_small_plan(const ll_config *cfg, int32_t pos, int32_t steps, int32_t *out2);
+ * the selection kernel) where the device state says `pos`, cached positions up to which a greedy, a sampled step runs in it,
+ * its own among them (0: none does) }. */
+int ll_dbg_small_plan(const ll_config *cfg, int32_t pos, int32_t steps, int32_t *out4);
 
 /* Per-length graph mode: out4 = { replays that found their graph in the buffer, captures that
  * blocked a step, captures overlapped with a replay, nanoseconds spent capturing }. */

@@ -202,9 +202,9 @@ def ll_dbg_tile_plan(kind, N, K, rows):
 
 def ll_dbg_small_plan(cfg, pos, steps, flags=0):
     """How a small model's decode steps run in one kernel (host arithmetic, no GPU needed)."""
-    out = (C.c_int32 * 2)()
+    out = (C.c_int32 * 4)()
     _check(load().ll_dbg_small_plan(C.byref(make_config(cfg, flags)), pos, steps, out))
-    return dict(zip(("workgroups", "first_pos"), out))
+    return dict(zip(("workgroups", "first_pos", "greedy_keys", "sampled_keys"), out))
 
 
 def ll_dbg_gemm_slice_count(N, K, nmat, rows, col):

@@ -100,6 +100,22 @@ inline int sm_grid(int d, int F, int cus) {
   if (g > F / SM_WAVES) g = F / SM_WAVES;
   return g * SM_WAVES * 2 >= d ? g : 0;
 }
+// Largest number of keys, the new one among them, with which a step is faster here than in the kernel chain; 0: never.
+// What the chain's launches cost is won, 10 us a step and 11 a layer; what one XCD takes longer for than eight is lost: 2.45 us
+// per million weights of a layer, 3 us per 1000 keys and layer, 0.27 us per row pair of the LM head and wave; and a sampled
+// step (one launch of its own, the candidates in memory) wins 12 us less.  Fitted to steps of 1 .. 8 layers of 64 / 136 ..
+// 512 / 1536 (d_model / ffn_hidden), both ways; us here / us in the chain, on either side of the line:
+//   vocabulary, 20 keys      1 layer of 256 / 688: 32000 37.2 / 42.1, 64000 62.2 / 52.3    1 of 512 / 1408: 16384 34.3 / 38.6,
+//                            32000 50.3 / 44.3    4 of 512 / 1408: 32000 93.1 / 103.6, 64000 125.3 / 114.2
+//   sampled, top-k 50        1 of 256 / 688: 8192 42.3 / 45.4, 16384 51.0 / 49.3
+//   keys, vocabulary 1024    1 of 256 / 688: 6000 34.1 / 38.8, 8000 41.5 / 39.4    8 of 256 / 688: 3000 161.9 / 188.8, 6000
+//                            247.9 / 221.7    4 of 512 / 1408: 800 85.6 / 96.1, 3000 116.3 / 105.6
+inline int sm_max_keys(int d, int F, int n_layers, int vocab, int grid, bool sampled) {
+  const double weights = 4.0 * d * d + 3.0 * d * F;
+  const double won = 10.0 + n_layers * (11.0 - 2.45e-6 * weights) - 0.27 * vocab / (2.0 * grid * SM_WAVES) - (sampled ? 12.0 : 0.0);
+  const double keys = won / (0.003 * n_layers);
+  return keys < 1.0 ? 0 : keys > (1 << 30) ? 1 << 30 : (int)keys;
+}
 inline int sm_max_splits(int grid, int n_heads) {
   int s = SM_MAX_SPLITS;
   while (s > 1 && n_heads * s > grid * SM_WAVES) s >>= 1;

@@ -333,6 +333,7 @@ struct Layout {
   size_t mk_layers, mk_bar, mk_amax_val, mk_amax_idx, mk_trace, zeros, sample_cfg, ao_sync;
   size_t sm_xch, sm_epoch;  // hand-off buffers of the small-model step kernel (two sets), and its step count
   int sm_grid, sm_splits;   // its workgroups (0: the model is not one of its kind), attention splits per head at most
+  int sm_keys[2];           // keys up to which a greedy, a sampled step runs in it
   size_t wf;                // fragment-major copy of the projection weights for the short-prompt kernels (0 bytes without it)
   size_t wf_qkv, wf_o, wf_gu, wf_down, wf_layer, wf_lm;   // offsets inside a layer's part, bytes per layer, offset of the LM head's copy
   size_t total;
@@ -358,6 +359,10 @@ int gemv_grid(int pairs, int wg_threads = LL_WG) {
 int small_grid(const ll_config& c) {
   if (c.flags & ~LL_FLAG_LEAN_WORKSPACE) return 0;          // every other flag asks for one of the other decode modes
   return sm_grid(c.d_model, c.ffn_hidden, num_cus());
+}
+int small_keys(const ll_config& c, bool sampled) {
+  const int grid = small_grid(c);
+  return grid ? sm_max_keys(c.d_model, c.ffn_hidden, c.n_layers, c.vocab, grid, sampled) : 0;
 }
 
 Layout make_layout(const ll_config& c) {
@@ -418,7 +423,9 @@ Layout make_layout(const ll_config& c) {
   L.mk_amax_val = take(1024 * 4);   // one candidate per workgroup of the persistent kernel
   L.mk_amax_idx = take(1024 * 4);
   L.mk_trace = take((size_t)(5 * c.n_layers + 2) * 8 * 8);
-  L.sm_grid = small_grid(c);
+  L.sm_keys[0] = small_keys(c, false);
+  L.sm_keys[1] = small_keys(c, true);                       // (never more than that)
+  L.sm_grid = L.sm_keys[0] > 0 ? small_grid(c) : 0;
   if (L.sm_grid > 0) {
     L.sm_splits = sm_max_splits(L.sm_grid, c.n_heads);
     L.sm_xch = take(2 * sm_set_floats(sm_layout(c.d_model, c.n_heads, c.head_dim, c.ffn_hidden, L.sm_splits), c.n_layers) * 4);
@@ -519,6 +526,8 @@ struct Instance {
   bool own_stream = false;
   hipGraph_t dec_graph = nullptr;
   hipGraphExec_t dec_exec = nullptr;
+  hipGraph_t small_graph = nullptr;         // one sampled step of the small-model kernel
+  hipGraphExec_t small_exec = nullptr;
   bool skinny = false;          // prompts of <= 32 tokens take the short-prompt kernels
   std::vector<int> pf_buckets;
   std::vector<hipGraph_t> pf_graph;
@@ -538,7 +547,7 @@ struct Instance {
   std::vector<hipEvent_t>* prof_events = nullptr;
   std::vector<int>* prof_class = nullptr;
   bool use_mega = false;         // decode step = one persistent kernel
-  bool small = false;            // decode steps run in the small-model kernel
+  bool small = false;            // decode steps run in the small-model kernel up to L.sm_keys keys
   bool sampled = false;          // ll_set_sampling: the selection kernel draws
   int fed = 0;                   // token the next step feeds
   int small_spin_limit = 1 << 20;   // polls of one hand-off: some two seconds, then the step is redone by the kernel chain
@@ -836,7 +845,6 @@ void enqueue_decode_small(Instance* I, hipStream_t s, int steps) {
 }
 
 void enqueue_decode(Instance* I, hipStream_t s) {
-  if (I->small && I->only_class < 0 && !I->prof_events) return enqueue_decode_small(I, s, 0);
   if (I->use_mega && I->only_class < 0 && !I->prof_events) enqueue_decode_mega(I, s);
   else enqueue_decode_multi(I, s);
 }
@@ -1085,6 +1093,8 @@ void destroy(Instance* I) {
   if (I->cap_stream) (void)hipStreamDestroy(I->cap_stream);
   if (I->dec_exec) (void)hipGraphExecDestroy(I->dec_exec);
   if (I->dec_graph) (void)hipGraphDestroy(I->dec_graph);
+  if (I->small_exec) (void)hipGraphExecDestroy(I->small_exec);
+  if (I->small_graph) (void)hipGraphDestroy(I->small_graph);
   if (I->pf_body_exec) (void)hipGraphExecDestroy(I->pf_body_exec);
   if (I->pf_body_graph) (void)hipGraphDestroy(I->pf_body_graph);
   for (auto e : I->pf_exec) if (e) (void)hipGraphExecDestroy(e);
@@ -1181,12 +1191,18 @@ void advance(Instance* I, int k) {
   I->last_logits = I->pf.logits;
 }
 
-int recapture_decode(Instance* I) {
-  if (I->dec_exec) (void)hipGraphExecDestroy(I->dec_exec);
-  if (I->dec_graph) (void)hipGraphDestroy(I->dec_graph);
-  I->dec_exec = nullptr;
-  I->dec_graph = nullptr;
-  return capture(I, &I->dec_graph, &I->dec_exec, 0);
+// The sampled step of the small-model kernel (again, where an argument changed)
+int capture_small(Instance* I) {
+  if (I->small_exec) (void)hipGraphExecDestroy(I->small_exec);
+  if (I->small_graph) (void)hipGraphDestroy(I->small_graph);
+  I->small_exec = nullptr;
+  I->small_graph = nullptr;
+  HIPCHK(hipStreamBeginCapture(I->stream, hipStreamCaptureModeThreadLocal));
+  enqueue_decode_small(I, I->stream, 0);
+  hipError_t e = hipStreamEndCapture(I->stream, &I->small_graph);
+  if (e != hipSuccess) return fail(LL_E_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+  HIPCHK(hipGraphInstantiate(&I->small_exec, I->small_graph, nullptr, nullptr, 0));
+  return LL_OK;
 }
 
 // A wait between the small-model kernel's workgroups ran out (they were not resident together): the step that has no
@@ -1197,8 +1213,7 @@ int small_retry(Instance* I, int k) {
   while (done < k && I->host_ring[I->steps + done] >= 0) ++done;
   if (done == k) return LL_OK;
   I->small = false;
-  int rc = recapture_decode(I);
-  if (rc != LL_OK) return rc;
+  int rc;
   const int fed = done ? I->host_ring[I->steps + done - 1] : I->fed;
   if ((rc = write_state(I, I->pos + done, fed, 0, I->steps + done)) != LL_OK) return rc;
   const int d = I->cfg.d_model;
@@ -1221,14 +1236,15 @@ int check_tokens(Instance* I, int k, const char* who) {
 
 int run_decode_steps(Instance* I, int k) {
   if (I->per_length) return run_decode_steps_per_length(I, k);
-  if (I->small && !I->sampled) {
-    enqueue_decode_small(I, I->stream, k);
+  // (either way leaves the state and the next step's input row as the other finds them)
+  const int here = I->small ? std::min(std::max(I->L.sm_keys[I->sampled] - I->pos, 0), k) : 0;
+  if (here > 0 && !I->sampled) {
+    enqueue_decode_small(I, I->stream, here);
     HIPCHK(hipGetLastError());
-    return LL_OK;
   }
-  for (int i = 0; i < k; ++i) {
+  for (int i = I->sampled ? 0 : here; i < k; ++i) {
     if (eager(I)) enqueue_decode(I, I->stream);
-    else HIPCHK(hipGraphLaunch(I->dec_exec, I->stream));
+    else HIPCHK(hipGraphLaunch(i < here ? I->small_exec : I->dec_exec, I->stream));
   }
   if (eager(I)) HIPCHK(hipGetLastError());
   return LL_OK;
@@ -1562,25 +1578,24 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   // nothing is compiled or loaded inside a capture), on state that is reset
   // afterwards.  Token 0 at position 0 / a one-token prompt touch only valid memory.
   if ((rc = write_state(I, 0, 0, 1, 0)) != LL_OK) return bail(rc);
-  enqueue_decode(I, I->stream);
   if (I->small) {
+    enqueue_decode_small(I, I->stream, 0);
     // A wait may run out here too (the GPU is busy, its workgroups not resident together): what that leaves in the hand-offs
     // must not be taken for values of a later step.  Looked at now: the prefills below start from a state of their own.
     int fault = 0;
     if (!hip_or_bail(hipStreamSynchronize(I->stream), "warm-up") ||
         !hip_or_bail(hipMemcpy(&fault, &I->state()->fault, 4, hipMemcpyDeviceToHost), "hipMemcpy(fault)")) return bail(rc);
     I->small_give_up = INT_MAX;
-    if (fault) {
-      I->small = false;
-      if ((rc = write_state(I, 0, 0, 1, 0)) != LL_OK) return bail(rc);
-      enqueue_decode(I, I->stream);
-    }
+    if (fault) I->small = false;
+    if ((rc = write_state(I, 0, 0, 1, 0)) != LL_OK) return bail(rc);
   }
+  enqueue_decode(I, I->stream);
   for (int b : I->pf_buckets) enqueue_prefill(I, I->stream, b);      // (each starts from the staged state: one token)
   if (!hip_or_bail(hipStreamSynchronize(I->stream), "warm-up")) return bail(rc);
   if (!hip_or_bail(hipGetLastError(), "warm-up launch")) return bail(rc);
 
   if (!(cfg->flags & LL_FLAG_EAGER)) {
+    if (I->small && (rc = capture_small(I)) != LL_OK) return bail(rc);
     if ((rc = capture(I, &I->dec_graph, &I->dec_exec, 0)) != LL_OK) return bail(rc);
     I->pf_graph.assign(I->pf_buckets.size(), nullptr);
     I->pf_exec.assign(I->pf_buckets.size(), nullptr);
@@ -2113,7 +2128,7 @@ int ll_dbg_set_spin_limit(int32_t polls) {
   if (!g->small) return 0;
   HIPCHK(hipStreamSynchronize(g->stream));
   g->small_spin_limit = polls;
-  const int rc = recapture_decode(g);          // (the sampled step's graph holds the kernel's arguments)
+  const int rc = capture_small(g);             // (the graph holds the kernel's arguments)
   return rc == LL_OK ? 1 : rc;
 }
 
@@ -2122,16 +2137,18 @@ int ll_dbg_give_up_at(int32_t token) {
   if (!g || !g->small) return 0;
   HIPCHK(hipStreamSynchronize(g->stream));
   g->small_give_up = token < 0 ? INT_MAX : token;
-  const int rc = recapture_decode(g);
+  const int rc = capture_small(g);
   return rc == LL_OK ? 1 : rc;
 }
 
-int ll_dbg_small_plan(const ll_config* cfg, int32_t pos, int32_t steps, int32_t* out2) {
+int ll_dbg_small_plan(const ll_config* cfg, int32_t pos, int32_t steps, int32_t* out4) {
   const char* why = nullptr;
   if (!config_ok(cfg, &why)) return fail(LL_E_BAD_CONFIG, "ll_dbg_small_plan: %s", why);
-  if (!out2 || pos < 0 || steps < 0 || steps > cfg->max_seq) return fail(LL_E_BAD_ARG, "ll_dbg_small_plan: bad argument");
-  out2[0] = small_grid(*cfg);
-  out2[1] = sm_first_pos(pos, steps, cfg->max_seq);
+  if (!out4 || pos < 0 || steps < 0 || steps > cfg->max_seq) return fail(LL_E_BAD_ARG, "ll_dbg_small_plan: bad argument");
+  out4[2] = small_keys(*cfg, false);
+  out4[3] = small_keys(*cfg, true);
+  out4[0] = out4[2] > 0 ? small_grid(*cfg) : 0;
+  out4[1] = sm_first_pos(pos, steps, cfg->max_seq);
   return LL_OK;
 }
 
@@ -2361,11 +2378,7 @@ int ll_dbg_time_decode(int32_t k, float* ms_out) {
   (void)hipEventDestroy(e1);
   if (rc != LL_OK) return rc;
   if ((rc = check_tokens(I, k, "ll_dbg_time_decode")) != LL_OK) {      // what was timed is no step
-    if (I->small) {
-      I->small = false;                                                 // (as after ll_decode_n: its hand-offs are used up)
-      const int again = recapture_decode(I);
-      if (again != LL_OK) return again;
-    }
+    I->small = false;                                                   // (as after ll_decode_n: its hand-offs are used up)
     return rc;
   }
   advance(I, k);

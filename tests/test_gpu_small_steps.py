@@ -97,3 +97,34 @@ def test_other_modes_and_wider_models_keep_the_kernel_chain(torch_cuda):
             assert not s.ll_dbg_set_spin_limit(1)
             s.ll_prefill(wl.make_tokens(5, 64, seed=1))
             assert len(s.ll_decode_n(3)) == 3
+
+
+@pytest.mark.parametrize("sampled", [False, True])
+@pytest.mark.parametrize("give_up", [None, 4])
+def test_steps_on_both_sides_of_the_most_keys(torch_cuda, sampled, give_up):
+    """A call that begins in the one kernel and ends in the chain: the same as step by step, and the chain's tokens; also
+    where the kernel gives up with the chain's steps queued behind it."""
+    cfg = wl.custom_cfg(1, 8, 64, 1408, 23552, 300) if not sampled else wl.custom_cfg(1, 4, 64, 688, 12800, 300)
+    most = b.ll_dbg_small_plan(cfg, 0, 1)["sampled_keys" if sampled else "greedy_keys"]
+    assert 20 < most < 280
+    w = _weights(cfg, 10)
+    prompt = wl.make_tokens(most - 7, cfg["vocab"], seed=11)
+    runs = []
+    for flags in (b.LL_FLAG_MULTIKERNEL, 0):
+        with _session(cfg, w, flags) as s:
+            if sampled:
+                s.ll_set_sampling(temperature=0.8, top_k=50, top_p=0.95, seed=3)
+            if flags == 0 and give_up:
+                assert s.ll_dbg_give_up_at(give_up)
+            many = [s.ll_prefill(prompt)] + list(s.ll_decode_n(12))
+            logits = s.ll_dbg_get_logits()
+            kv = [s.ll_dbg_get_kv(0, which, most + 5) for which in range(2)]
+            assert s.ll_position() == most + 5
+            if not give_up:
+                s.ll_reset()
+                assert [s.ll_prefill(prompt)] + [s.ll_decode_step() for _ in range(12)] == many
+                assert s.ll_dbg_get_logits().tobytes() == logits.tobytes()
+            runs.append((many, logits, kv))
+    assert runs[0][0] == runs[1][0] and max_abs(runs[0][1], runs[1][1]) < 1e-4
+    for a, c in zip(runs[0][2], runs[1][2]):
+        check_kv(c, a, "both sides")
