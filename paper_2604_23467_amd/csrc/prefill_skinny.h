@@ -446,20 +446,21 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
     }
   };
 
-  // First the partial sums of squares of the tokens this wave finishes (2 TB wave, ..), 16 lanes to a token and slots
-  // j, j + 16, .. to lane j, as in sk_ss_issue: K <= 4096 leaves at most 256.  One lane offset and constants, no branch, so
-  // that the wait for them below leaves everything younger in flight.  Then the weight stream's first row block and the
-  // (cached) activations.
+  // The weight stream's first half block, then the partial sums of squares of the tokens this wave finishes (2 TB wave, ..), 16
+  // lanes to a token and slots j, j + 16, .. to lane j, as in sk_ss_issue: K <= 4096 leaves at most 256.  One lane offset and
+  // constants, no branch, so that the wait for them leaves everything younger in flight: the (cached) activations and the
+  // other half block.  (In front of the weights these loads cost a batched step of four layers, us at 16 and 32 rows,
+  // 358.9 and 417.8 against 355.9 and 417.1, and a prompt of 25 tokens 399.7 against 393.4.)
   constexpr int WT = 2 * TB;
   float ssv[16];
   const __amdgpu_buffer_rsrc_t ssr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.ss_in), 0, TB * 16 * a.ss_stride * 4, 0x00027000);
   const int ss_off = ((wave * WT + (g & (WT - 1))) * a.ss_stride + r) * 4;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) ssv[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ssr, ss_off + i * 64, 0, 0));
-  __builtin_amdgcn_sched_barrier(0);
   int u = blockIdx.x;
   h8 fa0[HALF], fa1[HALF];
   load_half(u < units ? u : 0, 0, fa0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) ssv[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ssr, ss_off + i * 64, 0, 0));
   __builtin_amdgcn_sched_barrier(0);
   h8 fb[SKP_KSTEPS][TB];
 #pragma unroll
@@ -470,6 +471,8 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
       if constexpr (FRAG) fb[i][t] = frag.acts(st, t);
       else fb[i][t] = load_h8(a.X + (st < s_end && st * 32 + g * 8 < K ? ((long)(st * TB + t) * 64 + lane) * 8 : a.zeros_off));
     }
+  __builtin_amdgcn_sched_barrier(0);
+  load_half(u < units ? u : 0, HALF, fa1);
   __builtin_amdgcn_sched_barrier(0);
   float ssum = 0.f;
 #pragma unroll
@@ -487,8 +490,6 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_persist_kernel(Skinny
     epos = sk_row_pos(a, p0, etok);
     ecrow = sk_cache_row(a, etok, epos);
   }
-  load_half(u < units ? u : 0, HALF, fa1);
-  __builtin_amdgcn_sched_barrier(0);
   float ss_tok = 0.f;
 #pragma unroll
   for (int t = 0; t < WT; ++t) {
