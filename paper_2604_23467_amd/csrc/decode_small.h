@@ -302,8 +302,8 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
   const SmLayout L = sm_layout(d, a.n_heads, HD, F, a.max_splits);
   const LL_GLOBAL MkLayer* table = as_global(a.layers);
   const int piece = HALF ? lane & 31 : lane;       // this lane's 8 columns of a d-vector
-  // (where an earlier step of the call gave up, this one does at once; the flag from memory, not from a scalar cache)
-  SmWait wait{a.st, a.spin_limit, __builtin_amdgcn_readfirstlane(ld_dev_i(&a.st->fault)) != 0};
+  const int fault0 = ld_dev_i(&a.st->fault);       // from memory, not from a scalar cache
+  SmWait wait{a.st, a.spin_limit, false};
 
   SmRows rows[RQ];
 #pragma unroll
@@ -337,6 +337,7 @@ __global__ __launch_bounds__(SM_THREADS) void decode_small_kernel(SmArgs a) {
   }
   if (owner) { res0 = a.x[2 * gw]; res1 = a.x[2 * gw + 1]; }
   fetch_qkv(first_qkv);
+  wait.dead = __builtin_amdgcn_readfirstlane(fault0) != 0;     // where an earlier step of the call gave up, this one does at once
   auto poll_x = [&](const float* src) {
     const int off[2] = {piece * 32, piece * 32 + 16};
     SmWords v[2];
