@@ -1,5 +1,5 @@
-"""Stochastic selection at the vocabularies where its work split changes: fewer tokens than a wave, than the 256
-candidates one wave finishes, than the 1024 threads (one token each), and just past them (two each)."""
+"""Stochastic selection at the vocabularies where its work split changes: fewer tokens than a wave, about the 256
+candidates that four threads rank each, fewer than the 1024 threads (one token each), and just past them (two each)."""
 import numpy as np
 import pytest
 

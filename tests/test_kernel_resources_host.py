@@ -34,3 +34,13 @@ def test_paged_attention_runs_four_waves_per_simd_without_scratch(metadata):
     assert len(found) == 4                                       # head_dim 64 and 128, 16 and 32 rows
     for name, entry in found.items():
         assert _field(entry, "vgpr_count") <= 128 and _field(entry, "private_segment_fixed_size") == 0, name
+
+
+def test_one_workgroup_per_cu_kernels_keep_to_their_registers(metadata):
+    """Two waves per SIMD at 512 threads a workgroup: 256 vector registers, and no scratch on the paths that wait for one
+    another or stream the weights."""
+    for part, count in (("decode_small_kernel", 4), ("pf_skinny_persist_kernel", 12)):
+        found = {k: v for k, v in metadata.items() if part in k}
+        assert len(found) == count
+        for name, entry in found.items():
+            assert _field(entry, "vgpr_count") <= 256 and _field(entry, "private_segment_fixed_size") == 0, name
