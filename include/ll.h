@@ -102,7 +102,8 @@ enum {
 /* what ll_decode_step() replays, see ll_decode_mode() */
 enum {
   LL_MODE_PERSISTENT_GRAPH = 0,   /* graph of ONE persistent kernel with in-kernel grid barriers */
-  LL_MODE_MULTIKERNEL_GRAPH = 1,  /* graph of one kernel per fused operator */
+  LL_MODE_MULTIKERNEL_GRAPH = 1,  /* graph of one kernel per fused operator; also where a small model's steps run in one
+                                     kernel, which goes over to this graph and falls back to it */
   LL_MODE_EAGER = 2,              /* the multi-kernel chain launched kernel by kernel */
   LL_MODE_PER_LENGTH_GRAPHS = 3   /* the multi-kernel graph, captured once per KV length */
 };
@@ -316,8 +317,8 @@ int ll_dbg_force_next_token(int32_t tok);
  * [0, n_pos), converted to float, laid out [n_pos][d_model] on the host. */
 int ll_dbg_get_kv(int32_t layer, int32_t which, int32_t n_pos, float *host_out);
 
-/* Runs `steps` decode steps eagerly with a hipEvent pair around every kernel
- * launch and returns per-kernel-class mean durations.  The context advances by
+/* Runs `steps` decode steps of the multi-kernel chain, whatever the instance's mode, eagerly with a hipEvent
+ * pair around every kernel launch and returns per-kernel-class mean durations.  The context advances by
  * `steps` tokens.  us_out[LL_KC_COUNT] receives microseconds per launch and
  * launches_out[LL_KC_COUNT] (nullable) the launches per step of each class. */
 enum {
@@ -333,7 +334,7 @@ enum {
 };
 int ll_dbg_profile_decode(int32_t steps, float *us_out, int32_t *launches_out);
 
-/* Mean device time of one launch of kernel class `klass` (LL_KC_QKV ..
+/* Mean device time of one launch of kernel class `klass` of that chain (LL_KC_QKV ..
  * LL_KC_LMHEAD): `reps` passes over all layers, launching only that class back
  * to back (each layer's own weights, so nothing is re-read from cache) between
  * one hipEvent pair on the library's stream.  The position does not advance,

@@ -3,18 +3,20 @@
 // A model whose matrices stream in less time than a kernel boundary costs spends a step on launches: five kernels per
 // layer of 3.8 us each at d_model 256, and 8 us between two graph replays.  Here 32 workgroups stay: they
 // hand the activations over through memory, five times per layer (q/k/v, attention partials, residual, SwiGLU output,
-// residual) and once for the argmax, for as many steps as one call asks for.  Per greedy step, this kernel / the kernel
-// chain: 1 / 2 / 4 / 8 layers of d_model 256, F 688 11.4 / 20.0 / 39.2 / 74.3 us against 31.9 / 50.4 / 87.6 / 164.6;
-// 2 of those layers at 100 / 400 / 800 keys 23.1 / 25.8 / 29.0 against 51.1; 4 layers of 384 / 1024 55 against 91, of
-// 512 / 1408 59 against 93.  Wider models are left to the chain (4 layers of 512 / 2048 were level at 94 us, of 768 / 2048
-// 97 against 98): one XCD does not take their weights in fast enough.
+// residual) and once for the argmax, for as many steps as one call asks for.  Per greedy step, this kernel against the
+// kernel chain: 1 / 2 / 8 layers of d_model 256, F 688 11.1 / 19.5 / 72.1 us against 32.7 / 50.6 / 161.2;
+// 2 of those layers at 100 / 800 / 1900 keys 23.0 / 29.7 / 36.5 against 51.4 / 52.0 / 53.1; 4 layers of 384 / 1024 51.4
+// against 89.3, of 512 / 1408 61.7 against 92.7.  Wider models are left to the chain (4 layers of 512 / 2048 were level at 94
+// us, of 768 / 2048 97 against 98): one XCD does not take their weights in fast enough.  Nor does it a long cache or a large
+// vocabulary, see sm_max_keys.
 //
-// What is left: a phase is one hand-off (store, L2, poll) and a chain of some hundred dependent instructions in one
-// wave, whose latencies (9 cycles a product-add, 16 a lane-crossing sum) set 0.8 us a phase as much as memory does.
+// What is left: a phase (1.8 us, five to a layer) is one hand-off (store, L2, poll) and a chain of some hundred dependent
+// instructions in one wave, whose latencies (9 cycles a product-add, 12 a lane-crossing one, 92 a sum over the wave) weigh as
+// much as memory does; some 250 scalars that find no register sit in lanes of vector registers and are read back one by one.
 //
 // Why one XCD.  Its 32 CUs share an L2, so a value stored by one (the L1s write through) is one L2 hit away from the
-// others: 0.36 us from store to arrival among 32 workgroups, 1.5 us through memory where they sit on different XCDs
-// (across XCDs the same step took 42 us).
+// others: one word between two workgroups 0.28 us from store to arrival, polled as here, against 0.43 where they sit on
+// different XCDs, and there a vector that all workgroups wait for goes through memory once for every XCD.
 // Workgroups are dealt to the XCDs in turn, so every eighth workgroup of the grid takes part and the others leave at
 // once.  Were the dealing ever different, a workgroup elsewhere would read SM_EMPTY from its own L2 until its wait runs
 // out; it cannot read a wrong value.

@@ -14,9 +14,11 @@
 //   order of increasing INDEX and returns the first token whose running sum of e exceeds u * sum_F;
 //   u = (x0 >> 8) * 2^-24, x0 = first word of Philox4x32-10(counter = (draw index, 0, 0, 0), key = seed).
 //
-// No sort is needed: the k-th largest value and the nucleus threshold are found by bisecting the
-// 32 bits of an order-preserving integer image of z, one block-wide count or sum per bit, with
-// every thread holding up to 32 consecutive tokens in registers (vocabularies up to 32768).
+// Nothing is sorted.  Every thread holds up to 32 consecutive tokens in registers (vocabularies up to 32768).  A top-k cut
+// first finds a bound that leaves a few hundred candidates; up to 512 of them are ranked, each compared with all others,
+// and the ranks give the cut and, by one prefix sum, the nucleus.  Without a cut, or with more candidates, the k-th largest
+// value and the nucleus threshold are found by bisecting the 32 bits of an order-preserving integer image of z, two
+// bits to a block-wide count or sum.
 #pragma once
 #include "ll_device.h"
 
@@ -409,9 +411,9 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
   // (1) With a top-k cut of at most one candidate per thread, almost all of the vocabulary can be
   // discarded cheaply first: the k-th largest of the threads' own maxima is a lower bound of the
   // k-th largest key (at least k keys reach it), found with one slot per thread.  Its upper 16 bits (1 % of the
-  // value) are mostly bound enough; where more than one wave's candidates reach them (logits that share an offset much
-  // larger than their spread) the lower bits are found too (32000 logits of 100 +- 0.5 at temperature 0.8, top-k 200, a
-  // step: 95.6 us without, 66.3 with).  What reaches the bound is packed in index order, and up to 512 candidates
+  // value) are mostly bound enough; where more candidates reach them than the split of the ranking holds (logits that share
+  // an offset much larger than their spread) the lower bits are found too (32000 logits of 100 +- 0.5 at temperature 0.8,
+  // top-k 200, a step: 95.6 us without, 66.3 with).  What reaches the bound is packed in index order, and up to 512 candidates
   // are ranked; more go on with one slot per thread.
   bool done = false;
   if (top_k > 0 && top_k <= SMP_THREADS) {
