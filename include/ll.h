@@ -164,7 +164,7 @@ int32_t ll_prefill(const int32_t *tokens, int32_t n);
  * workspace: the same kernels, launched one by one, with everything a short prefill needs besides its
  * inputs and outputs (activations, per-token partial sums, logits, selection candidates, the staged
  * ids) in a static device array of the library (4 MiB, one copy per GPU, held until the process
- * ends) instead of the workspace.  Same arguments, result, state change and errors as ll_prefill;
+ * ends) instead of the workspace, but for the last row's vectors, which go where a decode step's do.  Same arguments, result, state change and errors as ll_prefill;
  * the KV rows, the state block and the token go where ll_prefill puts them, so ll_decode_step()
  * continues from either.  Limits, LL_E_CAPACITY beyond them: n <= 32 tokens, and a model whose
  * short-prompt buffers fit the array (about 336 d_model + 64 ffn_hidden + 4 vocab bytes <= 4 MiB;

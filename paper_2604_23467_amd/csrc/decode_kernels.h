@@ -36,11 +36,19 @@ struct GemvArgs {
   // LM-head epilogue
   float* amax_val;     // [gridDim.x] best logit seen by each workgroup
   int* amax_idx;
-  int x_row_from_prompt;  // 1: input vector is row (st->n_prompt - 1) of a [rows][K] matrix
   // O projection prologue: the input vector is the merge of attn_splits split-K partials per head
   const float* attn_part;
   int attn_splits;
+  const float* res_rows;  // O projection of a prompt's last row: the residual rows [n][N] it reads instead of `out`
 };
+
+// What a GEMV computes for.  The last layer of a prompt is needed for its last row only (behind the cache rows), so a prefill
+// ends in the decode kernels; its roundings are those of the rows in front of it.
+//   GR_STEP   a decode step: everything between two kernels is fp32
+//   GR_SHORT  last row of a prompt of at most 32 tokens: gate/up's operand is fp16(x gain), the norm factor's squares are added
+//             per 16 columns, those sums sixteen strided ones at a time and these as a tree; SwiGLU is rounded to fp16
+//   GR_LONG   last row of a longer prompt: SwiGLU is rounded to fp16
+enum GemvRow { GR_STEP = 0, GR_SHORT = 1, GR_LONG = 2 };
 
 // The input vector is staged in LDS as fp32 in a lane-major layout: for the
 // 512-element chunk c, lane l owns elements c*512 + l*8 .. +7, stored as two
@@ -58,7 +66,7 @@ struct GemvArgs {
 // Threads per workgroup: the O projection, whose every workgroup merges all of the attention partials
 // while it stages them, runs workgroups of 8 waves (half as many stagings for the same row pairs)
 #define GEMV_WG(MODE) ((MODE) == GM_ORES ? 2 * LL_WG : LL_WG)
-template <int MODE, int U>
+template <int MODE, int U, int ROW = GR_STEP>
 __global__ __launch_bounds__(GEMV_WG(MODE)) void gemv_kernel(GemvArgs a) {
   extern __shared__ float lds[];
   constexpr int WG = GEMV_WG(MODE);
@@ -118,7 +126,8 @@ __global__ __launch_bounds__(GEMV_WG(MODE)) void gemv_kernel(GemvArgs a) {
   const int gw = blockIdx.x * (WG / 64) + wave, GW = gridDim.x * (WG / 64);
 
   const float* xin = a.xin;
-  if (MODE == GM_LMHEAD && a.x_row_from_prompt) xin += (size_t)(a.st->n_prompt - 1) * K;
+  const float* res = a.out;                            // residual stream that the O and down projections add to
+  if (MODE == GM_ORES && ROW != GR_STEP) res = a.res_rows + (size_t)(a.st->n_prompt - 1) * a.N;
 
   // Staging of the input vector, four float4 per thread and pass, all of a pass's loads issued before
   // any is used (one L2 round trip, not four).  For the O projection in two separate steps (loads;
@@ -233,10 +242,26 @@ __global__ __launch_bounds__(GEMV_WG(MODE)) void gemv_kernel(GemvArgs a) {
         x0 = *reinterpret_cast<const f4*>(xp);
         x1 = *reinterpret_cast<const f4*>(xp + 256);
         const h8 gv = *reinterpret_cast<const h8*>(gl + c * 512 + lane * 8);
-        ss += x0[0] * x0[0] + x0[1] * x0[1] + x0[2] * x0[2] + x0[3] * x0[3] +
-              x1[0] * x1[0] + x1[1] * x1[1] + x1[2] * x1[2] + x1[3] * x1[3];
+        if constexpr (ROW == GR_SHORT) {
+          float bs = 0.f;                                       // two lanes hold 16 columns: their sum takes the place of the gains
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { x0[e] *= (float)gv[e]; x1[e] *= (float)gv[4 + e]; }
+          for (int e = 0; e < 4; ++e) bs += x0[e] * x0[e];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bs += x1[e] * x1[e];
+          bs += dpp_mov<0xB1>(bs);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            x0[e] = (float)(half_t)(x0[e] * (float)gv[e]);
+            x1[e] = (float)(half_t)(x1[e] * (float)gv[4 + e]);
+          }
+          asm volatile("" ::: "memory");                        // (read as halves above)
+          if (!(lane & 1)) reinterpret_cast<float*>(gl + c * 512)[lane >> 1] = bs;
+        } else {
+          ss += x0[0] * x0[0] + x0[1] * x0[1] + x0[2] * x0[2] + x0[3] * x0[3] +
+                x1[0] * x1[0] + x1[1] * x1[1] + x1[2] * x1[2] + x1[3] * x1[3];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { x0[e] *= (float)gv[e]; x1[e] *= (float)gv[4 + e]; }
+        }
       }
       *reinterpret_cast<f4*>(xp) = x0;                          // also the zero padding beyond K and up to nchp chunks
       *reinterpret_cast<f4*>(xp + 256) = x1;
@@ -273,13 +298,23 @@ __global__ __launch_bounds__(GEMV_WG(MODE)) void gemv_kernel(GemvArgs a) {
       }
     }
   }
-  if (NORM) {
+  if (NORM && ROW != GR_SHORT) {
     ss = wave_sum(ss);
     if (lane == 0) red[wave] = ss;
   }
   __syncthreads();
   float inv = 1.f;
-  if (NORM) inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)K + a.eps);
+  if constexpr (NORM && ROW == GR_SHORT) {
+    const half_t* gl = reinterpret_cast<const half_t*>(red + 16);
+    auto block_sum = [&](int i) { return i * 16 < K ? reinterpret_cast<const float*>(gl + (i >> 5) * 512)[i & 31] : 0.f; };
+    const int j = lane & 15;
+    for (int i = j + 256; i * 16 < K; i += 16) ss += block_sum(i);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) ss += block_sum(j + 16 * i);
+    inv = 1.0f / sqrtf(group_sum<16>(ss) / (float)K + a.eps);
+  } else if (NORM) {
+    inv = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)K + a.eps);
+  }
 
   float best_v = -INFINITY;
   int best_i = 0x7fffffff;
@@ -293,7 +328,7 @@ __global__ __launch_bounds__(GEMV_WG(MODE)) void gemv_kernel(GemvArgs a) {
     float pre0 = 0.f, pre1 = 0.f;
     float2 pcs = make_float2(1.f, 0.f);
     if (MODE == GM_ORES || MODE == GM_DOWN) {
-      if (lane == 0) { pre0 = *as_global(a.out + rowA); pre1 = *as_global(a.out + rowB); }
+      if (lane == 0) { pre0 = *as_global(res + rowA); pre1 = *as_global(res + rowB); }
     } else if (MODE == GM_QKV) {
       if (sec < 2) {
         const int head = rowA / a.head_dim, j = rowA - head * a.head_dim;
@@ -340,7 +375,8 @@ __global__ __launch_bounds__(GEMV_WG(MODE)) void gemv_kernel(GemvArgs a) {
         vr[e + 1] = (half_t)accB;
       }
     } else if (MODE == GM_GATEUP) {
-      if (lane == 0) a.out[p] = accA / (1.0f + expf(-accA)) * accB;
+      const float m = accA / (1.0f + expf(-accA)) * accB;
+      if (lane == 0) a.out[p] = ROW == GR_STEP ? m : (float)(half_t)sk_fp32(m);
     } else if (MODE == GM_ORES || MODE == GM_DOWN) {
       if (lane == 0) {
         a.out[rowA] = pre0 + accA;
@@ -505,9 +541,12 @@ __global__ __launch_bounds__(LL_WG) void embed_kernel(const half_t* __restrict__
 // stream, which saves this kernel a cross-workgroup hand-off (stores -> counter
 // -> reload: about 5 us of pure latency).
 
-template <int HD, int NTHR = ATTN_THREADS>
+//
+// QT = float: the query of a decode step, behind pos cached keys.  QT = half_t: the last of the n_prompt rotated queries of
+// a prompt chunk, [row][d], whose keys are cached behind the pos earlier ones.
+template <int HD, int NTHR = ATTN_THREADS, typename QT = float>
 __global__ __launch_bounds__(NTHR) void attn_decode_kernel(
-    const float* __restrict__ q, const half_t* __restrict__ kc, const half_t* __restrict__ vc,
+    const QT* __restrict__ q, const half_t* __restrict__ kc, const half_t* __restrict__ vc,
     const DevState* __restrict__ st, float* __restrict__ part, int max_seq) {
   constexpr int LPR = HD / 8;      // lanes per key row
   constexpr int GPW = 64 / LPR;    // lane groups per wave
@@ -519,13 +558,20 @@ __global__ __launch_bounds__(NTHR) void attn_decode_kernel(
   const int h = blockIdx.x, s = blockIdx.y, S = gridDim.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int gi = lane / LPR, li = lane % LPR;
-  const int n_keys = st->pos + 1;
+  constexpr bool PROMPT = sizeof(QT) == 2;
+  const int n_keys = st->pos + (PROMPT ? st->n_prompt : 1);
   const float scale = 1.0f / sqrtf((float)HD);
 
   // The query is used unscaled (the score takes the factor): nothing is computed from it before the
   // first keys are requested, so its L2 round trip runs underneath theirs instead of in front of it.
-  const f4 q0 = *reinterpret_cast<const f4*>(q + h * HD + li * 8);
-  const f4 q1 = *reinterpret_cast<const f4*>(q + h * HD + li * 8 + 4);
+  f4 q0, q1;
+  h8 qh;
+  if constexpr (PROMPT) {
+    qh = load_h8(q + ((size_t)(st->n_prompt - 1) * gridDim.x + h) * HD + li * 8);
+  } else {
+    q0 = *reinterpret_cast<const f4*>(q + h * HD + li * 8);
+    q1 = *reinterpret_cast<const f4*>(q + h * HD + li * 8 + 4);
+  }
   const half_t* kh = kc + (size_t)h * max_seq * HD + li * 8;
   const half_t* vh = vc + (size_t)h * max_seq * HD + li * 8;
 
@@ -543,6 +589,10 @@ __global__ __launch_bounds__(NTHR) void attn_decode_kernel(
       vv[j] = load_stream(vh + (size_t)u * HD);
     }
     __builtin_amdgcn_sched_barrier(0);     // all 16 requests out before the first use: one round trip, not several
+    if constexpr (PROMPT) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { q0[e] = (float)qh[e]; q1[e] = (float)qh[4 + e]; }
+    }
     // One online-softmax step per batch, not per key: the batch's scores, one new maximum, one correction
     // of the running state, one exponential per key.  No branch around any of it: inside one the compiler
     // sinks a value row's load to where it is used and waits for it there, a second round trip behind the first.

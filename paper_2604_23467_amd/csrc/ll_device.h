@@ -136,6 +136,13 @@ __device__ __forceinline__ h8 load_h8(const half_t* p) {
   return *as_global(reinterpret_cast<const h8*>(p));
 }
 
+// A result that is to be rounded to fp32 before it is rounded to fp16: without this a product or sum and its conversion
+// become one instruction (v_fma_mix) that rounds once
+__device__ __forceinline__ float sk_fp32(float v) {
+  asm("" : "+v"(v));
+  return v;
+}
+
 __device__ __forceinline__ float dot8(h8 w, f4 x0, f4 x1, float acc) {
   acc += (float)w[0] * x0[0];
   acc += (float)w[1] * x0[1];

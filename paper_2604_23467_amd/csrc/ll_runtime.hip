@@ -520,8 +520,7 @@ struct Instance {
   PfBuffers pf{};               // the workspace's set of these buffers
   int device = 0;               // GPU the instance lives on
   char* static_scratch = nullptr;   // that GPU's copy of the library's static scratch array
-  const float* last_logits = nullptr;   // where the most recent step left its logits / residual rows
-  const float* last_rows = nullptr;
+  const float* last_logits = nullptr;   // where the most recent step left its logits
   hipStream_t stream = nullptr;
   bool own_stream = false;
   hipGraph_t dec_graph = nullptr;
@@ -534,7 +533,6 @@ struct Instance {
   std::vector<hipGraphExec_t> pf_exec;
   hipGraph_t pf_body_graph = nullptr;       // largest bucket without LM head and sampling: all but the last chunk
   hipGraphExec_t pf_body_exec = nullptr;    // of a prompt longer than that bucket
-  int last_chunk_rows = 0;                  // rows of the most recent prefill's last chunk
   int* host_ring = nullptr;      // pinned, device-visible; kernels write generated ids here
   int* dev_ring = nullptr;       // device address of host_ring
   int ring_size = 0;
@@ -542,7 +540,6 @@ struct Instance {
   int* dev_stage = nullptr;      // device address of host_stage
   // host mirror of the device state (never read back from the GPU on the hot path)
   int pos = 0, steps = 0;
-  bool last_was_prefill = false;
   // profiling hook: when set, every decode launch is bracketed by events
   std::vector<hipEvent_t>* prof_events = nullptr;
   std::vector<int>* prof_class = nullptr;
@@ -612,11 +609,60 @@ struct ProfScope {
   }
 };
 
-template <int MODE>
+template <int MODE, int ROW = GR_STEP>
 void launch_gemv(const GemvArgs& a, int pairs, int grid_override, hipStream_t s) {
   const int grid = grid_override > 0 ? grid_override : gemv_grid(pairs, GEMV_WG(MODE));
-  hipLaunchKernelGGL((gemv_kernel<MODE, kGemvU>), dim3(grid), dim3(GEMV_WG(MODE)),
+  hipLaunchKernelGGL((gemv_kernel<MODE, kGemvU, ROW>), dim3(grid), dim3(GEMV_WG(MODE)),
                      gemv_lds_bytes(a.K, MODE == GM_QKV || MODE == GM_GATEUP || MODE == GM_LMHEAD), s, a);
+}
+
+// Attention, O, gate/up and down of layer l for one row, the decode step's (q: float) or a prompt's last one (q: half_t, and
+// rows: the prompt's residual rows); x holds the row's residual stream afterwards
+template <typename QT>
+void launch_attn_row(Instance* I, hipStream_t s, const QT* q, int l) {
+  const ll_config& c = I->cfg;
+  dim3 grid(c.n_heads, I->L.attn_splits);
+  auto go = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, q, I->kcache(l), I->vcache(l), I->state(),
+                       I->at<float>(I->L.attn_part), c.max_seq);
+  };
+  if (c.head_dim == 128) I->L.attn_threads == 512 ? go(attn_decode_kernel<128, 512, QT>, 512)
+                                                  : go(attn_decode_kernel<128, ATTN_THREADS, QT>, ATTN_THREADS);
+  else I->L.attn_threads == 512 ? go(attn_decode_kernel<64, 512, QT>, 512)
+                                : go(attn_decode_kernel<64, ATTN_THREADS, QT>, ATTN_THREADS);
+}
+template <int ROW>
+void launch_o_row(Instance* I, hipStream_t s, int l, const float* rows = nullptr) {
+  const ll_config& c = I->cfg;
+  GemvArgs a{};
+  a.w0 = (const half_t*)I->layers[l].wo; a.xin = I->at<float>(I->L.o); a.out = I->at<float>(I->L.x);
+  a.N = c.d_model; a.K = c.d_model;
+  a.attn_part = I->at<float>(I->L.attn_part);
+  a.attn_splits = I->L.attn_splits; a.head_dim = c.head_dim;
+  a.res_rows = rows; a.st = I->state();
+  launch_gemv<GM_ORES, ROW == GR_STEP ? GR_STEP : GR_LONG>(a, c.d_model / 2, 0, s);
+}
+template <int ROW>
+void launch_gateup_row(Instance* I, hipStream_t s, int l) {
+  const ll_config& c = I->cfg;
+  const ll_layer_weights& W = I->layers[l];
+  GemvArgs a{};
+  a.w0 = (const half_t*)W.w_gate; a.w1 = (const half_t*)W.w_up;
+  a.xin = I->at<float>(I->L.x); a.gain = (const half_t*)W.ffn_norm; a.out = I->at<float>(I->L.m);
+  a.N = c.ffn_hidden; a.K = c.d_model; a.eps = c.rms_eps;
+  launch_gemv<GM_GATEUP, ROW>(a, c.ffn_hidden, 0, s);
+}
+void launch_down_row(Instance* I, hipStream_t s, int l) {
+  const int d = I->cfg.d_model, F = I->cfg.ffn_hidden;
+  GemvArgs a{};
+  a.w0 = (const half_t*)I->layers[l].w_down; a.xin = I->at<float>(I->L.m); a.out = I->at<float>(I->L.x); a.N = d; a.K = F;
+  const int nch = (F + 511) / 512, nseg = (nch + 7) / 8;
+  const size_t lds = ((size_t)(nch + 1) * 512 + 4 * 4 * 2) * sizeof(float);
+  const int grid = (d / 2 + 3) / 4;
+  if (nseg == 2) hipLaunchKernelGGL(gemv_ksplit_kernel<2>, dim3(grid), dim3(512), lds, s, a);
+  else if (nseg == 3) hipLaunchKernelGGL(gemv_ksplit_kernel<3>, dim3(grid), dim3(768), lds, s, a);
+  else if (nseg == 4) hipLaunchKernelGGL(gemv_ksplit_kernel<4>, dim3(grid), dim3(1024), lds, s, a);
+  else launch_gemv<GM_DOWN>(a, d / 2, 0, s);   // short rows, or too long to split over one workgroup
 }
 
 // token selection + state advance + the next step's input row
@@ -629,14 +675,14 @@ void enqueue_select(Instance* I, hipStream_t s, const float* amax_val, const int
                      I->at<float>(I->L.x_keep), c.d_model);
 }
 
-// final RMSNorm + LM head + argmax + state advance, shared by decode and prefill
-void enqueue_head(Instance* I, hipStream_t s, const PfBuffers& B, const float* xin, int from_prompt_row, int prefill) {
+// final RMSNorm + LM head + argmax + state advance on the row in x, shared by decode and prefill
+void enqueue_head(Instance* I, hipStream_t s, const PfBuffers& B, int prefill) {
   const ll_config& c = I->cfg;
   if (I->runs(LL_KC_LMHEAD)) {
     ProfScope ps(I, s, LL_KC_LMHEAD);
     GemvArgs a{};
     a.w0 = (const half_t*)I->w.lm_head;
-    a.xin = xin;
+    a.xin = I->at<float>(I->L.x);
     a.gain = (const half_t*)I->w.final_norm;
     a.out = B.logits;
     a.N = c.vocab;
@@ -645,7 +691,6 @@ void enqueue_head(Instance* I, hipStream_t s, const PfBuffers& B, const float* x
     a.st = I->state();
     a.amax_val = B.amax_val;
     a.amax_idx = B.amax_idx;
-    a.x_row_from_prompt = from_prompt_row;
     launch_gemv<GM_LMHEAD>(a, (c.vocab + 1) / 2, I->L.lm_wgs, s);
   }
   if (I->runs(LL_KC_SAMPLE)) {
@@ -656,11 +701,9 @@ void enqueue_head(Instance* I, hipStream_t s, const PfBuffers& B, const float* x
 
 void enqueue_decode_multi(Instance* I, hipStream_t s) {
   const ll_config& c = I->cfg;
-  const int d = c.d_model, F = c.ffn_hidden;
+  const int d = c.d_model;
   float* x = I->at<float>(I->L.x);
   float* q = I->at<float>(I->L.q);
-  float* o = I->at<float>(I->L.o);
-  float* m = I->at<float>(I->L.m);
   // x already holds the embedding row of the token to feed: the selection kernel of the previous
   // step (or of the prefill) gathered it, and ll_dbg_force_next_token refreshes it
   if (I->use_mega && I->runs(LL_KC_EMBED)) {      // (the timing hooks of a persistent-kernel instance: its selection gathers nothing)
@@ -700,51 +743,23 @@ void enqueue_decode_multi(Instance* I, hipStream_t s) {
     } else {
     if (I->runs(LL_KC_ATTN)) {
       ProfScope ps(I, s, LL_KC_ATTN);
-      dim3 grid(c.n_heads, I->L.attn_splits);
-      if (c.head_dim == 128 && I->L.attn_threads == 512)
-        hipLaunchKernelGGL((attn_decode_kernel<128, 512>), grid, dim3(512), 0, s, q, I->kcache(l),
-                           I->vcache(l), I->state(), I->at<float>(I->L.attn_part), c.max_seq);
-      else if (c.head_dim == 128)
-        hipLaunchKernelGGL(attn_decode_kernel<128>, grid, dim3(ATTN_THREADS), 0, s, q, I->kcache(l),
-                           I->vcache(l), I->state(), I->at<float>(I->L.attn_part), c.max_seq);
-      else if (I->L.attn_threads == 512)
-        hipLaunchKernelGGL((attn_decode_kernel<64, 512>), grid, dim3(512), 0, s, q, I->kcache(l),
-                           I->vcache(l), I->state(), I->at<float>(I->L.attn_part), c.max_seq);
-      else
-        hipLaunchKernelGGL(attn_decode_kernel<64>, grid, dim3(ATTN_THREADS), 0, s, q, I->kcache(l),
-                           I->vcache(l), I->state(), I->at<float>(I->L.attn_part), c.max_seq);
+      launch_attn_row(I, s, (const float*)q, l);
     }
     if (I->runs(LL_KC_OPROJ)) {
       ProfScope ps(I, s, LL_KC_OPROJ);
-      GemvArgs a{};
-      a.w0 = (const half_t*)W.wo; a.xin = o; a.out = x; a.N = d; a.K = d;
-      a.attn_part = I->at<float>(I->L.attn_part);
-      a.attn_splits = I->L.attn_splits; a.head_dim = c.head_dim;
-      launch_gemv<GM_ORES>(a, d / 2, 0, s);
+      launch_o_row<GR_STEP>(I, s, l);
     }
     }
     if (I->runs(LL_KC_GATEUP)) {
       ProfScope ps(I, s, LL_KC_GATEUP);
-      GemvArgs a{};
-      a.w0 = (const half_t*)W.w_gate; a.w1 = (const half_t*)W.w_up;
-      a.xin = x; a.gain = (const half_t*)W.ffn_norm; a.out = m;
-      a.N = F; a.K = d; a.eps = c.rms_eps;
-      launch_gemv<GM_GATEUP>(a, F, 0, s);
+      launch_gateup_row<GR_STEP>(I, s, l);
     }
     if (I->runs(LL_KC_DOWN)) {
       ProfScope ps(I, s, LL_KC_DOWN);
-      GemvArgs a{};
-      a.w0 = (const half_t*)W.w_down; a.xin = m; a.out = x; a.N = d; a.K = F;
-      const int nch = (F + 511) / 512, nseg = (nch + 7) / 8;
-      const size_t lds = ((size_t)(nch + 1) * 512 + 4 * 4 * 2) * sizeof(float);
-      const int grid = (d / 2 + 3) / 4;
-      if (nseg == 2) hipLaunchKernelGGL(gemv_ksplit_kernel<2>, dim3(grid), dim3(512), lds, s, a);
-      else if (nseg == 3) hipLaunchKernelGGL(gemv_ksplit_kernel<3>, dim3(grid), dim3(768), lds, s, a);
-      else if (nseg == 4) hipLaunchKernelGGL(gemv_ksplit_kernel<4>, dim3(grid), dim3(1024), lds, s, a);
-      else launch_gemv<GM_DOWN>(a, d / 2, 0, s);   // short rows, or too long to split over one workgroup
+      launch_down_row(I, s, l);
     }
   }
-  enqueue_head(I, s, I->pf, x, 0, 0);
+  enqueue_head(I, s, I->pf, 0);
 }
 
 // Can the whole step run as one persistent kernel on this device / shape?
@@ -910,6 +925,21 @@ void enqueue_stage(Instance* I, hipStream_t s, const PfBuffers& B, int Mb, bool 
                      Mb, clear_zeros ? (int*)B.zeros : nullptr);
 }
 
+// Last layer of a prefill behind its Q/K/V projection, head included: of all its rows the first token needs only the last one
+// (the others have left their keys and values by then), and one row is a decode step's work, bound by the weights' way from
+// HBM.  The decode step's buffers take it; X holds the prompt's residual rows in front of the layer.  First token of four
+// layers of the 7B shape, all rows -> this, us: 25 tokens 418 -> 406, 50 481 -> 462, 100 581 -> 543, 250 788 -> 712,
+// 350 931 -> 830; 32 layers, 10 tokens 2653 -> 2656, 500 tokens 8390 -> 8257.
+template <int ROW>
+void enqueue_last_row(Instance* I, hipStream_t s, const PfBuffers& B) {
+  const int l = I->cfg.n_layers - 1;
+  launch_attn_row(I, s, (const half_t*)B.Q, l);
+  launch_o_row<ROW>(I, s, l, B.X);
+  launch_gateup_row<ROW>(I, s, l);
+  launch_down_row(I, s, l);
+  enqueue_head(I, s, B, 1);
+}
+
 // Prompts of at most 32 tokens: five kernels per layer, every projection streams its weights
 // once and finishes its own epilogue; the norms ride on the projections around them.
 void enqueue_prefill_skinny(Instance* I, hipStream_t s, const PfBuffers& B, int Mb, bool with_head) {
@@ -932,6 +962,7 @@ void enqueue_prefill_skinny(Instance* I, hipStream_t s, const PfBuffers& B, int 
     a.ss_in = ss_attn; a.ss_parts = l == 0 ? 1 : parts;     // the embedding gather leaves whole sums in slot 0
     a.Wf = I->wfrag(l, I->L.wf_qkv);
     launch_skinny<SK_QKV>(s, B, a, Mb);
+    if (l + 1 == c.n_layers) break;
     dim3 agrid(c.n_heads, 1);
     if (c.head_dim == 128)
       hipLaunchKernelGGL((pf_attn_kernel<128, 1>), agrid, dim3(128), PF_ATTN_LDS_BYTES(128, 1), s, Qh, I->kcache(l),
@@ -948,12 +979,12 @@ void enqueue_prefill_skinny(Instance* I, hipStream_t s, const PfBuffers& B, int 
     a.Wf = I->wfrag(l, I->L.wf_gu);
     launch_skinny<SK_GATEUP>(s, B, a, Mb);
     a.X = Hm; a.W[0] = (const half_t*)W.w_down; a.W[1] = nullptr; a.N = d; a.K = F; a.Xres = X;
-    a.gain_next = l + 1 < c.n_layers ? (const half_t*)I->layers[l + 1].attn_norm : nullptr;
+    a.gain_next = (const half_t*)I->layers[l + 1].attn_norm;
     a.Xh_next = Xn; a.ss_out = ss_attn;
     a.Wf = I->wfrag(l, I->L.wf_down);
     launch_skinny<SK_RES>(s, B, a, Mb);
   }
-  if (with_head) enqueue_head(I, s, B, X, 1, 1);
+  if (with_head) enqueue_last_row<GR_SHORT>(I, s, B);
 }
 
 // Prefill attention of layer l for a bucket of Mb >= 64 rows: key groups that share a query block (a chunk of a long
@@ -999,6 +1030,7 @@ void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb
     a.A = B.Xn; a.Wf = I->wfrag(l, I->L.wf_qkv); a.N = d; a.K = d;
     a.Q = B.Q; a.kc = I->kcache(l); a.vc = I->vcache(l); a.rope = I->at<float2>(I->L.rope);
     launch_tile<SK_QKV>(s, a, Mb);
+    if (l + 1 == c.n_layers) break;
     launch_attn(I, s, B, l, Mb, tb);
     a.C = B.part; a.slice_floats = (size_t)Mb * d;
     a.A = B.O; a.Wf = I->wfrag(l, I->L.wf_o);
@@ -1011,11 +1043,7 @@ void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb
     launch_tile<SK_RES>(s, a, Mb);
     part = B.part;
   }
-  if (with_head) {             // (a chunk that is not the prompt's last needs nothing of X any more)
-    hipLaunchKernelGGL(pf_fold_kernel, dim3(Mb, (d + LL_WG * 4 - 1) / (LL_WG * 4)), dim3(LL_WG), 0, s, B.X,
-                       I->state(), part, slices(ks_down), d);
-    enqueue_head(I, s, B, B.X, 1, 1);
-  }
+  if (with_head) enqueue_last_row<GR_LONG>(I, s, B);    // (a chunk that is not the prompt's last is done with its cache rows)
 }
 
 void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) {
@@ -1040,6 +1068,7 @@ void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) 
     hipLaunchKernelGGL(pf_rope_kv_kernel, dim3(Mb, (d / 8 + LL_WG - 1) / LL_WG), dim3(LL_WG), 0, s, P, qkv,
                        I->at<float2>(I->L.rope), I->state(), Qh, I->kcache(l), I->vcache(l), d,
                        c.head_dim, c.max_seq);
+    if (l + 1 == c.n_layers) break;
     launch_attn(I, s, B, l, Mb, 0);
     res = launch_gemm(I, s, B, Oh, W.wo, nullptr, nullptr, 1, d, d, d, Mb);
     res_part = P;
@@ -1050,10 +1079,7 @@ void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) 
                        s, P, gu, I->state(), Hm, F);
     res = launch_gemm(I, s, B, Hm, W.w_down, nullptr, nullptr, 1, d, d, F, Mb);
   }
-  if (with_head && res_part)    // (a chunk that is not the prompt's last needs nothing of X any more)
-    hipLaunchKernelGGL(pf_fold_kernel, dim3(Mb, (d + LL_WG * 4 - 1) / (LL_WG * 4)), dim3(LL_WG), 0, s, X,
-                       I->state(), P, res, d);
-  if (with_head) enqueue_head(I, s, B, X, 1, 1);
+  if (with_head) enqueue_last_row<GR_LONG>(I, s, B);
 }
 
 int capture_on(Instance* I, hipStream_t cs, hipGraph_t* graph, hipGraphExec_t* exec, int prefill_bucket,
@@ -1187,7 +1213,6 @@ void advance(Instance* I, int k) {
   I->pos += k;
   I->steps += k;
   I->fed = I->host_ring[I->steps - 1];
-  I->last_was_prefill = false;
   I->last_logits = I->pf.logits;
 }
 
@@ -1726,14 +1751,11 @@ int32_t ll_prefill(const int32_t* tokens, int32_t n) {
       HIPCHK(hipGraphLaunch(I->pf_exec[bi], I->stream));
     }
     HIPCHK(hipStreamSynchronize(I->stream));       // the staging buffer is reused by the next chunk
-    I->last_chunk_rows = m;
     p0 += m;
   }
   I->pos = n;
   I->steps = 1;
-  I->last_was_prefill = true;
   I->last_logits = I->pf.logits;
-  I->last_rows = I->pf.X;
   return I->fed = I->host_ring[0];
 }
 
@@ -1763,12 +1785,9 @@ int32_t ll_prefill_static(const int32_t* tokens, int32_t n) {
   enqueue_prefill_skinny(I, I->stream, B, n <= 16 ? 16 : 32, true);     // launched kernel by kernel: no graph holds these addresses
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(I->stream));
-  I->last_chunk_rows = n;
   I->pos = n;
   I->steps = 1;
-  I->last_was_prefill = true;
   I->last_logits = B.logits;
-  I->last_rows = B.X;
   return I->fed = I->host_ring[0];
 }
 
@@ -2172,9 +2191,7 @@ int ll_dbg_get_hidden(float* host_out) {
   if (!host_out) return fail(LL_E_BAD_ARG, "ll_dbg_get_hidden: null output");
   if (g->pos == 0) return fail(LL_E_STATE, "ll_dbg_get_hidden: no step has run");
   HIPCHK(hipStreamSynchronize(g->stream));
-  const float* src = g->last_was_prefill
-                         ? g->last_rows + (size_t)(g->last_chunk_rows - 1) * g->cfg.d_model
-                         : g->at<float>(g->use_mega ? g->L.x : g->L.x_keep);
+  const float* src = g->at<float>(g->use_mega ? g->L.x : g->L.x_keep);
   HIPCHK(hipMemcpy(host_out, src, (size_t)g->cfg.d_model * 4, hipMemcpyDeviceToHost));
   return LL_OK;
 }

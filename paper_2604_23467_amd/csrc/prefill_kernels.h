@@ -108,16 +108,6 @@ __global__ __launch_bounds__(PF_NORM_THREADS) void pf_rmsnorm_kernel(float* __re
   }
 }
 
-// X[r] += the slices of the last residual GEMM (nothing follows it that could).
-// grid = (rows, ceil(d / 1024))
-__global__ __launch_bounds__(LL_WG) void pf_fold_kernel(float* __restrict__ X, const DevState* __restrict__ st,
-                                                        const float* __restrict__ part, SliceMap map, int d) {
-  const int r = blockIdx.x, i = (blockIdx.y * LL_WG + threadIdx.x) * 4;
-  if (r >= st->n_prompt || i >= d) return;
-  float* x = X + (size_t)r * d + i;
-  *reinterpret_cast<f4*>(x) = *reinterpret_cast<const f4*>(x) + pf_slice_sum(part + (size_t)r * d + i, slice_count(map, i), map.slice_floats);
-}
-
 // RoPE on the q and k thirds of the QKV projection (fp32, slices of [Mb][3d], summed here) at
 // position p0 + r, then q -> fp16 Q[r], k/v -> the KV cache rows of position p0 + r.  Four rotation
 // pairs per thread with 16-byte loads, every load of a thread issued before the first use

@@ -124,13 +124,6 @@ __device__ __forceinline__ void sk_ss_finish(const SkSsLoads& L, int K, float ep
   if (tid < TB * 256 && (tid & 15) == 0) s_scale[tid >> 4] = 1.0f / sqrtf(s / (float)K + eps);
 }
 
-// A result that is to be rounded to fp32 before it is rounded to fp16: without this a product or sum and its conversion
-// become one instruction (v_fma_mix) that rounds once
-__device__ __forceinline__ float sk_fp32(float v) {
-  asm("" : "+v"(v));
-  return v;
-}
-
 // number of 16-row blocks the kernel's grid has to cover
 __host__ __device__ inline int skinny_units(int mode, int N) {
   return mode == SK_QKV ? 3 * (N / 16) : mode == SK_GATEUP ? N / 8 : N / 16;

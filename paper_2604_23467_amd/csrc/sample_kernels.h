@@ -500,8 +500,8 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
 //   prefill = 1: pos += n_prompt (rows of the last prompt chunk), steps := 1, ring[0] := token (draw index 0)
 //   prefill = 0: pos += 1, ring[steps] := token, steps += 1   (draw index = steps before the step)
 // It also gathers the selected token's embedding row into x_next (when given), the input of the next
-// decode step, which therefore needs no gather kernel of its own (what x_next held, the step's final
-// residual stream, is kept in x_keep for the read-back hook); and it reports token -1 to the host
+// decode step, which therefore needs no gather kernel of its own (what x_next held, the final residual
+// stream of the step or of the prompt's last row, is kept in x_keep for the read-back hook); and it reports token -1 to the host
 // when a kernel of the step raised DevState::fault (the device state still advances with a valid id).
 __global__ __launch_bounds__(SMP_THREADS) void sample_kernel(const float* __restrict__ pval,
                                                              const int* __restrict__ pidx, int nparts,
@@ -553,10 +553,8 @@ __global__ __launch_bounds__(SMP_THREADS) void sample_kernel(const float* __rest
   if (x_next) {
     for (int i = tid * 8; i < d; i += SMP_THREADS * 8) {
       const h8 e = load_h8(emb + (size_t)tok * d + i);
-      if (!prefill) {
-        *reinterpret_cast<f4*>(x_keep + i) = *reinterpret_cast<const f4*>(x_next + i);
-        *reinterpret_cast<f4*>(x_keep + i + 4) = *reinterpret_cast<const f4*>(x_next + i + 4);
-      }
+      *reinterpret_cast<f4*>(x_keep + i) = *reinterpret_cast<const f4*>(x_next + i);
+      *reinterpret_cast<f4*>(x_keep + i + 4) = *reinterpret_cast<const f4*>(x_next + i + 4);
       *reinterpret_cast<f4*>(x_next + i) = f4{(float)e[0], (float)e[1], (float)e[2], (float)e[3]};
       *reinterpret_cast<f4*>(x_next + i + 4) = f4{(float)e[4], (float)e[5], (float)e[6], (float)e[7]};
     }
