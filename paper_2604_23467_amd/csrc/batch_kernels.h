@@ -238,12 +238,14 @@ __global__ __launch_bounds__(LL_WG) void bt_scatter_kernel(const half_t* __restr
 }
 
 // Slots' state (by workgroup 0) and one page-table row per workgroup, from the host's pinned mirrors: one launch where
-// two copies in front of the next kernel cost 15 us more.  grid = rows, row first + blockIdx.x
+// two copies in front of the next kernel cost 15 us more.  grid = rows, row first + blockIdx.x.  st: optionally where slot
+// `first` finds its next token, that of a prefill still in the queue
 __global__ __launch_bounds__(LL_WG) void bt_push_kernel(const int* __restrict__ h_state, int* __restrict__ state,
                                                         const int* __restrict__ h_table, int* __restrict__ table,
-                                                        int pt_stride, int first) {
+                                                        int pt_stride, int first, const DevState* __restrict__ st) {
   if (blockIdx.x == 0)
-    for (int i = threadIdx.x; i < (int)(sizeof(BatchState) / 4); i += LL_WG) state[i] = h_state[i];
+    for (int i = threadIdx.x; i < (int)(sizeof(BatchState) / 4); i += LL_WG)
+      state[i] = st && i == (int)(offsetof(BatchState, next_token) / 4) + first ? st->next_token : h_state[i];
   const size_t row = (size_t)(first + blockIdx.x) * pt_stride;
   for (int i = threadIdx.x; i < pt_stride; i += LL_WG) table[row + i] = h_table[row + i];
 }

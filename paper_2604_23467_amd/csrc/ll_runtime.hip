@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <future>
 #include <string>
@@ -1131,6 +1132,35 @@ void destroy(Instance* I) {
   delete I;
 }
 
+// Waits until `count` words of pinned host memory that were kNoToken hold the tokens of queued work.  The words are polled:
+// the runtime's wait sleeps after some 200 us, and waking up costs 13 us a call (batched steps of four layers of the 7B
+// shape 389 -> 375 us).  For calls that are followed by more queued work, like a batch's: the runtime's own wait then finds
+// out about the work's end later, which costs a caller who does wait as much (a prompt of 25 tokens launched kernel by
+// kernel and its logits read back: 409 -> 425 us).  Work that takes longer than kPollMs is left to the runtime.
+constexpr int kNoToken = INT_MIN, kPollMs = 20;
+int wait_tokens(hipStream_t s, const int* words, int count) {
+  const volatile int* w = words;
+  const auto t0 = std::chrono::steady_clock::now();
+  for (int i = 0, polls = 0;; ++polls) {
+    while (i < count && w[i] != kNoToken) ++i;
+    if (i == count) break;
+    __builtin_ia32_pause();
+    if (polls % 64 == 63 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(kPollMs)) {
+      HIPCHK(hipStreamSynchronize(s));
+      for (; i < count; ++i)
+        if (w[i] == kNoToken) return fail(LL_E_HIP, "the queued work ended without its tokens");
+    }
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  return LL_OK;
+}
+// Before the work is queued: no token yet
+void expect_tokens(int* words, int count) {
+  volatile int* w = words;
+  for (int i = 0; i < count; ++i) w[i] = kNoToken;
+  std::atomic_thread_fence(std::memory_order_seq_cst);
+}
+
 bool eager(const Instance* I) { return (I->cfg.flags & LL_FLAG_EAGER) != 0; }
 
 // ---- one graph per KV length (Alg. 1; Sec. IV-A): rolling buffer, LRU eviction, the next length
@@ -1391,11 +1421,11 @@ void enqueue_batch_step(Instance* I, hipStream_t s) {
                      c.vocab, I->at<SampleCfg>(I->L.sample_cfg), bs, B->d_out);
 }
 
-// The slots' state and the page-table rows of slots first .. first + count - 1, host mirrors -> device
-int push_batch_state(Instance* I, int first, int count) {
+// The slots' state and the page-table rows of slots first .. first + count - 1, host mirrors -> device (st: see the kernel)
+int push_batch_state(Instance* I, int first, int count, const DevState* st = nullptr) {
   Batch* B = I->batch;
   hipLaunchKernelGGL(bt_push_kernel, dim3(count), dim3(LL_WG), 0, I->stream, (const int*)B->d_state_src,
-                     (int*)B->at<BatchState>(B->L.state), B->d_table_src, B->at<int>(B->L.page_table), B->L.pt_stride, first);
+                     (int*)B->at<BatchState>(B->L.state), B->d_table_src, B->at<int>(B->L.page_table), B->L.pt_stride, first, st);
   HIPCHK(hipGetLastError());
   return LL_OK;
 }
@@ -1718,14 +1748,10 @@ int prefill_check(Instance* I, const char* who, const int32_t* tokens, int32_t n
 
 }  // namespace
 
-extern "C" {
+namespace {
 
-int32_t ll_prefill(const int32_t* tokens, int32_t n) {
-  if (!g) return fail(LL_E_NOT_INIT, "ll_prefill: not initialised");
-  Instance* I = g;
-  const int chk = prefill_check(I, "ll_prefill", tokens, n);
-  if (chk != LL_OK) return chk;
-
+// Queues the prefill of a checked prompt; its token arrives in host_ring[0]
+int prefill_queue(Instance* I, const int32_t* tokens, int n) {
   // Prompt ids and the state block travel in one pinned staging buffer that the prefill's first kernel reads (two
   // host-to-device copies in front of it cost 15 us more).  A prompt longer than the
   // largest bucket goes through in chunks of that size: every chunk but the last runs the layers
@@ -1750,13 +1776,30 @@ int32_t ll_prefill(const int32_t* tokens, int32_t n) {
       while (I->pf_buckets[bi] != Mb) ++bi;
       HIPCHK(hipGraphLaunch(I->pf_exec[bi], I->stream));
     }
-    HIPCHK(hipStreamSynchronize(I->stream));       // the staging buffer is reused by the next chunk
+    if (!last) HIPCHK(hipStreamSynchronize(I->stream));       // the staging buffer is reused by the next chunk
     p0 += m;
   }
+  return LL_OK;
+}
+// Waits for it; the context then holds the prompt
+int prefill_finish(Instance* I, int n, const float* logits) {
+  HIPCHK(hipStreamSynchronize(I->stream));
   I->pos = n;
   I->steps = 1;
-  I->last_logits = I->pf.logits;
+  I->last_logits = logits;
   return I->fed = I->host_ring[0];
+}
+
+}  // namespace
+
+extern "C" {
+
+int32_t ll_prefill(const int32_t* tokens, int32_t n) {
+  if (!g) return fail(LL_E_NOT_INIT, "ll_prefill: not initialised");
+  Instance* I = g;
+  int rc = prefill_check(I, "ll_prefill", tokens, n);
+  if (rc == LL_OK) rc = prefill_queue(I, tokens, n);
+  return rc == LL_OK ? prefill_finish(I, n, I->pf.logits) : rc;
 }
 
 int32_t ll_prefill_static(const int32_t* tokens, int32_t n) {
@@ -1784,11 +1827,7 @@ int32_t ll_prefill_static(const int32_t* tokens, int32_t n) {
   enqueue_stage(I, I->stream, B, n <= 16 ? 16 : 32, true);
   enqueue_prefill_skinny(I, I->stream, B, n <= 16 ? 16 : 32, true);     // launched kernel by kernel: no graph holds these addresses
   HIPCHK(hipGetLastError());
-  HIPCHK(hipStreamSynchronize(I->stream));
-  I->pos = n;
-  I->steps = 1;
-  I->last_logits = B.logits;
-  return I->fed = I->host_ring[0];
+  return prefill_finish(I, n, B.logits);
 }
 
 int32_t ll_decode_n(int32_t k, int32_t* out_tokens) {
@@ -1927,10 +1966,11 @@ int32_t ll_batch_add(const int32_t* tokens, int32_t n, int32_t* first_token) {
       return fail(LL_E_BAD_ARG, "ll_batch_add: tokens[%d] = %d outside [0, %d)", i, tokens[i], I->cfg.vocab);
   // the prompt runs through the single-sequence prefill (whose context it replaces) ...
   int rc = ll_reset();
+  if (rc == LL_OK) rc = prefill_check(I, "ll_batch_add", tokens, n);
+  expect_tokens(I->host_ring, 1);
+  if (rc == LL_OK) rc = prefill_queue(I, tokens, n);
   if (rc != LL_OK) return rc;
-  const int32_t t1 = ll_prefill(tokens, n);
-  if (t1 < 0) return t1;
-  // ... and its cache rows move into the slot's pages
+  // ... and behind it, not waited for in between, its cache rows move into the slot's pages
   for (int i = 0; i < need; ++i) {
     const int pg = B->free_pages.back();
     B->free_pages.pop_back();
@@ -1938,16 +1978,18 @@ int32_t ll_batch_add(const int32_t* tokens, int32_t n, int32_t* first_token) {
     B->h_table[slot * B->L.pt_stride + i] = pg * B->page_tokens;
   }
   B->h_state->pos[slot] = n;
-  B->h_state->next_token[slot] = t1;
   B->h_state->active[slot] = 1;
   B->h_state->steps[slot] = 1;                  // the prefill drew with index 0
-  if ((rc = push_batch_state(I, slot, 1)) != LL_OK) return rc;
+  if ((rc = push_batch_state(I, slot, 1, I->state())) != LL_OK) return rc;
   const ll_config& c = I->cfg;
   hipLaunchKernelGGL(bt_scatter_kernel, dim3(n, c.n_layers * 2), dim3(LL_WG), 0, I->stream, I->kcache(0),
                      I->L.kv_layer_halves, c.max_seq, B->kpool(0), B->L.kv_layer_halves, B->L.pool_rows,
                      B->at<int>(B->L.page_table), B->L.pt_stride, B->page_tokens, slot, c.n_heads, c.head_dim);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipStreamSynchronize(I->stream));
+  if ((rc = wait_tokens(I->stream, I->host_ring, 1)) != LL_OK) return rc;
+  const int32_t t1 = prefill_finish(I, n, I->pf.logits);
+  if (t1 < 0) return t1;
+  B->h_state->next_token[slot] = t1;
   *first_token = t1;
   return slot;
 }
@@ -2009,13 +2051,15 @@ int ll_batch_step(int32_t* out_tokens) {
     hipLaunchKernelGGL(bt_page_update_kernel, dim3(1), dim3(64), 0, I->stream, B->at<int>(B->L.page_table), up);
     HIPCHK(hipGetLastError());
   }
+  expect_tokens(B->h_out, B->rows);
   if (eager(I)) {
     enqueue_batch_step(I, I->stream);
     HIPCHK(hipGetLastError());
   } else {
     HIPCHK(hipGraphLaunch(B->exec, I->stream));
   }
-  HIPCHK(hipStreamSynchronize(I->stream));
+  const int rc = wait_tokens(I->stream, B->h_out, B->rows);
+  if (rc != LL_OK) return rc;
   for (int j = 0; j < up.n; ++j) {                 // the step ran: the pages are the slots' now
     B->free_pages.pop_back();
     B->pages[up_slot[j]].push_back(up.row[j] / B->page_tokens);
