@@ -169,10 +169,9 @@ GemmPlan gemm_plan(int N, int K, int nmat, int Mb, int ldc) {
 }
 
 // ---- projections of 33..1024 rows from the fragment-major weight copy (prefill_tile.h) ----
-// Template arguments of one projection kernel.  kind: 'T' = pf_tile_kernel, 'S' = pf_stream_kernel (four K waves); then row
-// waves, K waves, row blocks and column blocks per wave, K steps per stage, ring stages ('S': steps of look-ahead), weights used once
+// Template arguments of one projection kernel: row waves, K waves, row blocks and column blocks per wave, K steps per stage,
+// ring stages, weights used once
 struct TileShape {
-  char kind;
   int wm, wk, mt, nb, s32, ns;
   bool wnt;
 };
@@ -183,32 +182,30 @@ constexpr int tile_rows(const TileShape& t) { return 32 * t.wm * t.mt; }
 // second column of shapes:
 //  * Q/K/V with more weight rows than its own smaller tiles cover in a round takes the gate/up shapes, which hold 96 or
 //    192 columns of all the bucket's rows (d_model 8192, 50 rows: 256 tiles of 96 columns 69 us, 384 of 64 columns 89 us);
-//  * a residual projection whose K loop can be cut into more pieces takes wider tiles (down at 512 rows: 51 us in 4
+//  * a residual projection whose K loop can be cut into more pieces takes wider tiles (down at 512 rows: 45 us in 4
 //    pieces of 128 columns, 62 us in 2 of 64; the O projection of the 7B shape is better off with fewer slices,
-//    25.3 against 27.3 us).
-// Each line is the fastest of those measured at the 7B shape (us, Q/K/V with RoPE and cache write / O / gate/up with
-// SwiGLU / down): 64 rows 23.4 / 9.9 / 34.3 / 20.3, 128: 29.9 / 12.9 / 40.4 / 25.5, 192: 37.4 / 16.5 / 50.2 / 31.1,
-// 256: 39.8 / 18.7 / 57.0 / 36.0, 384: 50.9 / 21.7 / 78.6 / 43.7, 512: 59.3 / 25.3 / 87.2 / 50.7,
-// 1024: 97.5 / 39.9 / 164.8 / 87.0.
+//    24.0 us in 2 pieces and 23.3 in 4, which the norm behind it has to add up).
+// Each line is the fastest of those measured at the 7B shape (prefill_tile.h has the times), stages of 4 K steps in rings of
+// 3 wherever the registers hold.
 constexpr TileShape tile_shape(int mode, int Mb, bool alt) {
   if (mode == SK_QKV && !alt) {
-    return Mb <= 64 ? TileShape{'S', 1, 4, 2, 2, 0, 8, true} : Mb <= 128 ? TileShape{'S', 1, 4, 2, 3, 0, 8, false}
-         : Mb <= 192 ? TileShape{'S', 1, 4, 3, 3, 0, 8, false} : Mb <= 256 ? TileShape{'T', 2, 2, 2, 3, 8, 3, false}
-         : Mb <= 384 ? TileShape{'T', 2, 2, 3, 3, 8, 3, false} : Mb <= 512 ? TileShape{'T', 4, 1, 2, 3, 8, 3, false}
-         : TileShape{'T', 4, 1, 2, 6, 4, 3, false};
+    return Mb <= 64 ? TileShape{2, 2, 1, 2, 4, 3, true} : Mb <= 128 ? TileShape{4, 1, 1, 2, 8, 3, true}
+         : Mb <= 192 ? TileShape{2, 2, 3, 2, 8, 3, true} : Mb <= 256 ? TileShape{2, 2, 2, 3, 4, 3, false}
+         : Mb <= 384 ? TileShape{2, 2, 3, 3, 4, 3, false} : Mb <= 512 ? TileShape{4, 1, 2, 3, 4, 3, false}
+         : TileShape{4, 1, 2, 6, 4, 3, false};
   }
   if (mode != SK_RES) {
-    return Mb <= 64 ? TileShape{'S', 1, 4, 2, 3, 0, 8, true} : Mb <= 128 ? TileShape{'T', 4, 1, 1, 3, 8, 3, true}
-         : Mb <= 192 ? TileShape{'T', 2, 2, 3, 3, 8, 3, true} : Mb <= 256 ? TileShape{'T', 4, 1, 2, 3, 8, 3, true}
-         : Mb <= 384 ? TileShape{'T', 4, 1, 3, 3, 8, 3, true} : TileShape{'T', 4, 1, 2, 6, 4, 3, false};
+    return Mb <= 64 ? TileShape{2, 2, 1, 3, 4, 3, true} : Mb <= 128 ? TileShape{4, 1, 1, 3, 4, 3, true}
+         : Mb <= 192 ? TileShape{2, 2, 3, 3, 4, 3, true} : Mb <= 256 ? TileShape{4, 1, 2, 3, 4, 3, true}
+         : Mb <= 384 ? TileShape{4, 1, 3, 3, 4, 3, true} : TileShape{4, 1, 2, 6, 4, 3, false};
   }
-  if (Mb <= 64) return alt ? TileShape{'S', 1, 4, 2, 2, 0, 8, true} : TileShape{'S', 1, 4, 2, 1, 0, 8, true};
-  if (Mb <= 128) return alt ? TileShape{'T', 2, 2, 2, 2, 8, 4, true} : TileShape{'S', 1, 4, 4, 2, 0, 6, true};
-  if (Mb <= 192) return TileShape{'T', 2, 2, 3, 2, 8, 4, true};
-  if (Mb <= 256) return TileShape{'T', 4, 1, 2, 2, 8, 4, true};
-  if (Mb <= 384) return alt ? TileShape{'T', 2, 2, 3, 4, 4, 4, false} : TileShape{'T', 2, 2, 3, 2, 8, 4, false};
-  if (Mb <= 512 && !alt) return TileShape{'T', 4, 1, 2, 2, 8, 4, false};
-  return TileShape{'T', 4, 1, 2, 4, 4, 4, false};
+  if (Mb <= 64) return TileShape{2, 2, 1, 2, 4, 3, true};
+  if (Mb <= 128) return TileShape{2, 2, 2, 2, 4, 3, true};
+  if (Mb <= 192) return TileShape{2, 2, 3, 2, 4, 3, true};
+  if (Mb <= 256) return TileShape{4, 1, 2, 2, 4, 3, true};
+  if (Mb <= 384) return alt ? TileShape{4, 1, 3, 2, 4, 3, true} : TileShape{2, 2, 3, 2, 4, 3, false};
+  if (Mb <= 512 && !alt) return TileShape{4, 1, 2, 2, 4, 3, false};
+  return TileShape{4, 1, 2, 4, 2, 3, false};
 }
 // Second shape or first?  Q/K/V: where the first takes more than one round.  Residual projections: where K is long, and
 // where the first shape leaves no CU for a second piece of the K loop (d_model above 4096).  Four layers, first tokens
@@ -225,7 +222,7 @@ bool tile_alt(int mode, int N, int K, int Mb) {
 int tile_pieces(int N, int K, int Mb) {
   const TileShape t = tile_shape(SK_RES, Mb, tile_alt(SK_RES, N, K, Mb));
   const int ctiles = (skinny_units(SK_RES, N) + 2 * t.nb - 1) / (2 * t.nb), mtiles = Mb / tile_rows(t);
-  const int ksteps = (K + 31) / 32, stages = t.kind == 'T' ? (ksteps + t.s32 - 1) / t.s32 : (ksteps + 7) / 8;
+  const int stages = ((K + 31) / 32 + t.s32 - 1) / t.s32;
   int ks = num_cus() / (ctiles * mtiles);
   ks = ks < 1 ? 1 : ks > 8 ? 8 : ks;
   if (ks > stages) ks = stages;
@@ -233,14 +230,14 @@ int tile_pieces(int N, int K, int Mb) {
   return (stages + q - 1) / q;
 }
 
-// 16-row weight blocks per column tile: whole tiles, except that the stream kernel takes the fewest that still make one
-// round of workgroups.  Its time goes with the bytes that one CU fetches, so a CU without a workgroup is lost: Q/K/V
-// at 50 rows in 256 tiles of 48 columns 23.4 us, in 192 of 64 columns 28.4 us.  A tile kernel multiplies the rows that
-// read as zero like the others and gains nothing (gate/up at 512 rows in 252 tiles of 176 columns instead of 230 of
-// 192: the whole prefill 1 % slower).  `per_ctile`: workgroups per column tile.
-int tile_units(int mode, int N, const TileShape& t, int per_ctile) {
+// 16-row weight blocks per column tile: whole tiles, except that up to 128 rows it is the fewest that still make one
+// round of workgroups.  There the time goes with the bytes that one CU fetches, so a CU without a workgroup is lost: Q/K/V
+// at 50 rows in 256 tiles of 48 columns 22.6 us, in 192 of 64 columns 25.5; at 100 rows 27.2 and 28.4.  From 192 rows on
+// the columns that read as zero cost as much as the others (Q/K/V at 180 rows 35.6 in 256 tiles, 35.0 in 192).
+// `per_ctile`: workgroups per column tile.
+int tile_units(int mode, int N, const TileShape& t, int Mb, int per_ctile) {
   const int units = pt_units(mode, N), most = 2 * t.nb;
-  for (int u = t.nb; t.kind == 'S' && u < most; ++u)
+  for (int u = t.nb; Mb <= 128 && u < most; ++u)
     if ((units + u - 1) / u * per_ctile <= num_cus()) return u;
   return most;
 }
@@ -256,19 +253,11 @@ template <int MODE, int I>
 void tile_go(TileLaunch& L) {
   constexpr int kRows[] = {64, 128, 192, 256, 384, 512, 1024};
   constexpr TileShape t = tile_shape(MODE, kRows[I >> 1], (I & 1) != 0);
-  if constexpr (t.kind == 'T') {
-    auto k = pf_tile_kernel<MODE, t.wm, t.wk, t.mt, t.nb, t.s32, t.ns, t.wnt>;
-    constexpr int lds = PT_LDS_BYTES(t.nb, t.s32, t.ns);
-    static_assert(lds <= 160 * 1024 && (t.wk == 1 || lds >= t.wm * t.mt * t.nb * 4096), "ring and exchange fit the LDS");
-    if (L.init) L.err = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    else hipLaunchKernelGGL(k, dim3(L.grid), dim3(PT_THREADS), lds, L.s, *L.a);
-  } else {
-    auto k = pf_stream_kernel<MODE, t.mt, t.nb, t.ns, t.wnt>;
-    constexpr int lds = PS_LDS_BYTES(t.mt, t.nb);
-    static_assert(lds <= 160 * 1024, "partial sums fit the LDS");
-    if (L.init) L.err = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    else hipLaunchKernelGGL(k, dim3(L.grid), dim3(PT_THREADS), lds, L.s, *L.a);
-  }
+  auto k = pf_tile_kernel<MODE, t.wm, t.wk, t.mt, t.nb, t.s32, t.ns, t.wnt>;
+  constexpr int lds = PT_LDS_BYTES(t.nb, t.s32, t.ns);
+  static_assert(lds <= 160 * 1024 && (t.wk == 1 || lds >= t.wm * t.mt * t.nb * 4096), "ring and exchange fit the LDS");
+  if (L.init) L.err = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  else hipLaunchKernelGGL(k, dim3(L.grid), dim3(pt_threads(t.mt, t.nb)), lds, L.s, *L.a);
 }
 template <int MODE>
 void tile_dispatch(TileLaunch& L, int Mb, bool alt) {
@@ -303,7 +292,7 @@ TilePlan tile_plan(int mode, int N, int K, int Mb) {
   p.shape = tile_shape(mode, Mb, p.alt);
   p.ks = mode == SK_RES ? tile_pieces(N, K, Mb) : 1;
   p.mtiles = Mb / tile_rows(p.shape);
-  p.upt = tile_units(mode, N, p.shape, p.mtiles * p.ks);
+  p.upt = tile_units(mode, N, p.shape, Mb, p.mtiles * p.ks);
   p.ctiles = (pt_units(mode, N) + p.upt - 1) / p.upt;
   return p;
 }
@@ -2181,7 +2170,7 @@ int ll_dbg_tile_plan(int32_t kind, int32_t N, int32_t K, int32_t rows, int32_t* 
     return fail(LL_E_BAD_ARG, "ll_dbg_tile_plan: bad argument");
   const TilePlan p = tile_plan(kind, N, K, rows);
   out6[0] = p.mtiles; out6[1] = p.ctiles; out6[2] = p.upt; out6[3] = p.ks;
-  out6[4] = p.shape.kind == 'T' ? p.shape.s32 : 0; out6[5] = p.grid();
+  out6[4] = p.shape.s32; out6[5] = p.grid();
   return LL_OK;
 }
 

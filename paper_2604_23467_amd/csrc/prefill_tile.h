@@ -10,14 +10,25 @@
 // next RMSNorm adds up.
 //
 // What bounds these kernels, measured with timing-only builds.  Every byte of both operands enters a CU through
-// its vector L1 once per tile, (rows + columns) * K * 2, and those bytes cost 40 TB/s chip-wide ON TOP of the
-// time the weights take from HBM (gate/up, 256 rows: weights alone 47 us, with the activations 58): the two do
-// not overlap, so tiles are as square as a single round allows.  At 512 rows and more the matrix instructions
+// its vector L1 once per tile, (rows + columns) * K * 2.  A CU's loads come back in the order they were issued, whichever
+// wave issued them, and some 70 KB of them are in flight at most: what stands behind a weight that comes from HBM waits as
+// long as that weight.  So a CU takes 60 .. 75 GB/s of a mixed stream (gate/up at 250 rows on a quarter of the chip: the
+// weights alone 18 us, the activations alone 20, both 44), where it takes 150 of the activations alone, deeper look-ahead
+// changes nothing, and tiles are as square as a single round allows.  The weights' loads are therefore the work of four
+// waves of their own: a stage at a time, back to back, while the four waves that multiply never wait to issue, and with
+// no more stages in flight than it takes (rings of 5 and 6 stages are slower).  Before, the multiplying waves dealt the
+// weights' loads out behind their matrix instructions, or, up to 192 rows, brought them to registers; now, us at
+// 64 / 128 / 192 / 256 / 384 / 512 rows, before -> with waves that load:
+//   Q/K/V    22.8 30.0 35.7 40.1 50.6 55.7 -> 22.4 27.2 35.0 38.4 47.1 52.0
+//   gate/up  34.4 39.6 49.2 55.0 74.1      -> 31.2 39.2 46.5 49.7 65.0
+//   O         9.6 12.3 16.0 18.2 22.6 25.9 ->  9.2 11.3 14.6 16.2 20.7 24.0
+//   down     20.3 26.1 32.0 36.5 42.1 48.0 -> 19.5 23.4 29.3 31.1 42.3 45.2
+// At 512 rows and more the matrix instructions
 // are the larger part (gate/up at 512 rows: 98 k of 114 k cycles in the K loop) and the chip runs them at 1.6-1.8
-// GHz.  LDS holds only the weights (direct loads in, 4 or 2 fragment reads per byte out); the
-// activations go straight to registers, one stage ahead.  With both operands in LDS (128 x 256 tiles, eight
-// waves) the LDS port was busy 1.4 times as long as the matrix cores: gate/up at 512 rows 110 us + 16 us SwiGLU
-// kernel against 88 us here, Q/K/V 67 + 12 against 59.
+// GHz; tiles of 256 x 192 leave no registers for a second wave per SIMD, and keep the old way.  LDS holds only the weights
+// (direct loads in, 4 or 2 fragment reads per byte out); the activations go straight to registers.  With both operands in
+// LDS (128 x 256 tiles, eight waves) the LDS port was busy 1.4 times as long as the matrix cores: gate/up at 512 rows
+// 110 us + 16 us SwiGLU kernel against 88 us here, Q/K/V 67 + 12 against 59.
 //
 // v_mfma_f32_32x32x16_f16: 1.76 PFLOP/s from one wave per SIMD; the 16x16x32 form reaches 1.1.
 #pragma once
@@ -30,7 +41,7 @@ struct TileArgs {
   const DevState* st;
   int N, K, tb;
   int mtiles, ctiles, ks; // row tiles, column tiles, pieces of the K loop
-  int upt;                // stream kernel: 16-row weight blocks of a column tile, at most 2 NB (the rest reads as zero)
+  int upt;                // 16-row weight blocks of a column tile, at most 2 NB (the rest reads as zero, without traffic)
   half_t* Hout;           // GATEUP: [rows][N] fp16, fragment-major
   half_t* Q;              // QKV: [rows][N] fp16 rotated queries
   half_t* kc;             // QKV: this layer's K cache [head][max_seq][head_dim]
@@ -47,7 +58,10 @@ __host__ __device__ inline int pt_units(int mode, int N) {
   return mode == SK_GATEUP ? (N + 31) / 32 * 4 : skinny_units(mode, N);
 }
 
-#define PT_THREADS 256
+#define PT_WAVES 4           // waves that multiply
+// Tiles whose accumulators leave room for two waves per SIMD have four more waves, which load the weights
+__host__ __device__ constexpr bool pt_fed(int mt, int nb) { return mt * nb <= 9; }
+__host__ __device__ constexpr int pt_threads(int mt, int nb) { return (pt_fed(mt, nb) ? 2 : 1) * PT_WAVES * 64; }
 #define PT_LDS_BYTES(NB, S32, NS) ((NS) * (NB) * (S32) * 2048)
 
 // g / (1 + expf(-g)) * u at the library functions' own error (max 2.2e-7, rms 4.6e-8 of the value against 64 bits over
@@ -143,16 +157,26 @@ __host__ __device__ constexpr PtWaits pt_waits(int NS, int PP, int WS, int MT, i
   return w;
 }
 
-// Tile of 32 WM MT rows x 32 NB columns, four waves: WM along the rows (MT row blocks of 32 each), WK = 2
+// k16 steps by which a wave requests its activations ahead, in tiles that are fed by other waves: a stage's, where that is
+// what the measured tiles wanted (gate/up at 250 rows: 8 steps 49.7 us, 4 52.6; Q/K/V at 100: 16 steps 27.2, 4 29.2), but
+// 4 for the residual projections (down at 250 rows: 31.1, 8 32.3), in stages of a single row block and 8 steps (gate/up
+// at 100: 39.2, 8 42.4), and where three row blocks leave no registers for more
+__host__ __device__ constexpr int pt_look(int mode, int wk, int mt, int s32) {
+  const int ws = s32 * 2 / wk;
+  return mode == SK_RES || (mt == 1 && s32 == 4) || (wk == 1 && mt >= 3) ? (ws < 4 ? ws : 4) : ws;
+}
+
+// Tile of 32 WM MT rows x 32 NB columns, four waves that multiply: WM along the rows (MT row blocks of 32 each), WK = 2
 // splitting every K step in half between two waves per row group (half the LDS reads; the two halves of the
 // accumulators are exchanged through LDS at the end).  Weights: a ring of NS stages of S32 32-wide K steps in LDS,
-// filled by direct loads, 1 KB of consecutive bytes each, dealt one behind a matrix instruction over the steps
-// that follow a stage's release.  Activations: WS steps of MT fragments in registers, each re-requested for the
-// next stage as soon as its last product is issued.  WNT: weights used by a single row tile are loaded
-// non-temporal.
+// filled by direct loads, 1 KB of consecutive bytes each: by four waves of their own, a freed stage at a time, or
+// dealt one behind a matrix instruction over the steps that follow a stage's release (pt_fed).  Activations: steps of MT
+// fragments in registers, each re-requested for a later step (pt_look; the next stage's) as soon as its last product is
+// issued.  WNT: weights used by a single row tile are loaded non-temporal.
 template <int MODE, int WM, int WK, int MT, int NB, int S32, int NS, bool WNT>
-__global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
-  static_assert(WM * WK == 4, "four waves");
+__global__ __launch_bounds__(pt_threads(MT, NB), 1) void pf_tile_kernel(TileArgs a) {
+  static_assert(WM * WK == PT_WAVES, "four waves");
+  constexpr bool FED = pt_fed(MT, NB);
   constexpr int BM = 32 * WM * MT;                 // rows of the tile
   constexpr int WS = S32 * 2 / WK;                 // k16 steps of a wave per stage
   constexpr int PIECES = 2 * NB * S32;             // 1 KB pieces per stage
@@ -162,7 +186,7 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
   extern __shared__ __attribute__((aligned(16))) half_t pt_lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave % WM, wk = wave / WM;
+  const int w4 = wave & 3, wm = w4 % WM, wk = w4 / WM;
   const int r = lane & 31, half = lane >> 5;
 
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -172,24 +196,24 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
   if (run >= a.ctiles * a.ks || m0 >= n) return;
   const int ct = run / a.ks, split = run - ct * a.ks;
   const int K = a.K, ksteps = (K + 31) >> 5;
-  const int units = skinny_units(MODE, a.N), upad = pt_units(MODE, a.N), u0 = ct * NB * 2;
+  const int units = skinny_units(MODE, a.N), upad = min(pt_units(MODE, a.N), (ct + 1) * a.upt), u0 = ct * a.upt;
   const int stages = (ksteps + S32 - 1) / S32;
   const int q = (stages + a.ks - 1) / a.ks;
   const int sl0 = split * q, cnt = min(q, stages - sl0);
 
-  // Piece idx of this wave in a stage: 16-row block blk and K step s of piece p = idx * 4 + wave, k-step major
+  // Piece idx of this wave in a stage: 16-row block blk and K step s of piece p = idx * 4 + w4, k-step major
   // in LDS.  Everything that does not change from stage to stage sits in registers: the byte offset of the
   // lane's 16 bytes from the stage's start in the weight copy.
   int pvoff[PP], pks[PP];
 #pragma unroll
   for (int idx = 0; idx < PP; ++idx) {
-    const int p = idx * 4 + wave, s = p / (2 * NB), blk = p - s * (2 * NB);
+    const int p = idx * 4 + w4, s = p / (2 * NB), blk = p - s * (2 * NB);
     pks[idx] = s;
     pvoff[idx] = (blk * ksteps + s) * 1024 + lane * 16;
   }
   // Operands are fetched through buffer descriptors: what lies outside (blocks past the matrix, K steps past
   // its end, stages past this piece of the K loop) reads as zero without a branch and without traffic.
-  const int blocks = max(min(units - u0, 2 * NB), 0);
+  const int blocks = max(min(units - u0, a.upt), 0);
   const half_t* wbase = a.Wf + (size_t)u0 * ksteps * 512;
   const unsigned wbytes = (unsigned)blocks * ksteps * 1024u;
   const unsigned astep = (unsigned)a.tb * 1024u, abytes = (unsigned)ksteps * astep;
@@ -207,9 +231,40 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
   auto issue_piece = [&](__amdgpu_buffer_rsrc_t w, int left, int stage, int idx) {
     const int voff = pvoff[idx] | (pks[idx] < left ? 0 : 0x40000000);       // a K step past the end: out of range
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        w, (__attribute__((address_space(3))) void*)(pt_lds + stage * STAGE + (idx * 4 + wave) * 512), 16, voff, 0, 0,
+        w, (__attribute__((address_space(3))) void*)(pt_lds + stage * STAGE + (idx * 4 + w4) * 512), 16, voff, 0, 0,
         WNT ? 2 : 0);
   };
+  if constexpr (FED) {
+    // The waves that load: a stage is handed over when its pieces have landed (each wave's own come back in order) and refilled
+    // when all have left it.  Behind the K loop they leave, once nothing of theirs is on its way into the ring any more.
+    if (__builtin_expect(wave >= PT_WAVES, 1)) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int k32 = stage_k(s);
+        const __amdgpu_buffer_rsrc_t w = w_rsrc(k32);
+#pragma unroll
+        for (int idx = 0; idx < PP; ++idx) issue_piece(w, ksteps - k32, s, idx);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      static_assert(PP * (NS - 1) < 64, "vmcnt has 6 bits");
+      wait_vm_at_most<PP * (NS - 1)>();
+      __builtin_amdgcn_s_barrier();
+      int stage = 0;
+      for (int it = 0; it < cnt; ++it) {
+        wait_vm_at_most<PP * (NS - 2)>();          // stage it + 1; the younger ones are on their way
+        __builtin_amdgcn_s_barrier();
+        const int k32 = stage_k(it + NS);
+        const __amdgpu_buffer_rsrc_t w = w_rsrc(k32);
+#pragma unroll
+        for (int idx = 0; idx < PP; ++idx) issue_piece(w, ksteps - k32, stage, idx);
+        __builtin_amdgcn_sched_barrier(0);
+        stage = stage + 1 == NS ? 0 : stage + 1;
+      }
+      wait_vm_at_most<0>();
+      if (WK == 2) __builtin_amdgcn_s_barrier();   // the exchange takes the ring's place
+      return;
+    }
+  }
   // activation fragment of the wave's k16 step ws, row block mt
   int avoff[MT];
 #pragma unroll
@@ -231,91 +286,136 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  auto slot_of = [](int idx) { return pt_slot(idx, WS, PP); };
-  constexpr int N_SLOT0 = (PP + WS - 1) / WS;
-
-  h8 fa[WS][MT], fb[2][NB];
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s) {
-    const int k32 = stage_k(s);
-    const __amdgpu_buffer_rsrc_t w = w_rsrc(k32);
-#pragma unroll
-    for (int idx = 0; idx < PP; ++idx) issue_piece(w, ksteps - k32, s, idx);
-    __builtin_amdgcn_sched_barrier(0);      // the waits below count loads: they hold for this order of issue only
-    if (s == 0) {
-      const __amdgpu_buffer_rsrc_t ar = a_rsrc(k32);
-#pragma unroll
-      for (int ws = 0; ws < WS; ++ws)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) fa[ws][mt] = load_a(ar, ws, mt);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  // the refill under way: descriptor and K steps left of the stage that is being fetched
-  int rk = stage_k(NS - 1);
-  __amdgpu_buffer_rsrc_t rw = w_rsrc(rk);
-#pragma unroll
-  for (int idx = 0; idx < PP; ++idx)
-    if (slot_of(idx) == 0) issue_piece(rw, ksteps - rk, NS - 1, idx);
-
+  constexpr int LOOK = FED ? pt_look(MODE, WK, MT, S32) : WS;
+  static_assert(WS % LOOK == 0, "a step's registers are the same in every stage");
+  static_assert(WS % 2 == 0, "the fragment double buffer keeps its parity across stages");
+  h8 fa[LOOK][MT], fb[2][NB];
   auto load_b = [&](int stage, int ws, h8 (&f)[NB]) {
     const int s = WK == 1 ? ws >> 1 : ws, ks = WK == 1 ? ws & 1 : wk;
     const half_t* base = pt_lds + stage * STAGE + (s * 2 * NB + (r >> 4)) * 512 + ((ks * 2 + half) * 16 + (r & 15)) * 8;
 #pragma unroll
     for (int j = 0; j < NB; ++j) f[j] = *reinterpret_cast<const h8*>(base + j * 1024);
   };
-  constexpr PtWaits WAIT = pt_waits(NS, PP, WS, MT, NB);
-  __builtin_amdgcn_sched_barrier(0);
-  wait_vm_at_most<WAIT.first>();
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-  load_b(0, 0, fb[0]);
-  __builtin_amdgcn_sched_barrier(0);
-  int stage = 0;
-  for (int it = 0; it < cnt; ++it) {
-    const __amdgpu_buffer_rsrc_t ar = a_rsrc(stage_k(it + 1));
-    const int nstage = stage + 1 == NS ? 0 : stage + 1;
-    const int pstage = stage == 0 ? NS - 1 : stage - 1;
+  if constexpr (FED) {
+    __amdgpu_buffer_rsrc_t ar = a_rsrc(stage_k(0));
 #pragma unroll
-    for (int ws = 0; ws < WS; ++ws) {
-      wait_lgkm_at_most<0>();
-      __builtin_amdgcn_sched_barrier(0);
-      if (ws + 1 < WS) {
-        load_b(stage, ws + 1, fb[(ws + 1) & 1]);
-      } else {
-        wait_vm_at_most<WAIT.handover>();
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        load_b(nstage, 0, fb[0]);
-        rk = stage_k(it + NS);
-        rw = w_rsrc(rk);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      // the refill under way: slot 0 right behind the hand-over of stage it, slot s in step s - 1 of stage it + 1
-      const int rstage = ws == WS - 1 ? stage : pstage;
-      const int sl = (ws + 1) % WS;
-      const int first = (sl * PP + WS - 1) / WS;
+    for (int ws = 0; ws < LOOK; ++ws)
 #pragma unroll
-      for (int t = 0; t < MT * NB; ++t) {
-        const int mt = t / NB, nb = t % NB;
-        acc[mt][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[ws & 1][nb], fa[ws][mt], acc[mt][nb], 0, 0, 0);
+      for (int mt = 0; mt < MT; ++mt) fa[ws][mt] = load_a(ar, ws, mt);
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    load_b(0, 0, fb[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    int stage = 0;
+    for (int it = 0; it < cnt; ++it) {
+      const __amdgpu_buffer_rsrc_t ar1 = a_rsrc(stage_k(it + 1));
+      const int nstage = stage + 1 == NS ? 0 : stage + 1;
+#pragma unroll
+      for (int ws = 0; ws < WS; ++ws) {
+        wait_lgkm_at_most<0>();
         __builtin_amdgcn_sched_barrier(0);
-        if (first + t < PP && slot_of(first + t) == sl) {
-          issue_piece(rw, ksteps - rk, rstage, first + t);
-          __builtin_amdgcn_sched_barrier(0);
+        if (ws + 1 < WS) {
+          load_b(stage, ws + 1, fb[(ws + 1) & 1]);
+        } else {                       // this wave has left the stage, and the next one is complete
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+          load_b(nstage, 0, fb[0]);
         }
-        if (nb == NB - 1) {
-          fa[ws][mt] = load_a(ar, ws, mt);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < MT * NB; ++t) {
+          const int mt = t / NB, nb = t % NB;
+          acc[mt][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[ws & 1][nb], fa[ws % LOOK][mt], acc[mt][nb], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
+          if (nb == NB - 1) {
+            fa[ws % LOOK][mt] = ws + LOOK < WS ? load_a(ar, ws + LOOK, mt) : load_a(ar1, ws + LOOK - WS, mt);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
       }
-      static_assert(WS % 2 == 0, "the fragment double buffer keeps its parity across stages");
-      static_assert(N_SLOT0 <= MT * NB, "one piece behind each matrix instruction at most");
+      stage = nstage;
+      ar = ar1;
     }
-    stage = nstage;
+  } else {
+    auto slot_of = [](int idx) { return pt_slot(idx, WS, PP); };
+    constexpr int N_SLOT0 = (PP + WS - 1) / WS;
+
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) {
+      const int k32 = stage_k(s);
+      const __amdgpu_buffer_rsrc_t w = w_rsrc(k32);
+#pragma unroll
+      for (int idx = 0; idx < PP; ++idx) issue_piece(w, ksteps - k32, s, idx);
+      __builtin_amdgcn_sched_barrier(0);      // the waits below count loads: they hold for this order of issue only
+      if (s == 0) {
+        const __amdgpu_buffer_rsrc_t ar = a_rsrc(k32);
+#pragma unroll
+        for (int ws = 0; ws < WS; ++ws)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) fa[ws][mt] = load_a(ar, ws, mt);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    // the refill under way: descriptor and K steps left of the stage that is being fetched
+    int rk = stage_k(NS - 1);
+    __amdgpu_buffer_rsrc_t rw = w_rsrc(rk);
+#pragma unroll
+    for (int idx = 0; idx < PP; ++idx)
+      if (slot_of(idx) == 0) issue_piece(rw, ksteps - rk, NS - 1, idx);
+
+    constexpr PtWaits WAIT = pt_waits(NS, PP, WS, MT, NB);
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vm_at_most<WAIT.first>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    load_b(0, 0, fb[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    int stage = 0;
+    for (int it = 0; it < cnt; ++it) {
+      const __amdgpu_buffer_rsrc_t ar = a_rsrc(stage_k(it + 1));
+      const int nstage = stage + 1 == NS ? 0 : stage + 1;
+      const int pstage = stage == 0 ? NS - 1 : stage - 1;
+#pragma unroll
+      for (int ws = 0; ws < WS; ++ws) {
+        wait_lgkm_at_most<0>();
+        __builtin_amdgcn_sched_barrier(0);
+        if (ws + 1 < WS) {
+          load_b(stage, ws + 1, fb[(ws + 1) & 1]);
+        } else {
+          wait_vm_at_most<WAIT.handover>();
+          __builtin_amdgcn_s_barrier();
+          asm volatile("" ::: "memory");
+          load_b(nstage, 0, fb[0]);
+          rk = stage_k(it + NS);
+          rw = w_rsrc(rk);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // the refill under way: slot 0 right behind the hand-over of stage it, slot s in step s - 1 of stage it + 1
+        const int rstage = ws == WS - 1 ? stage : pstage;
+        const int sl = (ws + 1) % WS;
+        const int first = (sl * PP + WS - 1) / WS;
+#pragma unroll
+        for (int t = 0; t < MT * NB; ++t) {
+          const int mt = t / NB, nb = t % NB;
+          acc[mt][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[ws & 1][nb], fa[ws][mt], acc[mt][nb], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (first + t < PP && slot_of(first + t) == sl) {
+            issue_piece(rw, ksteps - rk, rstage, first + t);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if (nb == NB - 1) {
+            fa[ws][mt] = load_a(ar, ws, mt);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        static_assert(N_SLOT0 <= MT * NB, "one piece behind each matrix instruction at most");
+      }
+      stage = nstage;
+    }
+    wait_vm_at_most<0>();     // the look-ahead loads must not outlive the workgroup's LDS
+    wait_lgkm_at_most<0>();
   }
-  wait_vm_at_most<0>();     // the look-ahead loads must not outlive the workgroup's LDS
-  wait_lgkm_at_most<0>();
 
   if constexpr (WK == 2) {
     // the two K halves of a row block: every wave hands over half of its accumulators and finishes the other half
@@ -358,112 +458,6 @@ __global__ __launch_bounds__(PT_THREADS, 1) void pf_tile_kernel(TileArgs a) {
       f4 lo, hi;
 #pragma unroll
       for (int i = 0; i < 4; ++i) { lo[i] = acc[mt][nb][hb * 8 + i]; hi[i] = acc[mt][nb][hb * 8 + 4 + i]; }
-      pt_finish<MODE>(a, u, tok, half, p0 + tok, split, lo, hi);
-    }
-  }
-}
-
-// The same product for few rows (or narrow tiles), where the weight stream is nearly all there is: the four
-// waves split K, so nothing is shared and nothing is staged; every operand goes straight to registers, D steps
-// of (MT + NB) KB ahead per wave, with no barrier before the partial sums meet in LDS at the end.  At 64 rows gate/up
-// takes 34.3 us this way and 36.8 us with the weights in LDS, Q/K/V 26.0 and 27.5 (both in 192 workgroups); deeper
-// look-ahead (D = 12) is slower (37.3 us).  A CU's own fetches set the time, so `upt` lets the host make the tiles narrower
-// than 32 NB columns where that occupies CUs that would have none: Q/K/V of 50 rows 28.4 us in 192 tiles of 64
-// columns, 23.4 in 256 of 48; what is left out of a tile reads as zero, without traffic.
-#define PS_LDS_BYTES(MT, NB) (4 * ((MT) < 2 ? 1 : 2) * (NB) * 4096)
-template <int MODE, int MT, int NB, int D, bool WNT>
-__global__ __launch_bounds__(PT_THREADS, 1) void pf_stream_kernel(TileArgs a) {
-  static_assert(D * (MT + NB) < 64, "vmcnt is a 6-bit counter");
-  extern __shared__ __attribute__((aligned(16))) float ps_lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r = lane & 31, half = lane >> 5;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int run = (slot / a.mtiles) * 8 + xcd, m0 = (slot % a.mtiles) * (32 * MT);
-  const int n = a.st->n_prompt, p0 = a.st->pos;
-  if (run >= a.ctiles * a.ks || m0 >= n) return;
-  const int ct = run / a.ks, split = run - ct * a.ks;
-  const int ksteps = (a.K + 31) >> 5, units = skinny_units(MODE, a.N), upad = min(pt_units(MODE, a.N), (ct + 1) * a.upt), u0 = ct * a.upt;
-  // K range of this wave in 16-wide steps
-  const int parts = 4 * a.ks, per = (ksteps + parts - 1) / parts * 2;
-  const int k_begin = (split * 4 + wave) * per, k_end = min(k_begin + per, 2 * ksteps);
-  const unsigned wbytes = (unsigned)max(min(units - u0, a.upt), 0) * ksteps * 1024u;
-  const unsigned astep = (unsigned)a.tb * 1024u;
-  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<half_t*>(a.Wf + (size_t)u0 * ksteps * 512), 0, wbytes, 0x00027000);
-  const __amdgpu_buffer_rsrc_t ar = __builtin_amdgcn_make_buffer_rsrc(const_cast<half_t*>(a.A), 0, ksteps * astep, 0x00027000);
-  int wv[NB], av[MT];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) wv[j] = (j * 2 + (r >> 4)) * ksteps * 1024 + (half * 16 + (r & 15)) * 16;
-#pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int tok = m0 + i * 32 + r;
-    av[i] = (tok >> 4) * 1024 + (half * 16 + (tok & 15)) * 16 + ((tok & ~15) < n ? 0 : 0x40000000);
-  }
-  auto ld = [](__amdgpu_buffer_rsrc_t rs, int off) { return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0)); };
-  auto ldw = [](__amdgpu_buffer_rsrc_t rs, int off) { return __builtin_bit_cast(h8, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, WNT ? 2 : 0)); };
-  h8 fa[D][MT], fw[D][NB];
-  f16v acc[MT][NB];
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  auto issue = [&](int k16, h8 (&A)[MT], h8 (&W)[NB]) {
-    const bool in = k16 < k_end;
-    const int wo = in ? k16 * 512 : 0x40000000;                                     // past the range: reads zero
-    const int ao = in ? (k16 >> 1) * (int)astep + (k16 & 1) * 512 : 0x20000000;
-#pragma unroll
-    for (int j = 0; j < NB; ++j) W[j] = ldw(wr, wv[j] + wo);
-#pragma unroll
-    for (int i = 0; i < MT; ++i) A[i] = ld(ar, av[i] + ao);
-  };
-#pragma unroll
-  for (int d = 0; d < D; ++d) issue(k_begin + d, fa[d], fw[d]);
-  __builtin_amdgcn_sched_barrier(0);
-  for (int k = k_begin; k < k_end; k += D) {
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fw[d][j], fa[d][i], acc[i][j], 0, 0, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      issue(k + d + D, fa[d], fw[d]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  // the waves' partial sums meet in LDS, two row blocks at a time; a wave finishes every fourth 16-row block
-  constexpr int MR = MT < 2 ? 1 : 2;                 // row blocks per round
-#pragma unroll
-  for (int i0 = 0; i0 < MT; i0 += MR) {
-    if (m0 + i0 * 32 >= n) break;
-    if (i0) __syncthreads();
-#pragma unroll
-    for (int i = 0; i < MR; ++i) {
-      if (i0 + i >= MT) continue;
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const f16v& v = acc[i0 + i][j];
-          *reinterpret_cast<f4*>(ps_lds + (((wave * MR + i) * NB + j) * 4 + e) * 256 + lane * 4) =
-              f4{v[4 * e], v[4 * e + 1], v[4 * e + 2], v[4 * e + 3]};
-        }
-    }
-    __syncthreads();
-    for (int h = wave; h < MR * NB * 2; h += 4) {
-      const int i = h / (NB * 2), ub = h - i * (NB * 2), u = u0 + ub, tok = m0 + (i0 + i) * 32 + r;
-      if (u >= upad || tok >= n || i0 + i >= MT) continue;
-      f4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const float* src = ps_lds + (((w * MR + i) * NB + (ub >> 1)) * 4 + (ub & 1) * 2) * 256 + lane * 4;
-        lo += *reinterpret_cast<const f4*>(src);
-        hi += *reinterpret_cast<const f4*>(src + 256);
-      }
       pt_finish<MODE>(a, u, tok, half, p0 + tok, split, lo, hi);
     }
   }
