@@ -304,8 +304,12 @@ int ll_dbg_gemm_slice_count(int32_t N, int32_t K, int32_t nmat, int32_t rows, in
 /* The same for the projections that read the weight copy (default; prompts of more than 32 tokens).  kind: 0 = Q/K/V
  * (N = K = d_model), 1 = O or down (N = d_model), 2 = gate/up (N = ffn_hidden); rows: a prompt bucket (64, 128, 192,
  * 256, 384, 512 or 1024).  out6 = { row tiles, column tiles, 16-row weight blocks per column tile, K pieces, 32-wide K
- * steps per stage of the LDS ring (0: no ring, the waves split K), workgroups launched }. */
+ * steps per stage of the LDS ring, workgroups launched }. */
 int ll_dbg_tile_plan(int32_t kind, int32_t N, int32_t K, int32_t rows, int32_t *out6);
+
+/* Order in which a batched step's attention takes its slots (host arithmetic): order[i] = slot of grid row i, for slots
+ * with pos[] cached positions (active[] = 0: free) and per_round slots to a round of workgroups over the CUs. */
+int ll_dbg_batch_order(const int32_t *pos, const int32_t *active, int32_t rows, int32_t per_round, int32_t *order);
 
 /* Logits [vocab] of the most recent prefill/decode step, copied to the host. */
 int ll_dbg_get_logits(float *host_out);

@@ -30,7 +30,7 @@ EXPORTS = ("ll_workspace_bytes", "ll_init", "ll_prefill", "ll_prefill_static", "
            "ll_set_sampling", "ll_shutdown", "ll_max_prompt", "ll_position", "ll_decode_mode", "ll_last_error", "ll_dbg_get_logits",
            "ll_batch_pool_bytes", "ll_batch_open", "ll_batch_add", "ll_batch_step", "ll_batch_remove", "ll_batch_close",
            "ll_batch_dbg_get_logits", "ll_batch_dbg_force_next_token", "ll_batch_dbg_time_steps",
-           "ll_dbg_get_hidden", "ll_dbg_set_spin_limit", "ll_dbg_give_up_at", "ll_dbg_small_plan", "ll_dbg_graph_stats", "ll_dbg_gemm_plan", "ll_dbg_gemm_slice_count", "ll_dbg_tile_plan", "ll_dbg_force_next_token", "ll_dbg_get_kv", "ll_dbg_profile_decode",
+           "ll_dbg_get_hidden", "ll_dbg_set_spin_limit", "ll_dbg_give_up_at", "ll_dbg_small_plan", "ll_dbg_graph_stats", "ll_dbg_gemm_plan", "ll_dbg_gemm_slice_count", "ll_dbg_tile_plan", "ll_dbg_batch_order", "ll_dbg_force_next_token", "ll_dbg_get_kv", "ll_dbg_profile_decode",
            "ll_dbg_time_decode", "ll_dbg_time_kernel_class", "ll_dbg_stream_copy", "ll_dbg_stream_read", "ll_dbg_poison_scratch", "ll_dbg_trace_decode")
 
 
@@ -109,6 +109,8 @@ def load():
     L.ll_batch_dbg_force_next_token.argtypes = [C.c_int32, C.c_int32]
     L.ll_batch_dbg_time_steps.restype = C.c_int
     L.ll_batch_dbg_time_steps.argtypes = [C.c_int32, C.POINTER(C.c_float)]
+    L.ll_dbg_batch_order.restype = C.c_int
+    L.ll_dbg_batch_order.argtypes = [C.POINTER(C.c_int32)] * 2 + [C.c_int32] * 2 + [C.POINTER(C.c_int32)]
     L.ll_dbg_tile_plan.restype = C.c_int
     L.ll_dbg_tile_plan.argtypes = [C.c_int32] * 4 + [C.POINTER(C.c_int32)]
     L.ll_dbg_gemm_plan.restype = C.c_int
@@ -198,6 +200,15 @@ def ll_dbg_tile_plan(kind, N, K, rows):
     out = (C.c_int32 * 6)()
     _check(load().ll_dbg_tile_plan(kind, N, K, rows, out))
     return dict(zip(("row_tiles", "col_tiles", "blocks", "pieces", "stage_steps", "workgroups"), out))
+
+
+def ll_dbg_batch_order(pos, active, per_round):
+    """Slots in the order in which a batched step's attention takes them (host arithmetic, no GPU needed)."""
+    n = len(pos)
+    arr = C.c_int32 * n
+    out = arr()
+    _check(load().ll_dbg_batch_order(arr(*pos), arr(*active), n, per_round, out))
+    return list(out)
 
 
 def ll_dbg_small_plan(cfg, pos, steps, flags=0):

@@ -1413,6 +1413,7 @@ void enqueue_batch_step(Instance* I, hipStream_t s) {
 // The slots' state and the page-table rows of slots first .. first + count - 1, host mirrors -> device (st: see the kernel)
 int push_batch_state(Instance* I, int first, int count, const DevState* st = nullptr) {
   Batch* B = I->batch;
+  bt_order(B->h_state->pos, B->h_state->active, B->rows, std::max(1, num_cus() / I->cfg.n_heads), B->h_state->order);
   hipLaunchKernelGGL(bt_push_kernel, dim3(count), dim3(LL_WG), 0, I->stream, (const int*)B->d_state_src,
                      (int*)B->at<BatchState>(B->L.state), B->d_table_src, B->at<int>(B->L.page_table), B->L.pt_stride, first, st);
   HIPCHK(hipGetLastError());
@@ -2171,6 +2172,13 @@ int ll_dbg_tile_plan(int32_t kind, int32_t N, int32_t K, int32_t rows, int32_t* 
   const TilePlan p = tile_plan(kind, N, K, rows);
   out6[0] = p.mtiles; out6[1] = p.ctiles; out6[2] = p.upt; out6[3] = p.ks;
   out6[4] = p.shape.s32; out6[5] = p.grid();
+  return LL_OK;
+}
+
+int ll_dbg_batch_order(const int32_t* pos, const int32_t* active, int32_t rows, int32_t per_round, int32_t* order) {
+  if (!pos || !active || !order || rows < 1 || rows > BT_MAX_BATCH || per_round < 1)
+    return fail(LL_E_BAD_ARG, "ll_dbg_batch_order: bad argument");
+  bt_order(pos, active, rows, per_round, order);
   return LL_OK;
 }
 
