@@ -185,6 +185,7 @@ constexpr int tile_rows(const TileShape& t) { return 32 * t.wm * t.mt; }
 //  * a residual projection whose K loop can be cut into more pieces takes wider tiles (down at 512 rows: 45 us in 4
 //    pieces of 128 columns, 62 us in 2 of 64; the O projection of the 7B shape is better off with fewer slices,
 //    24.0 us in 2 pieces and 23.3 in 4, which the norm behind it has to add up).
+//    At 250 rows O in 2 pieces of 128 x 64 takes as long as in 4 of 256 x 64 (16.5 and 16.2 us), and the norm half a us less.
 // Each line is the fastest of those measured at the 7B shape (prefill_tile.h has the times), stages of 4 K steps in rings of
 // 3 wherever the registers hold.
 constexpr TileShape tile_shape(int mode, int Mb, bool alt) {
@@ -202,7 +203,7 @@ constexpr TileShape tile_shape(int mode, int Mb, bool alt) {
   if (Mb <= 64) return TileShape{2, 2, 1, 2, 4, 3, true};
   if (Mb <= 128) return TileShape{2, 2, 2, 2, 4, 3, true};
   if (Mb <= 192) return TileShape{2, 2, 3, 2, 4, 3, true};
-  if (Mb <= 256) return TileShape{4, 1, 2, 2, 4, 3, true};
+  if (Mb <= 256) return alt ? TileShape{4, 1, 2, 2, 4, 3, true} : TileShape{2, 2, 2, 2, 4, 3, false};
   if (Mb <= 384) return alt ? TileShape{4, 1, 3, 2, 4, 3, true} : TileShape{2, 2, 3, 2, 4, 3, false};
   if (Mb <= 512 && !alt) return TileShape{4, 1, 2, 2, 4, 3, false};
   return TileShape{4, 1, 2, 4, 2, 3, false};
@@ -997,6 +998,14 @@ void launch_attn(Instance* I, hipStream_t s, const PfBuffers& B, int l, int Mb, 
   else launch_attn_hd<64>(I, s, B, l, Mb, tb);
 }
 
+// RMSNorm of a prefill's rows in front of layer l's attention block or FFN; the first one of a prompt gathers the embedding
+void launch_norm(Instance* I, hipStream_t s, const PfBuffers& B, const void* gain, int Mb, bool first, const float* part,
+                 const SliceMap& map, int tb) {
+  const ll_config& c = I->cfg;
+  hipLaunchKernelGGL(first ? pf_rmsnorm_kernel<true> : pf_rmsnorm_kernel<false>, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, B.X,
+                     (const half_t*)I->w.tok_emb, B.tokens, (const half_t*)gain, B.Xn, c.d_model, c.rms_eps, I->state(), part, map, tb);
+}
+
 // Prompts (or chunks) of 33..1024 rows with the weight copy: per layer the norm (which adds the previous residual
 // projection's slices to X), Q/K/V with RoPE and cache write, attention, O, norm, gate/up with SwiGLU, down.
 void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb, bool with_head) {
@@ -1008,13 +1017,10 @@ void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb
     m.nslabs = ks; m.quota = 1; m.ntiles = (d + 255) / 256; m.N = d; m.slice_floats = (size_t)Mb * d;
     return m;
   };
-  hipLaunchKernelGGL(pf_embed_kernel, dim3(Mb, (d + LL_WG * 8 - 1) / (LL_WG * 8)), dim3(LL_WG), 0, s,
-                     (const half_t*)I->w.tok_emb, B.tokens, I->state(), B.X, d);
   const float* part = nullptr;                     // slices still to be added to X
   for (int l = 0; l < c.n_layers; ++l) {
     const ll_layer_weights& W = I->layers[l];
-    hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, B.X, (const half_t*)W.attn_norm,
-                       B.Xn, d, c.rms_eps, I->state(), part, slices(ks_down), tb);
+    launch_norm(I, s, B, W.attn_norm, Mb, l == 0, part, slices(ks_down), tb);
     TileArgs a{};
     a.st = I->state(); a.head_dim = c.head_dim; a.max_seq = c.max_seq;
     a.A = B.Xn; a.Wf = I->wfrag(l, I->L.wf_qkv); a.N = d; a.K = d;
@@ -1025,8 +1031,7 @@ void enqueue_prefill_tile(Instance* I, hipStream_t s, const PfBuffers& B, int Mb
     a.C = B.part; a.slice_floats = (size_t)Mb * d;
     a.A = B.O; a.Wf = I->wfrag(l, I->L.wf_o);
     launch_tile<SK_RES>(s, a, Mb);
-    hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, B.X, (const half_t*)W.ffn_norm,
-                       B.Xn, d, c.rms_eps, I->state(), B.part, slices(ks_o), tb);
+    launch_norm(I, s, B, W.ffn_norm, Mb, false, B.part, slices(ks_o), tb);
     a.A = B.Xn; a.Wf = I->wfrag(l, I->L.wf_gu); a.N = F; a.Hout = B.H;
     launch_tile<SK_GATEUP>(s, a, Mb);
     a.A = B.H; a.Wf = I->wfrag(l, I->L.wf_down); a.N = d; a.K = F;
@@ -1043,17 +1048,13 @@ void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) 
   if (has_copy(I->cfg)) return enqueue_prefill_tile(I, s, B, Mb, with_head);
   const ll_config& c = I->cfg;
   const int d = c.d_model, F = c.ffn_hidden;
-  float* X = B.X;
   half_t *Xn = B.Xn, *Qh = B.Q, *Oh = B.O, *Hm = B.H;
   const float* P = B.part;                         // slices of the GEMM that ran last
-  hipLaunchKernelGGL(pf_embed_kernel, dim3(Mb, (d + LL_WG * 8 - 1) / (LL_WG * 8)), dim3(LL_WG), 0, s,
-                     (const half_t*)I->w.tok_emb, B.tokens, I->state(), X, d);
   SliceMap res{};                                  // the residual GEMM whose slices are still to be added to X
   const float* res_part = nullptr;
   for (int l = 0; l < c.n_layers; ++l) {
     const ll_layer_weights& W = I->layers[l];
-    hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, X, (const half_t*)W.attn_norm,
-                       Xn, d, c.rms_eps, I->state(), res_part, res, 0);
+    launch_norm(I, s, B, W.attn_norm, Mb, l == 0, res_part, res, 0);
     const SliceMap qkv = launch_gemm(I, s, B, Xn, W.wq, W.wk, W.wv, 3, 3 * d, d, d, Mb);
     hipLaunchKernelGGL(pf_rope_kv_kernel, dim3(Mb, (d / 8 + LL_WG - 1) / LL_WG), dim3(LL_WG), 0, s, P, qkv,
                        I->at<float2>(I->L.rope), I->state(), Qh, I->kcache(l), I->vcache(l), d,
@@ -1062,8 +1063,7 @@ void enqueue_prefill(Instance* I, hipStream_t s, int Mb, bool with_head = true) 
     launch_attn(I, s, B, l, Mb, 0);
     res = launch_gemm(I, s, B, Oh, W.wo, nullptr, nullptr, 1, d, d, d, Mb);
     res_part = P;
-    hipLaunchKernelGGL(pf_rmsnorm_kernel, dim3(Mb), dim3(PF_NORM_THREADS), 0, s, X, (const half_t*)W.ffn_norm,
-                       Xn, d, c.rms_eps, I->state(), res_part, res, 0);
+    launch_norm(I, s, B, W.ffn_norm, Mb, false, res_part, res, 0);
     const SliceMap gu = launch_gemm(I, s, B, Xn, W.w_gate, W.w_up, nullptr, 2, 2 * F, F, d, Mb);
     hipLaunchKernelGGL(pf_swiglu_kernel, dim3(Mb, (F + LL_WG * 4 - 1) / (LL_WG * 4)), dim3(LL_WG), 0,
                        s, P, gu, I->state(), Hm, F);

@@ -25,25 +25,6 @@ __global__ __launch_bounds__(LL_WG) void pf_stage_kernel(const int* __restrict__
   if (zeros && tid < 64) zeros[tid] = 0;
 }
 
-// X[r] = float(E[tokens[r]]) for r < n, 0 otherwise.  grid = (Mb, ceil(d / 2048))
-__global__ __launch_bounds__(LL_WG) void pf_embed_kernel(const half_t* __restrict__ emb,
-                                                         const int* __restrict__ tokens,
-                                                         const DevState* __restrict__ st,
-                                                         float* __restrict__ X, int d) {
-  const int r = blockIdx.x;
-  const int i = (blockIdx.y * LL_WG + threadIdx.x) * 8;
-  if (i >= d) return;
-  float* xr = X + (size_t)r * d + i;
-  if (r < st->n_prompt) {
-    const h8 e = *reinterpret_cast<const h8*>(emb + (size_t)tokens[r] * d + i);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) xr[j] = (float)e[j];
-  } else {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) xr[j] = 0.f;
-  }
-}
-
 // Sum of np split-K slices at p (slice stride in floats), four loads in flight at a time.
 __device__ __forceinline__ f4 pf_slice_sum(const float* p, int np, size_t slice_floats) {
   f4 v = {0.f, 0.f, 0.f, 0.f};
@@ -60,13 +41,20 @@ __device__ __forceinline__ f4 pf_slice_sum(const float* p, int np, size_t slice_
 }
 
 // Row-wise RMSNorm of the fp32 residual stream into fp16 GEMM operands, one
-// 1024-thread workgroup per row.  The residual GEMM in front of it may have left
-// its result as np split-K slices ([np][rows][d] at part): they are added to X
+// 1024-thread workgroup per row.  FIRST: the row is the embedding of token r, stored to X as well.  Otherwise the residual
+// GEMM in front of it may have left its result as np split-K slices ([np][rows][d] at part): they are added to X
 // here, X is stored back, and the norm is taken of the sum.  Rows past the prompt
 // give zero operands.  frag_tb != 0 writes the operands in the short-prompt
 // kernels' fragment-major layout.
+// Everything it reads is requested up front and kept in registers, PF_NORM_CHUNKS pieces of a thread (d_model up to 12288, more
+// than any instance has).  At 50 rows it is one memory round trip and a barrier long (5.0 us a launch), at 500 the slices'
+// way between XCDs (11.2, 4 TB/s); the first one takes 4.6 / 6.4 / 7.6 us at 50 / 250 / 500 rows where a gather kernel and a
+// norm took 5.5 / 9.5 / 12.8.
 #define PF_NORM_THREADS 1024
-__global__ __launch_bounds__(PF_NORM_THREADS) void pf_rmsnorm_kernel(float* __restrict__ X,
+#define PF_NORM_CHUNKS 3
+template <bool FIRST>
+__global__ __launch_bounds__(PF_NORM_THREADS) void pf_rmsnorm_kernel(float* __restrict__ X, const half_t* __restrict__ emb,
+                                                                     const int* __restrict__ tokens,
                                                                      const half_t* __restrict__ gain,
                                                                      half_t* __restrict__ Xn, int d, float eps,
                                                                      const DevState* __restrict__ st,
@@ -74,37 +62,52 @@ __global__ __launch_bounds__(PF_NORM_THREADS) void pf_rmsnorm_kernel(float* __re
                                                                      int frag_tb) {
   __shared__ float red[PF_NORM_THREADS / 64];
   const int r = blockIdx.x, tid = threadIdx.x;
-  if (r >= st->n_prompt) {
+  const int n = st->n_prompt, token = FIRST ? tokens[r] : 0;      // (an id is staged for every row of the bucket)
+  auto at = [&](int c) { return (c * PF_NORM_THREADS + tid) * 4; };
+  if (r >= n) {
     const h4 zero = {0, 0, 0, 0};
-    for (int i = tid * 4; i < d; i += PF_NORM_THREADS * 4)
-      *reinterpret_cast<h4*>(Xn + act_offset(r, i, d, frag_tb)) = zero;
+#pragma unroll
+    for (int c = 0; c < PF_NORM_CHUNKS; ++c)
+      if (at(c) < d) *reinterpret_cast<h4*>(Xn + act_offset(r, at(c), d, frag_tb)) = zero;
     return;
   }
   float* xr = X + (size_t)r * d;
   const float* pr = part + (size_t)r * d;
+  f4 v[PF_NORM_CHUNKS];
+  h4 g[PF_NORM_CHUNKS];
   float ss = 0.f;
-  for (int i = tid * 4; i < d; i += PF_NORM_THREADS * 4) {
-    f4 v = *reinterpret_cast<const f4*>(xr + i);
-    if (part) {
-      v += pf_slice_sum(pr + i, slice_count(map, i), map.slice_floats);
-      *reinterpret_cast<f4*>(xr + i) = v;
+#pragma unroll
+  for (int c = 0; c < PF_NORM_CHUNKS; ++c) {
+    const int i = at(c);
+    if (i >= d) continue;
+    g[c] = *as_global(reinterpret_cast<const h4*>(gain + i));
+    if constexpr (FIRST) {
+      const h4 e = *as_global(reinterpret_cast<const h4*>(emb + (size_t)token * d + i));
+      v[c] = f4{(float)e[0], (float)e[1], (float)e[2], (float)e[3]};
+    } else {
+      v[c] = *as_global(reinterpret_cast<const f4*>(xr + i));
+      if (part) v[c] += pf_slice_sum(pr + i, map.quota == 1 ? map.nslabs : slice_count(map, i), map.slice_floats);
     }
-    ss += v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
+    if (FIRST || part) *as_global(reinterpret_cast<f4*>(xr + i)) = v[c];
+    ss += v[c][0] * v[c][0] + v[c][1] * v[c][1] + v[c][2] * v[c][2] + v[c][3] * v[c][3];
   }
   ss = wave_sum(ss);
   if ((tid & 63) == 0) red[tid >> 6] = ss;
-  __syncthreads();
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();                       // (nobody waits for the rows' way back to memory here)
+  asm volatile("" ::: "memory");
   float tot = 0.f;
 #pragma unroll
   for (int w = 0; w < PF_NORM_THREADS / 64; ++w) tot += red[w];
   const float inv = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int i = tid * 4; i < d; i += PF_NORM_THREADS * 4) {
-    const f4 v = *reinterpret_cast<const f4*>(xr + i);      // this thread's own stores of the loop above
-    const h4 g = *reinterpret_cast<const h4*>(gain + i);
+#pragma unroll
+  for (int c = 0; c < PF_NORM_CHUNKS; ++c) {
+    const int i = at(c);
+    if (i >= d) continue;
     h4 o;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = (half_t)(v[j] * inv * (float)g[j]);
-    *reinterpret_cast<h4*>(Xn + act_offset(r, i, d, frag_tb)) = o;
+    for (int j = 0; j < 4; ++j) o[j] = (half_t)(v[c][j] * inv * (float)g[c][j]);
+    *as_global(reinterpret_cast<h4*>(Xn + act_offset(r, i, d, frag_tb))) = o;
   }
 }
 
