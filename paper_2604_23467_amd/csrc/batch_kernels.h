@@ -182,25 +182,28 @@ __global__ __launch_bounds__(NT, 4) void bt_attn_kernel(
 
 // Token of every slot and the slots' state advance: greedy (lowest index among equal maxima), or
 // the stochastic selection of sample_kernels.h with the slot's own draw index, so a sequence draws
-// the same stream in a batch as alone.  grid = rows of the step, SMP_THREADS threads, SMP_Z_WORDS
-// words of dynamic LDS; out = device-visible host memory, -1 for free slots.
+// the same stream in a batch as alone.  grid = rows of the step, SMP_THREADS threads, SMP_Z_BYTES(PER)
+// of dynamic LDS; out = device-visible host memory, -1 for free slots.
+template <int PER>
 __global__ __launch_bounds__(SMP_THREADS) void bt_select_kernel(const float* __restrict__ logits, int vocab,
                                                                 const SampleCfg* __restrict__ cfg,
                                                                 BatchState* bs, int* out) {
   extern __shared__ float bt_z[];
-  __shared__ float sv[SMP_THREADS];
   __shared__ int si[SMP_THREADS];
   __shared__ uint32_t sk[SMP_THREADS];
   __shared__ float red[2 * 3 * (SMP_THREADS / 64)];
   __shared__ int found;
   const int b = blockIdx.x, tid = threadIdx.x;
-  if (!bs->active[b]) {
+  const float* row = logits + (size_t)b * vocab;
+  // (requested together: see sample_kernel)
+  const float inv_temp = cfg->inv_temp, logit0 = row[min(tid, vocab - 1)];
+  const int active = bs->active[b], pos = bs->pos[b], steps = bs->steps[b];
+  if (!active) {
     if (tid == 0) out[b] = -1;
     return;
   }
-  const float* row = logits + (size_t)b * vocab;
   int tok;
-  if (cfg->inv_temp == 0.f || vocab > SMP_MAX_VOCAB) {
+  if (inv_temp == 0.f || vocab > SMP_THREADS * PER) {
     float bv = -INFINITY;
     int bi = 0x7fffffff;
     for (int i = tid * 4; i < vocab; i += SMP_THREADS * 4) {     // vocab % 16 == 0 (checked when the batch is opened)
@@ -209,26 +212,15 @@ __global__ __launch_bounds__(SMP_THREADS) void bt_select_kernel(const float* __r
       for (int e = 0; e < 4; ++e)
         if (v[e] > bv) { bv = v[e]; bi = i + e; }                // indices ascend: the first maximum stays
     }
-    sv[tid] = bv;
-    si[tid] = bi;
-    __syncthreads();
-    for (int off = SMP_THREADS / 2; off > 0; off >>= 1) {
-      if (tid < off) {
-        const float v = sv[tid + off];
-        const int ix = si[tid + off];
-        if (v > sv[tid] || (v == sv[tid] && ix < si[tid])) { sv[tid] = v; si[tid] = ix; }
-      }
-      __syncthreads();
-    }
-    tok = si[0];
+    tok = smp_block_argmax(bv, bi, red, si);
     if (tok == 0x7fffffff) tok = 0;          // every logit NaN: still a valid id
   } else {
-    tok = smp_draw_token(row, vocab, cfg, (uint32_t)bs->steps[b], bt_z, si, sk, red, &found);
+    tok = smp_draw_token<PER>(row, vocab, cfg, (uint32_t)steps, logit0, bt_z, si, sk, red, &found);
   }
   if (tid == 0) {
     bs->next_token[b] = tok;
-    bs->pos[b] = bs->pos[b] + 1;
-    bs->steps[b] = bs->steps[b] + 1;
+    bs->pos[b] = pos + 1;
+    bs->steps[b] = steps + 1;
     out[b] = tok;
   }
 }

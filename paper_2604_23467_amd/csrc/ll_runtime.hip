@@ -660,10 +660,15 @@ void launch_down_row(Instance* I, hipStream_t s, int l) {
 void enqueue_select(Instance* I, hipStream_t s, const float* amax_val, const int* amax_idx, int nparts, const float* logits,
                     int prefill) {
   const ll_config& c = I->cfg;
-  hipLaunchKernelGGL(sample_kernel, dim3(1), dim3(SMP_THREADS), SMP_Z_WORDS * 4, s, amax_val, amax_idx, nparts, logits,
-                     c.vocab, I->at<SampleCfg>(I->L.sample_cfg), I->state(), I->dev_ring, I->ring_size, prefill,
-                     (const half_t*)I->w.tok_emb, I->use_mega ? nullptr : I->at<float>(I->L.x),
-                     I->at<float>(I->L.x_keep), c.d_model);
+  auto go = [&](auto kernel, int lds) {
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(SMP_THREADS), lds, s, amax_val, amax_idx, nparts, logits,
+                       c.vocab, I->at<SampleCfg>(I->L.sample_cfg), I->state(), I->dev_ring, I->ring_size, prefill,
+                       (const half_t*)I->w.tok_emb, I->use_mega ? nullptr : I->at<float>(I->L.x),
+                       I->at<float>(I->L.x_keep), c.d_model);
+  };
+  const int per = smp_per(c.vocab);
+  per == 1 ? go(sample_kernel<1>, SMP_Z_BYTES(1)) : per == 8 ? go(sample_kernel<8>, SMP_Z_BYTES(8))
+                                                  : go(sample_kernel<SMP_PER>, SMP_Z_BYTES(SMP_PER));
 }
 
 // final RMSNorm + LM head + argmax + state advance on the row in x, shared by decode and prefill
@@ -1406,8 +1411,13 @@ void enqueue_batch_step(Instance* I, hipStream_t s) {
     a.Wf = I->wfrag_lm();
     launch_skinny<SK_LOGITS>(s, P, a, Mb);
   }
-  hipLaunchKernelGGL(bt_select_kernel, dim3(Mb), dim3(SMP_THREADS), SMP_Z_WORDS * 4, s, B->at<float>(B->L.logits),
-                     c.vocab, I->at<SampleCfg>(I->L.sample_cfg), bs, B->d_out);
+  auto select = [&](auto kernel, int lds) {
+    hipLaunchKernelGGL(kernel, dim3(Mb), dim3(SMP_THREADS), lds, s, B->at<float>(B->L.logits), c.vocab,
+                       I->at<SampleCfg>(I->L.sample_cfg), bs, B->d_out);
+  };
+  const int per = smp_per(c.vocab);
+  per == 1 ? select(bt_select_kernel<1>, SMP_Z_BYTES(1)) : per == 8 ? select(bt_select_kernel<8>, SMP_Z_BYTES(8))
+                                                         : select(bt_select_kernel<SMP_PER>, SMP_Z_BYTES(SMP_PER));
 }
 
 // The slots' state and the page-table rows of slots first .. first + count - 1, host mirrors -> device (st: see the kernel)
@@ -1524,11 +1534,11 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
   if (!hip_or_bail(hipMemset(I->at<char>(L.ao_sync), 0, 64 * 4), "hipMemset(sync)")) return bail(rc);
   if (!hip_or_bail(hipMemset(I->at<char>(L.sample_cfg), 0, sizeof(SampleCfg)), "hipMemset(sampling)"))
     return bail(rc);                                           // inv_temp = 0: greedy
-  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&sample_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMP_Z_WORDS * 4),
+  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&sample_kernel<SMP_PER>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMP_Z_BYTES(SMP_PER)),
                    "hipFuncSetAttribute(sample)")) return bail(rc);
-  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&bt_select_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMP_Z_WORDS * 4),
+  if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&bt_select_kernel<SMP_PER>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMP_Z_BYTES(SMP_PER)),
                    "hipFuncSetAttribute(batch select)")) return bail(rc);
   if (!hip_or_bail(hipFuncSetAttribute(reinterpret_cast<const void*>(&pf_gemm_kernel<128, 3, 2, 4, 64>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, PF_GEMM_LDS_BYTES(128, 3, 64)),

@@ -25,7 +25,9 @@
 #define SMP_THREADS 1024
 #define SMP_PER 32                               // consecutive tokens per thread
 #define SMP_MAX_VOCAB (SMP_THREADS * SMP_PER)
-#define SMP_Z_WORDS (SMP_THREADS * (SMP_PER + 1))   // dynamic LDS of sample_kernel, in 4-byte words
+// tokens per thread that a selection kernel is built for, and its dynamic LDS
+inline int smp_per(int vocab) { return vocab <= SMP_THREADS ? 1 : vocab <= SMP_THREADS * 8 ? 8 : SMP_PER; }
+#define SMP_Z_BYTES(PER) (((PER) == 1 ? SMP_THREADS : SMP_THREADS / 32 * 33 * (PER)) * 4)
 
 struct SampleCfg {
   float inv_temp;      // float(1 / T); 0 selects greedy argmax
@@ -374,30 +376,34 @@ __device__ __forceinline__ int smp_ranked_pick(const uint32_t* sk, const int* si
 }
 
 // One draw from logits[0 .. vocab) by a workgroup of SMP_THREADS threads (all of them call this;
-// vocab <= SMP_MAX_VOCAB, cfg->inv_temp != 0).  smp_z: SMP_Z_WORDS words of LDS; si, sk: SMP_THREADS
-// words each; red: 6 words per wave; found: one word.  Returns the token in every thread.
+// vocab <= SMP_THREADS * PER, cfg->inv_temp != 0).  smp_z: SMP_Z_BYTES(PER) of LDS; si, sk: SMP_THREADS
+// words each; red: 6 words per wave; found: one word; logit0: logits[thread], fetched by the caller.  Returns the token in
+// every thread.
+template <int PER>
 __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, int vocab,
-                                              const SampleCfg* __restrict__ cfg, uint32_t draw_index,
-                                              float* smp_z, int* si, uint32_t* sk, float* red, int* found) {
+                                           const SampleCfg* __restrict__ cfg, uint32_t draw_index, float logit0,
+                                           float* smp_z, int* si, uint32_t* sk, float* red, int* found) {
   const int tid = threadIdx.x;
   const float inv_temp = cfg->inv_temp;
   int phase = 0;
   int tok;
   // Thread t holds tokens t * per .. + per - 1: every thread has some, whatever the vocabulary (with 32 each, a
-  // vocabulary of 1024 sat in 32 threads, too few for the bound of (1)).  The logits are
+  // vocabulary of 1024 sat in 32 threads, too few for the bound of (1)).  More than one each: the logits are
   // read once, coalesced, into LDS rows of 32 padded to 33 words, from which a thread takes its share almost without
   // bank conflicts (read straight from global memory, every load instruction of a wave would touch 64 cache lines).
-  const int per = (vocab + SMP_THREADS - 1) / SMP_THREADS;
-  for (int i = tid; i < vocab; i += SMP_THREADS) smp_z[i + (i >> 5)] = logits[i];
-  __syncthreads();
+  const int per = PER == 1 ? 1 : (vocab + SMP_THREADS - 1) / SMP_THREADS;
+  if (PER > 1) {
+    for (int i = tid; i < vocab; i += SMP_THREADS) smp_z[i + (i >> 5)] = logits[i];
+    __syncthreads();
+  }
   const int base = tid * per;
-  uint32_t key[SMP_PER];
+  uint32_t key[PER];
   float zmax = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < SMP_PER; ++j) {
+  for (int j = 0; j < PER; ++j) {
     const int i = base + j;
     const bool have = j < per && i < vocab;
-    const float z = have ? __fmul_rn(smp_z[i + (i >> 5)], inv_temp) + 0.f : 0.f;   // + 0: -0 and +0 are one value
+    const float z = have ? __fmul_rn(PER == 1 ? logit0 : smp_z[i + (i >> 5)], inv_temp) + 0.f : 0.f;   // + 0: -0 and +0 are one value
     key[j] = have ? order_key(z) : 0u;
     if (have) zmax = fmaxf(zmax, z);
   }
@@ -419,7 +425,7 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
   if (top_k > 0 && top_k <= SMP_THREADS) {
     uint32_t tmax[1] = {0u};
 #pragma unroll
-    for (int j = 0; j < SMP_PER; ++j) tmax[0] = key[j] > tmax[0] ? key[j] : tmax[0];
+    for (int j = 0; j < PER; ++j) tmax[0] = key[j] > tmax[0] ? key[j] : tmax[0];
     uint32_t bound = 0u;
     // candidates to go on with: as many as the smallest split of the ranking that holds top_k of them
     const int enough = top_k <= SMP_THREADS / 4 ? SMP_THREADS / 4 : SMP_THREADS / 2;
@@ -427,7 +433,7 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
     auto count_reach = [&]() {
       int reach = 0;
 #pragma unroll
-      for (int j = 0; j < SMP_PER; ++j) reach += key[j] >= bound;
+      for (int j = 0; j < PER; ++j) reach += key[j] >= bound;
       float all;
       at = (int)(smp_block_scan_excl((float)reach, red, phase, &all) + 0.5f);
       nreach = (int)(all + 0.5f);
@@ -463,7 +469,7 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
     }
     if (bound != 0u && nreach <= SMP_THREADS) {
 #pragma unroll
-      for (int j = 0; j < SMP_PER; ++j) {
+      for (int j = 0; j < PER; ++j) {
         if (key[j] >= bound) {
           sk[at] = key[j];
           si[at] = base + j;
@@ -481,20 +487,45 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
       tok = smp_nucleus_and_draw<1>(k1, e1, id, cfg->top_p, u, red, phase, found);
       done = true;
     }
-  } else if (per == 1) {            // one token per thread: the cuts and the draw need one slot, not 32
-    uint32_t k1[1] = {key[0]};
-    float e1[1];
-    smp_apply_topk<1>(k1, e1, top_k, zmax, red, phase);
-    tok = smp_nucleus_and_draw<1>(k1, e1, tid, cfg->top_p, u, red, phase, found);
-    done = true;
   }
-  // (2) otherwise: the cut (if any), the nucleus and the draw over all 32 slots per thread
+  // (2) otherwise: the cut (if any), the nucleus and the draw over all slots of a thread
   if (!done) {
-    float e[SMP_PER];
-    smp_apply_topk<SMP_PER>(key, e, top_k, zmax, red, phase);
-    tok = smp_nucleus_and_draw<SMP_PER>(key, e, base, cfg->top_p, u, red, phase, found);
+    float e[PER];
+    smp_apply_topk<PER>(key, e, top_k, zmax, red, phase);
+    tok = smp_nucleus_and_draw<PER>(key, e, base, cfg->top_p, u, red, phase, found);
   }
   return tok;
+}
+
+// Index of the largest value over a workgroup, the lowest index among equals (v: -inf where a thread has none), in every
+// thread: lane-crossing moves inside a wave, and one barrier.  sv, si: a word per wave.  (A tree over LDS takes a
+// barrier per level.)
+__device__ __forceinline__ int smp_block_argmax(float v, int i, float* sv, int* si) {
+  constexpr int NW = SMP_THREADS / 64;
+  const int tid = threadIdx.x;
+  auto over_rows = [](auto x, auto op) {          // the four rows of 16 lanes
+    auto at = [&](int lane) { return __builtin_bit_cast(decltype(x), __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane)); };
+    return op(op(at(0), at(16)), op(at(32), at(48)));
+  };
+  auto big = [](float a, float b) { return fmaxf(a, b); };
+  auto low = [](int a, int b) { return a < b ? a : b; };
+  float top = big(v, dpp_mov<0xB1>(v));
+  top = big(top, dpp_mov<0x4E>(top));
+  top = big(top, dpp_mov<0x141>(top));
+  top = over_rows(big(top, dpp_mov<0x140>(top)), big);
+  int at = v == top ? i : 0x7fffffff;
+  at = low(at, __builtin_amdgcn_update_dpp(0, at, 0xB1, 0xf, 0xf, true));
+  at = low(at, __builtin_amdgcn_update_dpp(0, at, 0x4E, 0xf, 0xf, true));
+  at = low(at, __builtin_amdgcn_update_dpp(0, at, 0x141, 0xf, 0xf, true));
+  at = over_rows(low(at, __builtin_amdgcn_update_dpp(0, at, 0x140, 0xf, 0xf, true)), low);
+  if ((tid & 63) == 0) { sv[tid >> 6] = top; si[tid >> 6] = at; }
+  __syncthreads();
+  top = sv[0];
+  at = si[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w)
+    if (sv[w] > top || (sv[w] == top && si[w] < at)) { top = sv[w]; at = si[w]; }
+  return at;
 }
 
 //   prefill = 1: pos += n_prompt (rows of the last prompt chunk), steps := 1, ring[0] := token (draw index 0)
@@ -503,6 +534,13 @@ __device__ __forceinline__ int smp_draw_token(const float* __restrict__ logits, 
 // decode step, which therefore needs no gather kernel of its own (what x_next held, the final residual
 // stream of the step or of the prompt's last row, is kept in x_keep for the read-back hook); and it reports token -1 to the host
 // when a kernel of the step raised DevState::fault (the device state still advances with a valid id).
+//
+// A slot costs some 15 instructions, used or not, with four waves to a SIMD, and what the 32 of a large vocabulary spill costs
+// every launch: built for up to 1024, 8192 and SMP_MAX_VOCAB tokens (PER = 1, 8, SMP_PER).  A step of a toy model, us, with 32
+// slots for all and loads behind the choice / now: vocabulary 1024 greedy 32.1 / 31.3, top-k 50 39.6 / 36.1, with top-p 0.95
+// 40.0 / 36.6, top-p 0.95 alone 50.3 / 47.5; 4096 33.1 / 32.2, 42.1 / 39.3, 42.6 / 39.6, 79.1 / 56.3; 32000 41.0 / 40.1,
+// 57.8 / 57.1, 58.8 / 58.1, 99.2 / 98.8.
+template <int PER>
 __global__ __launch_bounds__(SMP_THREADS) void sample_kernel(const float* __restrict__ pval,
                                                              const int* __restrict__ pidx, int nparts,
                                                              const float* __restrict__ logits, int vocab,
@@ -511,67 +549,52 @@ __global__ __launch_bounds__(SMP_THREADS) void sample_kernel(const float* __rest
                                                              int prefill, const half_t* __restrict__ emb,
                                                              float* __restrict__ x_next, float* __restrict__ x_keep,
                                                              int d) {
-  extern __shared__ float smp_z[];     // SMP_Z_WORDS words, used by the stochastic path only
-  __shared__ float sv[SMP_THREADS];
+  extern __shared__ float smp_z[];     // SMP_Z_BYTES(PER), used by the stochastic path only
   __shared__ int si[SMP_THREADS];
   __shared__ uint32_t sk[SMP_THREADS];
   __shared__ float red[2 * 3 * (SMP_THREADS / 64)];
   __shared__ int found;
   const int tid = threadIdx.x;
-  const float inv_temp = cfg->inv_temp;
+  // Nothing the kernel reads depends on anything but the token's embedding row on the token: requested up front, a memory
+  // round trip instead of one behind the other.
+  const float inv_temp = cfg->inv_temp, logit0 = logits[min(tid, vocab - 1)];
+  const int last = min(tid, nparts - 1), pos = st->pos, n_prompt = st->n_prompt, steps = st->steps, fault = st->fault;
+  const float v0 = pval[last];
+  const int i0 = pidx[last];
   int tok;
+  // what the step leaves in x_next is kept (d <= SMP_THREADS * 8)
+  if (x_next && tid * 8 < d) {
+    *as_global(reinterpret_cast<f4*>(x_keep + tid * 8)) = *as_global(reinterpret_cast<const f4*>(x_next + tid * 8));
+    *as_global(reinterpret_cast<f4*>(x_keep + tid * 8 + 4)) = *as_global(reinterpret_cast<const f4*>(x_next + tid * 8 + 4));
+  }
 
-  if (inv_temp == 0.f || vocab > SMP_MAX_VOCAB) {
+  if (inv_temp == 0.f || vocab > SMP_THREADS * PER) {
     // ---- greedy: reduce the LM head's per-workgroup (max, lowest index) candidates
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    for (int i = tid; i < nparts; i += SMP_THREADS) {
-      const float v = pval[i];
-      const int ix = pidx[i];
+    auto offer = [&](float v, int ix) {
       if (v > bv || (v == bv && ix < bi)) { bv = v; bi = ix; }
-    }
-    sv[tid] = bv;
-    si[tid] = bi;
-    __syncthreads();
-    for (int off = SMP_THREADS / 2; off > 0; off >>= 1) {
-      if (tid < off) {
-        const float v = sv[tid + off];
-        const int ix = si[tid + off];
-        if (v > sv[tid] || (v == sv[tid] && ix < si[tid])) { sv[tid] = v; si[tid] = ix; }
-      }
-      __syncthreads();
-    }
-    tok = si[0];
+    };
+    offer(v0, i0);                                  // (a thread without a candidate offers the last one again)
+    for (int i = tid + SMP_THREADS; i < nparts; i += SMP_THREADS) offer(pval[i], pidx[i]);
+    tok = smp_block_argmax(bv, bi, red, si);
     if ((unsigned)tok >= (unsigned)vocab) tok = 0;   // no candidate (every logit NaN): still a valid id
   } else {
-    tok = smp_draw_token(logits, vocab, cfg, (uint32_t)(prefill ? 0 : st->steps), smp_z, si, sk, red, &found);
+    tok = smp_draw_token<PER>(logits, vocab, cfg, (uint32_t)(prefill ? 0 : steps), logit0, smp_z, si, sk, red, &found);
   }
 
-  if (tid == 0) found = tok;        // one value for every thread, whichever path chose it
-  __syncthreads();
-  tok = found;
-  if (x_next) {
-    for (int i = tid * 8; i < d; i += SMP_THREADS * 8) {
-      const h8 e = load_h8(emb + (size_t)tok * d + i);
-      *reinterpret_cast<f4*>(x_keep + i) = *reinterpret_cast<const f4*>(x_next + i);
-      *reinterpret_cast<f4*>(x_keep + i + 4) = *reinterpret_cast<const f4*>(x_next + i + 4);
-      *reinterpret_cast<f4*>(x_next + i) = f4{(float)e[0], (float)e[1], (float)e[2], (float)e[3]};
-      *reinterpret_cast<f4*>(x_next + i + 4) = f4{(float)e[4], (float)e[5], (float)e[6], (float)e[7]};
-    }
+  tok = __builtin_amdgcn_readfirstlane(tok);        // one value for every thread, whichever path chose it
+  if (x_next && tid * 8 < d) {
+    const h8 e = load_h8(emb + (size_t)tok * d + tid * 8);
+    *as_global(reinterpret_cast<f4*>(x_next + tid * 8)) = f4{(float)e[0], (float)e[1], (float)e[2], (float)e[3]};
+    *as_global(reinterpret_cast<f4*>(x_next + tid * 8 + 4)) = f4{(float)e[4], (float)e[5], (float)e[6], (float)e[7]};
   }
 
   if (tid == 0) {
-    int idx;
-    if (prefill) {
-      st->pos = st->pos + st->n_prompt;
-      idx = 0;
-      st->steps = 1;
-    } else {
-      st->pos = st->pos + 1;
-      idx = st->steps;
-      st->steps = idx + 1;
-    }
+    const int idx = prefill ? 0 : steps;
+    st->pos = pos + (prefill ? n_prompt : 1);
+    st->steps = idx + 1;
     st->next_token = tok;
-    if (idx < ring_size) host_ring[idx] = st->fault ? -1 : tok;
+    if (idx < ring_size) host_ring[idx] = fault ? -1 : tok;
   }
 }
