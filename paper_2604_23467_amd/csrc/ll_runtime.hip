@@ -191,12 +191,12 @@ constexpr int tile_rows(const TileShape& t) { return 32 * t.wm * t.mt; }
 constexpr TileShape tile_shape(int mode, int Mb, bool alt) {
   if (mode == SK_QKV && !alt) {
     return Mb <= 64 ? TileShape{2, 2, 1, 2, 4, 3, true} : Mb <= 128 ? TileShape{4, 1, 1, 2, 8, 3, true}
-         : Mb <= 192 ? TileShape{2, 2, 3, 2, 8, 3, true} : Mb <= 256 ? TileShape{2, 2, 2, 3, 4, 3, false}
+         : Mb <= 192 ? TileShape{2, 2, 3, 2, 4, 3, true} : Mb <= 256 ? TileShape{2, 2, 2, 3, 4, 3, false}
          : Mb <= 384 ? TileShape{2, 2, 3, 3, 4, 3, false} : Mb <= 512 ? TileShape{4, 1, 2, 3, 4, 3, false}
          : TileShape{4, 1, 2, 6, 4, 3, false};
   }
   if (mode != SK_RES) {
-    return Mb <= 64 ? TileShape{2, 2, 1, 3, 4, 3, true} : Mb <= 128 ? TileShape{4, 1, 1, 3, 4, 3, true}
+    return Mb <= 64 ? TileShape{2, 2, 1, 3, 4, 3, true} : Mb <= 128 ? TileShape{2, 2, 2, 3, 4, 3, true}
          : Mb <= 192 ? TileShape{2, 2, 3, 3, 4, 3, true} : Mb <= 256 ? TileShape{4, 1, 2, 3, 4, 3, true}
          : Mb <= 384 ? TileShape{4, 1, 3, 3, 4, 3, true} : TileShape{4, 1, 2, 6, 4, 3, false};
   }

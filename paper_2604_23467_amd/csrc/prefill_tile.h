@@ -23,6 +23,7 @@
 //   gate/up  34.4 39.6 49.2 55.0 74.1      -> 31.2 39.2 46.5 49.7 65.0
 //   O         9.6 12.3 16.0 18.2 22.6 25.9 ->  9.2 11.3 14.6 16.2 20.7 24.0
 //   down     20.3 26.1 32.0 36.5 42.1 48.0 -> 19.5 23.4 29.3 31.1 42.3 45.2
+// (gate/up at 128 and Q/K/V at 192 and 256 rows have gained again since, see pt_pairs)
 // At 512 rows and more the matrix instructions
 // are the larger part (gate/up at 512 rows: 98 k of 114 k cycles in the K loop) and the chip runs them at 1.6-1.8
 // GHz; tiles of 256 x 192 leave no registers for a second wave per SIMD, and keep the old way.  LDS holds only the weights
@@ -167,12 +168,20 @@ __host__ __device__ constexpr PtWaits pt_waits(int NS, int PP, int WS, int MT, i
 
 // k16 steps by which a wave requests its activations ahead, in tiles that are fed by other waves: a stage's, where that is
 // what the measured tiles wanted (gate/up at 250 rows: 8 steps 49.7 us, 4 52.6; Q/K/V at 100: 16 steps 27.2, 4 29.2), but
-// 4 for the residual projections (down at 250 rows: 31.1, 8 32.3), in stages of a single row block and 8 steps (gate/up
-// at 100: 39.2, 8 42.4), and where three row blocks leave no registers for more
+// 4 for the residual projections (down at 250 rows: 31.1, 8 32.3) and where three row blocks leave no registers for more
 __host__ __device__ constexpr int pt_look(int mode, int wk, int mt, int s32) {
   const int ws = s32 * 2 / wk;
-  return mode == SK_RES || (mt == 1 && s32 == 4) || (wk == 1 && mt >= 3) ? (ws < 4 ? ws : 4) : ws;
+  return mode == SK_RES || (wk == 1 && mt >= 3) ? (ws < 4 ? ws : 4) : ws;
 }
+// Q/K/V and gate/up in tiles of six accumulator blocks per wave with K split between the waves have registers for two stages
+// of activations: those of two steps are requested together, a stage ahead and more.  us, step by step -> in pairs: gate/up
+// at 100 rows 42.2 (as 128 x 96 without the split, its best step by step) -> 36.4, Q/K/V at 180 38.2 (8 K steps a stage) -> 37.0,
+// at 250 40.7 -> 38.4.  Requested in fours: 37.5, 38.6 and 39.1; whole stages at once 39.9 and 40.5 (100 and 250 rows); two stages ahead
+// step by step 40.7 (250).  In the other tiles that have the registers nothing is gained (O and down at 50 .. 250 rows, Q/K/V at
+// 50: within 1 %) or it loses (Q/K/V at 100 rows 28.1 -> 29.9, gate/up at 50 31.8 -> 32.2); pairs without the second set of
+// registers, which are requested later, lose everywhere.
+__host__ __device__ constexpr bool pt_pairs(int mode, int wk, int mt, int nb) { return mode != SK_RES && wk == 2 && mt * nb == 6; }
+template <int H> struct PtHalf { static constexpr int value = H; };
 
 // Tile of 32 WM MT rows x 32 NB columns, four waves that multiply: WM along the rows (MT row blocks of 32 each), WK = 2
 // splitting every K step in half between two waves per row group (half the LDS reads; the two halves of the
@@ -294,10 +303,11 @@ __global__ __launch_bounds__(pt_threads(MT, NB), 1) void pf_tile_kernel(TileArgs
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  constexpr int LOOK = FED ? pt_look(MODE, WK, MT, S32) : WS;
+  constexpr bool PAIRS = FED && pt_pairs(MODE, WK, MT, NB);
+  constexpr int LOOK = FED && !PAIRS ? pt_look(MODE, WK, MT, S32) : WS;
   static_assert(WS % LOOK == 0, "a step's registers are the same in every stage");
   static_assert(WS % 2 == 0, "the fragment double buffer keeps its parity across stages");
-  h8 fa[LOOK][MT], fb[2][NB];
+  h8 fa[PAIRS ? 2 * WS : LOOK][MT], fb[2][NB];
   auto load_b = [&](int stage, int ws, h8 (&f)[NB]) {
     const int s = WK == 1 ? ws >> 1 : ws, ks = WK == 1 ? ws & 1 : wk;
     const half_t* base = pt_lds + stage * STAGE + (s * 2 * NB + (r >> 4)) * 512 + ((ks * 2 + half) * 16 + (r & 15)) * 8;
@@ -316,7 +326,9 @@ __global__ __launch_bounds__(pt_threads(MT, NB), 1) void pf_tile_kernel(TileArgs
     load_b(0, 0, fb[0]);
     __builtin_amdgcn_sched_barrier(0);
     int stage = 0;
-    for (int it = 0; it < cnt; ++it) {
+    // stage it, its activations in the registers from CUR on (PAIRS: the next stage's go to the other half)
+    auto steps = [&](int it, auto half_of) {
+      constexpr int CUR = decltype(half_of)::value * WS;
       const __amdgpu_buffer_rsrc_t ar1 = a_rsrc(stage_k(it + 1));
       const int nstage = stage + 1 == NS ? 0 : stage + 1;
 #pragma unroll
@@ -334,16 +346,27 @@ __global__ __launch_bounds__(pt_threads(MT, NB), 1) void pf_tile_kernel(TileArgs
 #pragma unroll
         for (int t = 0; t < MT * NB; ++t) {
           const int mt = t / NB, nb = t % NB;
-          acc[mt][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[ws & 1][nb], fa[ws % LOOK][mt], acc[mt][nb], 0, 0, 0);
+          acc[mt][nb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[ws & 1][nb], fa[CUR + ws % LOOK][mt], acc[mt][nb], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
-          if (nb == NB - 1) {
+          if (!PAIRS && nb == NB - 1) {
             fa[ws % LOOK][mt] = ws + LOOK < WS ? load_a(ar, ws + LOOK, mt) : load_a(ar1, ws + LOOK - WS, mt);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
+        if (PAIRS && (ws & 1) == 0) {
+#pragma unroll
+          for (int w2 = ws; w2 < ws + 2; ++w2)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) fa[WS - CUR + w2][mt] = load_a(ar1, w2, mt);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
       stage = nstage;
       ar = ar1;
+    };
+    for (int it = 0; it < cnt; ++it) {
+      steps(it, PtHalf<0>());
+      if (PAIRS && ++it < cnt) steps(it, PtHalf<PAIRS>());
     }
   } else {
     auto slot_of = [](int idx) { return pt_slot(idx, WS, PP); };
