@@ -231,7 +231,7 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
   const __amdgpu_buffer_rsrc_t wr = frag.block(a.Wf, blockIdx.x);
   // Two token blocks: a batch's weights go out together, its activations behind them.  A CU's loads come back in order, so
   // activations (L2) that stand between weights (HBM) wait as long as these; 25 rows of the 7B shape, dealt step by step ->
-  // this, us: down 23.4 -> 22.0, O 10.5 -> 10.1 (batches of 4, 6 or 16 steps, weights a batch earlier, waves in step: 22.0 ..
+  // this, us: down 23.3 -> 22.3, O 10.3 -> 10.05 (batches of 4 or 6 steps, weights a batch earlier, waves in step: 22.0 ..
   // 22.9).  With one block it is the other way round: O 8.7 us step by step, 9.0 this way, down the same.
   constexpr bool GROUPED = FRAG && TB == 2;
   auto issue = [&](int s0, h8 (&A)[U], h8 (&B)[U][TB]) {
