@@ -254,7 +254,8 @@ int ll_batch_open(int32_t max_batch, int32_t page_tokens, int32_t n_pages, void 
  * pages, stores the first generated token in *first_token and returns the slot (>= 0) the sequence
  * occupies.  LL_E_CAPACITY when no slot or not enough pages are free, or n + 1 > max_seq; those and
  * the argument checks come first and leave everything as it was.  Past them the single-sequence
- * context is replaced, whether or not the prefill then succeeds. */
+ * context is replaced, whether or not the prefill then succeeds; one that fails takes no slot and no
+ * pages. */
 int32_t ll_batch_add(const int32_t *tokens, int32_t n, int32_t *first_token);
 /* One decode step of every sequence in the batch.  out_tokens (host, max_batch entries) receives
  * the new token of every occupied slot and -1 for free slots.  A sequence that crosses a page border

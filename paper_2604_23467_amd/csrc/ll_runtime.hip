@@ -1430,6 +1430,17 @@ int push_batch_state(Instance* I, int first, int count, const DevState* st = nul
   return LL_OK;
 }
 
+// Frees a slot in the host mirrors; its pages go back in the order in which they would be taken again
+void clear_slot(Batch* B, int slot) {
+  B->free_pages.insert(B->free_pages.end(), B->pages[slot].rbegin(), B->pages[slot].rend());
+  B->pages[slot].clear();
+  for (int i = 0; i < B->L.pt_stride; ++i) B->h_table[slot * B->L.pt_stride + i] = 0;
+  B->h_state->pos[slot] = 0;
+  B->h_state->next_token[slot] = 0;
+  B->h_state->active[slot] = 0;
+  B->h_state->steps[slot] = 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1980,15 +1991,26 @@ int32_t ll_batch_add(const int32_t* tokens, int32_t n, int32_t* first_token) {
   B->h_state->pos[slot] = n;
   B->h_state->active[slot] = 1;
   B->h_state->steps[slot] = 1;                  // the prefill drew with index 0
-  if ((rc = push_batch_state(I, slot, 1, I->state())) != LL_OK) return rc;
-  const ll_config& c = I->cfg;
-  hipLaunchKernelGGL(bt_scatter_kernel, dim3(n, c.n_layers * 2), dim3(LL_WG), 0, I->stream, I->kcache(0),
-                     I->L.kv_layer_halves, c.max_seq, B->kpool(0), B->L.kv_layer_halves, B->L.pool_rows,
-                     B->at<int>(B->L.page_table), B->L.pt_stride, B->page_tokens, slot, c.n_heads, c.head_dim);
-  HIPCHK(hipGetLastError());
-  if ((rc = wait_tokens(I->stream, I->host_ring, 1)) != LL_OK) return rc;
-  const int32_t t1 = prefill_finish(I, n, I->pf.logits);
-  if (t1 < 0) return t1;
+  auto join = [&]() -> int32_t {
+    int e = push_batch_state(I, slot, 1, I->state());
+    if (e != LL_OK) return e;
+    const ll_config& c = I->cfg;
+    hipLaunchKernelGGL(bt_scatter_kernel, dim3(n, c.n_layers * 2), dim3(LL_WG), 0, I->stream, I->kcache(0),
+                       I->L.kv_layer_halves, c.max_seq, B->kpool(0), B->L.kv_layer_halves, B->L.pool_rows,
+                       B->at<int>(B->L.page_table), B->L.pt_stride, B->page_tokens, slot, c.n_heads, c.head_dim);
+    HIPCHK(hipGetLastError());
+    if ((e = wait_tokens(I->stream, I->host_ring, 1)) != LL_OK) return e;
+    return prefill_finish(I, n, I->pf.logits);
+  };
+  const int32_t t1 = join();
+  if (t1 < 0) {                                 // the caller never hears the slot's number: nothing of it stays
+    const std::string why = g_err;
+    clear_slot(B, slot);
+    (void)push_batch_state(I, slot, 1);
+    (void)hipStreamSynchronize(I->stream);      // the queue still reads the pinned mirrors and the staged prompt
+    g_err = why;
+    return t1;
+  }
   B->h_state->next_token[slot] = t1;
   *first_token = t1;
   return slot;
@@ -2000,13 +2022,7 @@ int ll_batch_remove(int32_t slot) {
   if (!B) return fail(LL_E_STATE, "ll_batch_remove: call ll_batch_open first");
   if (slot < 0 || slot >= B->max_batch || !B->h_state->active[slot])
     return fail(LL_E_BAD_ARG, "ll_batch_remove: slot %d holds no sequence", slot);
-  for (int pg : B->pages[slot]) B->free_pages.push_back(pg);
-  B->pages[slot].clear();
-  for (int i = 0; i < B->L.pt_stride; ++i) B->h_table[slot * B->L.pt_stride + i] = 0;
-  B->h_state->pos[slot] = 0;
-  B->h_state->next_token[slot] = 0;
-  B->h_state->active[slot] = 0;
-  B->h_state->steps[slot] = 0;
+  clear_slot(B, slot);
   int rc = push_batch_state(g, slot, 1);
   if (rc != LL_OK) return rc;
   HIPCHK(hipStreamSynchronize(g->stream));
