@@ -241,6 +241,10 @@ const char *ll_last_error(void);
  * caller and kept alive until ll_batch_close (or ll_shutdown, which closes the batch).  The calls
  * share the instance's stream and prefill scratch: ll_batch_add runs the prompt through the
  * single-sequence prefill, which REPLACES the context of ll_prefill / ll_decode_step.
+ * ll_batch_step and ll_batch_add poll pinned memory for their tokens: the calling thread is busy until these are there (for
+ * at most 20 ms, then the runtime's own wait takes over).  When ll_batch_step returns, its tokens are there but its last
+ * kernel may not have retired yet: work on another stream that touches the pool needs an ordering of its own behind the
+ * instance's stream, and an error that the runtime reports late comes with the next call.
  * Errors: negative LL_E_* codes, state unchanged; not thread-safe. */
 
 /* Bytes of `pool` for pages of page_tokens positions, n_pages of them (page 0 is reserved, so

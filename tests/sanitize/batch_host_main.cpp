@@ -192,6 +192,31 @@ int main() {
   CHECK(ll_batch_add(prompt, 14, &first) == 0 && ll_batch_add(prompt, 3, &first) == 1 && ll_batch_remove(0) == LL_OK);
   if (joins_that_fail(B)) return 1;
 
+  // a step's tokens: there at once, late, only once the stream has been waited for
+  for (fake::When when : {fake::AT_ONCE, fake::LATE, fake::IN_SYNC}) {
+    const Books before(B);
+    fake::reset();
+    fake::when = when;
+    fake::token = 20 + when;
+    fake::syncs = 0;
+    const auto t0 = std::chrono::steady_clock::now();
+    CHECK(ll_batch_step(out) == LL_OK);
+    const auto took = std::chrono::steady_clock::now() - t0;
+    CHECK(out[1] == 20 + when && B->h_state->pos[1] == before.state.pos[1] + 1 && B->h_state->next_token[1] == 20 + when);
+    CHECK(fake::syncs == (when == fake::IN_SYNC) && (when != fake::IN_SYNC || took > std::chrono::milliseconds(kPollMs)));
+  }
+  // never: the step is reported, and the lists are those from before it, also where it was to take a page
+  while (B->h_state->pos[1] % 8) { fake::reset(); CHECK(ll_batch_step(out) == LL_OK); }
+  for (const void* bad : {(const void*)nullptr, fake::id(&bt_select_kernel<1>)}) {
+    const Books before(B);
+    fake::reset();
+    fake::when = fake::NEVER;
+    fake::sync_fails_behind = bad;
+    CHECK(ll_batch_step(out) == LL_E_HIP && Books(B) == before);
+  }
+  fake::reset();
+  CHECK(ll_batch_step(out) == LL_OK && B->pages[1].size() == 2);
+
   CHECK(ll_shutdown() == LL_OK);
   std::free(pool);
   std::free(ws);

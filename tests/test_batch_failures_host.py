@@ -1,5 +1,6 @@
 """Batched decoding's host side under failures (no GPU): a join that fails at any point leaves no slot, page or table entry
-behind.  The runtime is compiled for the host with made-up HIP calls and the sanitizers, see sanitize/batch_host_main.cpp."""
+behind; a step's tokens are taken whether they come at once, late or with the stream's end, and their absence is reported.  The
+runtime is compiled for the host with made-up HIP calls and the sanitizers, see sanitize/batch_host_main.cpp."""
 import os
 
 import pytest
