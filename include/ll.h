@@ -109,7 +109,8 @@ enum {
 };
 
 /* Model shape.  Constraints: n_heads * head_dim == d_model; head_dim is 64 or
- * 128; d_model and ffn_hidden are multiples of 8; max_seq >= 2. */
+ * 128; d_model and ffn_hidden are multiples of 8; max_seq >= 2.  ll_init also refuses d_model above
+ * 8192 and ffn_hidden above 12288. */
 typedef struct {
   int32_t n_layers, d_model, n_heads, head_dim, ffn_hidden, vocab, max_seq;
   float rope_theta; /* RoPE base, e.g. 10000 */

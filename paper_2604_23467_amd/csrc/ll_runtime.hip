@@ -62,6 +62,10 @@ constexpr int kAttnMaxSplits = 16;
 constexpr int kMaxPromptBucket = 1024;   // rows of the largest prefill graph; longer prompts go through in chunks of it
 constexpr int kGemmMinSlabs = 8;
 constexpr size_t kAlign = 256;
+// Widest models that every kernel holds: the GEMVs' input vector in 64 KB of LDS (with the norm's gains where there are any),
+// a row in the registers of one workgroup of the prefill's norm and of the selection, which copies and gathers rows
+constexpr int kMaxDModel = 8192, kMaxFfnHidden = 12288;
+static_assert(kMaxDModel <= SMP_THREADS * 8 && kMaxDModel <= PF_NORM_THREADS * 4 * PF_NORM_CHUNKS, "a thread's share of a row");
 constexpr size_t kAttnOLdsBytes = 9 * 512 * sizeof(float);   // staged o of the fused attention + O kernel (8 chunks + a zero chunk)
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -571,12 +575,13 @@ struct Instance {
 Instance* g = nullptr;
 int g_warm_up_give_up = INT_MAX;   // test hook: the same for the warm-up of the next ll_init
 
-size_t gemv_lds_bytes(int K, bool norm) {
+constexpr size_t gemv_lds_bytes(int K, bool norm) {
   const int nch = (K + 511) / 512;
   const int nchp = (nch + kGemvU - 1) / kGemvU * kGemvU;
   // input vector, reduction scratch, and for the normalising projections the staged gains
   return ((size_t)nchp * 512 + 16) * sizeof(float) + (norm ? (size_t)nch * 512 * sizeof(half_t) : 0);
 }
+static_assert(gemv_lds_bytes(kMaxDModel, true) <= 64 * 1024 && gemv_lds_bytes(kMaxFfnHidden, false) <= 64 * 1024, "LDS of a GEMV");
 
 struct ProfScope {
   Instance* I;
@@ -1471,8 +1476,10 @@ int ll_init(const ll_config* cfg, const ll_weights* w, void* workspace, size_t w
     return fail(LL_E_WORKSPACE, "ll_init: workspace has %zu bytes, %zu needed", workspace_bytes, L.total);
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign)
     return fail(LL_E_WORKSPACE, "ll_init: workspace must be %zu-byte aligned", kAlign);
-  if (gemv_lds_bytes(cfg->ffn_hidden, false) > 64 * 1024 || gemv_lds_bytes(cfg->d_model, true) > 64 * 1024)
-    return fail(LL_E_BAD_CONFIG, "ll_init: d_model / ffn_hidden too large for the LDS-staged GEMV (at most 12288)");
+  if (cfg->d_model > kMaxDModel)
+    return fail(LL_E_BAD_CONFIG, "ll_init: d_model = %d, at most %d", cfg->d_model, kMaxDModel);
+  if (cfg->ffn_hidden > kMaxFfnHidden)
+    return fail(LL_E_BAD_CONFIG, "ll_init: ffn_hidden = %d, at most %d", cfg->ffn_hidden, kMaxFfnHidden);
   if (cfg->n_heads > 256)
     return fail(LL_E_BAD_CONFIG, "ll_init: n_heads = %d, at most 256 (two attention workgroups per head)", cfg->n_heads);
 

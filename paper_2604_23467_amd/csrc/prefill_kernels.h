@@ -46,8 +46,8 @@ __device__ __forceinline__ f4 pf_slice_sum(const float* p, int np, size_t slice_
 // here, X is stored back, and the norm is taken of the sum.  Rows past the prompt
 // give zero operands.  frag_tb != 0 writes the operands in the short-prompt
 // kernels' fragment-major layout.
-// Everything it reads is requested up front and kept in registers, PF_NORM_CHUNKS pieces of a thread (d_model up to 12288, more
-// than any instance has).  At 50 rows it is one memory round trip and a barrier long (5.0 us a launch), at 500 the slices'
+// Everything it reads is requested up front and kept in registers, PF_NORM_CHUNKS pieces of a thread (d_model up to 12288; an
+// instance has at most 8192).  At 50 rows it is one memory round trip and a barrier long (5.0 us a launch), at 500 the slices'
 // way between XCDs (11.2, 4 TB/s); the first one takes 4.6 / 6.4 / 7.6 us at 50 / 250 / 500 rows where a gather kernel and a
 // norm took 5.5 / 9.5 / 12.8.
 #define PF_NORM_THREADS 1024
