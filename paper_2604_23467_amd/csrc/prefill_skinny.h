@@ -54,7 +54,7 @@ struct SkinnyArgs {
   const DevState* st;
   int N, K;
   float* Xres;            // RES: residual stream [rows][N] fp32, updated in place for rows < n
-  const half_t* gain_next;// RES: gain of the norm in front of the next projection (null: none follows)
+  const half_t* gain_next;// RES: gain of the norm in front of the next projection
   half_t* Xh_next;        // RES: fp16 x * gain_next, fragment-major, operand of the next projection
   float* ss_out;          // RES: [16 TB][ss_stride] per-token sums of squares of the updated residual, slot
                           //      blockIdx.x = the 16 columns of this workgroup
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
     const float* xp = a.Xres + (size_t)(tid >> 1) * N + c0;
     ex0 = *as_global(reinterpret_cast<const f4*>(xp));
     ex1 = *as_global(reinterpret_cast<const f4*>(xp + 4));
-    if (a.gain_next) egain = load_h8(a.gain_next + c0);
+    egain = load_h8(a.gain_next + c0);
   }
   if (MODE != SK_RES) {
     SkSsLoads sl;
@@ -324,19 +324,17 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
       for (int j = 0; j < 4; ++j) { v[j] += ex0[j]; v[4 + j] += ex1[j]; }
       *reinterpret_cast<f4*>(xp) = f4{v[0], v[1], v[2], v[3]};
       *reinterpret_cast<f4*>(xp + 4) = f4{v[4], v[5], v[6], v[7]};
-      if (a.gain_next) {
-        h8 xh;
+      h8 xh;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          xh[j] = (half_t)(v[j] * (float)egain[j]);
-          ss += v[j] * v[j];
-        }
-        *reinterpret_cast<h8*>(a.Xh_next + act_offset(tok, c0, N, TB)) = xh;
+      for (int j = 0; j < 8; ++j) {
+        xh[j] = (half_t)(v[j] * (float)egain[j]);
+        ss += v[j] * v[j];
       }
+      *reinterpret_cast<h8*>(a.Xh_next + act_offset(tok, c0, N, TB)) = xh;
     }
     if (tid < TB * 32) {
       ss += dpp_mov<0xB1>(ss);                     // the token's other half sits in the neighbouring lane
-      if (efin && (tid & 1) == 0 && a.gain_next) a.ss_out[(size_t)(tid >> 1) * a.ss_stride + blockIdx.x] = ss;
+      if (efin && (tid & 1) == 0) a.ss_out[(size_t)(tid >> 1) * a.ss_stride + blockIdx.x] = ss;
     }
   } else {
     for (int o = tid; o < RB * TB * 16; o += SK_THREADS) {
