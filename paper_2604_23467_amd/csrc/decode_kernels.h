@@ -43,11 +43,14 @@ struct GemvArgs {
 };
 
 // What a GEMV computes for.  The last layer of a prompt is needed for its last row only (behind the cache rows), so a prefill
-// ends in the decode kernels; its roundings are those of the rows in front of it.
+// ends in the decode kernels.  These round as the kernels of the rows in front do, or less: the attention's output enters O
+// in fp32, which those rows store as fp16.
 //   GR_STEP   a decode step: everything between two kernels is fp32
-//   GR_SHORT  last row of a prompt of at most 32 tokens: gate/up's operand is fp16(x gain), the norm factor's squares are added
-//             per 16 columns, those sums sixteen strided ones at a time and these as a tree; SwiGLU is rounded to fp16
-//   GR_LONG   last row of a longer prompt: SwiGLU is rounded to fp16
+//   GR_SHORT  last row of a prompt of at most 32 tokens: gate/up's operand is fp16(x gain) as in the rows in front, and so is
+//             the order of the norm factor's squares (per 16 columns, sixteen strided sums of these, a tree); SwiGLU is
+//             rounded to fp16
+//   GR_LONG   last row of a longer prompt: SwiGLU is rounded to fp16; gate/up's operand is x gain in fp32, the norm factor
+//             applied behind the product, where the rows in front take fp16(x factor gain)
 enum GemvRow { GR_STEP = 0, GR_SHORT = 1, GR_LONG = 2 };
 
 // The input vector is staged in LDS as fp32 in a lane-major layout: for the

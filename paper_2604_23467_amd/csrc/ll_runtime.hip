@@ -185,7 +185,8 @@ constexpr int tile_rows(const TileShape& t) { return 32 * t.wm * t.mt; }
 // square as one round allows, with K split between the waves while the rows are few.  `alt` (tile_alt() below) selects the
 // second column of shapes:
 //  * Q/K/V with more weight rows than its own smaller tiles cover in a round takes the gate/up shapes, which hold 96 or
-//    192 columns of all the bucket's rows (d_model 8192, 50 rows: 256 tiles of 96 columns 69 us, 384 of 64 columns 89 us);
+//    192 columns of all the bucket's rows (d_model 8192, 50 rows: first token of four layers 911 us, 998 in two rounds of
+//    the first shape's 64 columns);
 //  * a residual projection whose K loop can be cut into more pieces takes wider tiles (down at 512 rows: 45 us in 4
 //    pieces of 128 columns, 62 us in 2 of 64; the O projection of the 7B shape is better off with fewer slices,
 //    24.0 us in 2 pieces and 23.3 in 4, which the norm behind it has to add up).
@@ -213,9 +214,14 @@ constexpr TileShape tile_shape(int mode, int Mb, bool alt) {
   return TileShape{4, 1, 2, 4, 2, 3, false};
 }
 // Second shape or first?  Q/K/V: where the first takes more than one round.  Residual projections: where K is long, and
-// where the first shape leaves no CU for a second piece of the K loop (d_model above 4096).  Four layers, first tokens
-// of 50 / 100 / 350 rows, first shapes only -> this rule: d_model 5120 626 / 795 / 1340 -> 623 / 754 / 1219 us,
-// 6144 839 / 952 / 1618 -> 745 / 913 / 1479, 8192 1118 / 1273 / 2264 -> 979 / 1105 / 1932 (F = 12288).
+// where the first shape leaves no CU for a second piece of the K loop (d_model above 4096).  First tokens of four layers, us,
+// this rule / without the part for Q/K/V / without that for a second piece (F = 12288):
+//   d_model 5120 at 250, 350, 500 rows   873 1048 1295 /  946 1155 1381 /  884 1059 1317
+//   6144                                1043 1278 1565 / 1122 1395 1650 / 1061 1290 1585
+//   8192                                1405 1703 2138 / 1504 1834 2206 / 1466 1750 2206
+// At 50 and 100 rows Q/K/V's part gives 698 795 / 773 874 (6144) and 911 1007 / 998 1115 (8192), and the residual projections
+// have one shape up to 192 rows and above 512.  The long K: 646 776 926 with it and 660 780 932 without at 250, 350 and 500 rows
+// of the 7B shape; 473 570 674 and 481 576 661 at d_model 3072, F 8192.
 bool tile_alt(int mode, int N, int K, int Mb) {
   if (mode == SK_RES && K >= 2 * N) return true;
   const TileShape t = tile_shape(mode, Mb, false);
@@ -1132,10 +1138,11 @@ void destroy(Instance* I) {
 }
 
 // Waits until `count` words of pinned host memory that were kNoToken hold the tokens of queued work.  The words are polled:
-// the runtime's wait sleeps after some 200 us, and waking up costs 13 us a call (batched steps of four layers of the 7B
-// shape 389 -> 375 us).  For calls that are followed by more queued work, like a batch's: the runtime's own wait then finds
-// out about the work's end later, which costs a caller who does wait as much (a prompt of 25 tokens launched kernel by
-// kernel and its logits read back: 409 -> 425 us).  Work that takes longer than kPollMs is left to the runtime.
+// the runtime's wait sleeps after some 200 us, and waking up costs 13 us a call (16 sequences of four layers of the 7B shape
+// joining, 64 steps, logits read back and leaving: 34.04 -> 33.23 ms, 32 of them 48.78 -> 47.99).  For calls that are followed
+// by more queued work, like a batch's: the runtime's own wait then finds out about the work's end later, which costs a caller
+// who does wait as much (a prompt of 25 tokens launched kernel by kernel and its logits read back: 409 -> 425 us).  Work that
+// takes longer than kPollMs is left to the runtime.
 constexpr int kNoToken = INT_MIN, kPollMs = 20;
 int wait_tokens(hipStream_t s, const int* words, int count) {
   const volatile int* w = words;

@@ -5,8 +5,9 @@
 //
 // Every kernel is launched on a grid sized for a prompt-length bucket Mb and
 // reads the true n from DevState, so one captured graph per bucket serves all
-// prompts that fit it.  Rows >= n are zero on entry and never reach the KV
-// cache or the logits.  A prompt longer than the largest bucket is fed in
+// prompts that fit it.  Rows >= n are zero operands for the projections beyond
+// 32 rows, whatever the residual stream holds there, and never reach the KV cache
+// or the logits.  A prompt longer than the largest bucket is fed in
 // chunks: DevState.pos holds the number of positions already cached (p0), row r
 // of the chunk sits at position p0 + r, and attention also covers the p0 keys
 // of the earlier chunks.
