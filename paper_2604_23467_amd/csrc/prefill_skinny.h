@@ -198,6 +198,14 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
 #pragma unroll
   for (int t = 0; t < TB; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
 
+  // K range of this wave, in 32-wide MFMA steps.  It and the descriptors stand in front of the branch below: behind it the
+  // compiler takes them for lane values and wraps every load into a loop over the lanes (batch of 32: 1 % a step).
+  const int ksteps = (K + 31) >> 5;
+  const int per_wave = (ksteps + SK_WAVES - 1) / SK_WAVES;
+  const int s_begin = wave * per_wave, s_end = min(s_begin + per_wave, ksteps);
+  const SkFrag<TB> frag(a, lane, s_end);
+  const __amdgpu_buffer_rsrc_t wr = frag.block(a.Wf, blockIdx.x);
+
   // SK_RES: thread o < 32 TB finishes rows 8 (o & 1) .. + 8 of token o >> 1.  What it adds to
   // (the residual) and scales by (the next norm's gain) does not depend on the contraction, so
   // it is fetched now and has long arrived when the sums are ready.
@@ -218,17 +226,12 @@ __global__ __launch_bounds__(SK_THREADS, 1) void pf_skinny_kernel(SkinnyArgs a) 
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // K range of this wave, in 32-wide MFMA steps, walked in batches of U steps.  Two batches
+  // The K range is walked in batches of U steps.  Two batches
   // of registers alternate, so a batch's loads are in flight while the previous one is
   // multiplied.  A step outside the range (or a lane's 8 halves past K) re-reads the row
   // start and takes its B fragment from a block of zeros: no load is ever predicated.
-  const int ksteps = (K + 31) >> 5;
-  const int per_wave = (ksteps + SK_WAVES - 1) / SK_WAVES;
-  const int s_begin = wave * per_wave, s_end = min(s_begin + per_wave, ksteps);
   constexpr int U = 8;
   h8 fa[2][U], fb[2][U][TB];
-  const SkFrag<TB> frag(a, lane, s_end);
-  const __amdgpu_buffer_rsrc_t wr = frag.block(a.Wf, blockIdx.x);
   // Two token blocks: a batch's weights go out together, its activations behind them.  A CU's loads come back in order, so
   // activations (L2) that stand between weights (HBM) wait as long as these; 25 rows of the 7B shape, dealt step by step ->
   // this, us: down 23.3 -> 22.3, O 10.3 -> 10.05 (batches of 4 or 6 steps, weights a batch earlier, waves in step: 22.0 ..
